@@ -6,6 +6,8 @@
 // bucket code, the caller still picks it at run time.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -136,6 +138,9 @@ struct cf_filter {
     Launchers L;
     int grid_cap;         // blocks of the query, delete and whole-table launches
     int insert_grid_cap;  // blocks of an insert launch
+    bool may_partition;   // false: the caller fixed the launch shape
+    char *bulk;           // workspace of the partitioned insert
+    uint64_t bulk_bytes;
     bool owns_table;     // false for a table in caller memory (cf_create_in)
 };
 
@@ -182,6 +187,141 @@ cf_status grow_queue(cf_filter *f, uint64_t n, hipStream_t s) {
                     (unsigned long long)want);
     }
     f->queue_cap = want;
+    return CF_OK;
+}
+
+// ------------------------------------------------- partitioned insert
+// (cf_bulk.hpp)
+
+// Layout of one pass of `len` keys.
+struct BulkPlan {
+    uint32_t shift, parts;      // parts of 2^shift buckets
+    uint32_t bins, fine;        // bins of 2^fine parts; fine = 0: a bin is a part
+    uint32_t cap1, cap2;        // entries per run of a bin, per part (fine > 0)
+    uint32_t list_cap;
+    uint64_t cursors;           // words cleared before a pass: cursors, overflow count
+    uint64_t o_cur, o_listn, o_a, o_a32, o_b, o_b32, o_list, o_ovl, bytes;
+};
+
+constexpr uint64_t kPartBytes = 64 << 10;
+constexpr uint64_t kMinPartBytes = 1 << 10;
+constexpr uint32_t kWantParts = 256;
+constexpr uint32_t kOneLevelBins = 256;
+constexpr uint64_t kMinBulkKeys = 1 << 16;
+constexpr uint32_t kRestExtra = 64;  // blocks on the overflow list
+
+uint64_t slots_of(const cf_filter *f) { return f->p.num_buckets * f->p.slots_per_bucket; }
+
+bool bulk_wanted(const cf_filter *f, uint64_t n) {
+    return f->may_partition && n >= kMinBulkKeys &&
+           std::min(n, cfk::kMaxBulkKeys) >= slots_of(f) / 8;
+}
+
+uint32_t bulk_cap(double mean) {
+    return (uint32_t(mean + 8 * std::sqrt(mean) + 16) + 15u) & ~15u;
+}
+
+BulkPlan bulk_plan(const cf_filter *f, uint64_t len) {
+    const uint64_t m = f->p.num_buckets, bucket = uint64_t(f->p.slots_per_bucket) * f->p.fp_bits / 8;
+    BulkPlan p{};
+    while ((bucket << (p.shift + 1)) <= kPartBytes) ++p.shift;
+    auto parts_at = [&](uint32_t s) { return (m + (1ull << s) - 1) >> s; };
+    while (parts_at(p.shift) < kWantParts && (bucket << p.shift) > kMinPartBytes) --p.shift;
+    p.parts = uint32_t(parts_at(p.shift));
+    while (p.parts > kOneLevelBins && (1u << (2 * p.fine)) < p.parts) ++p.fine;
+    p.bins = (p.parts + (1u << p.fine) - 1) >> p.fine;
+    const double share = double(1ull << (p.shift + p.fine)) / double(m);  // of a bin
+    const uint64_t tiles = (len + cfk::kSplitTile - 1) / cfk::kSplitTile;
+    const uint64_t per_run = (tiles + cfk::kBulkSegs - 1) / cfk::kBulkSegs * cfk::kSplitTile;
+    p.cap1 = bulk_cap(std::min(1.0, share) * double(std::min(per_run, len)));
+    p.cap2 = p.fine ? bulk_cap(double(len) * double(1ull << p.shift) / double(m)) : 0;
+    p.list_cap = p.fine ? p.cap2 : cfk::kBulkSegs * p.cap1;
+    const uint64_t wide = f->p.fp_bits == 32 ? 4 : 0;
+    const uint64_t n1 = uint64_t(p.bins) * cfk::kBulkSegs * p.cap1;
+    const uint64_t n2 = uint64_t(p.parts) * p.cap2;
+    const uint64_t lists = uint64_t(p.parts) * p.list_cap;
+    auto take = [&](uint64_t bytes) {
+        const uint64_t o = p.bytes;
+        p.bytes += (bytes + 255) & ~uint64_t(255);
+        return o;
+    };
+    p.cursors = uint64_t(p.bins) * cfk::kBulkSegs + (p.fine ? p.parts : 0) + 1;
+    p.o_cur = take(p.cursors * 4);
+    p.o_listn = take(uint64_t(p.parts) * 4);
+    // the first level's entries, and later (they are used up by then) the
+    // eviction queues of the keys left over
+    p.o_a = take(std::max(n1 * 8, (lists + len) * 4));
+    p.o_a32 = take(n1 * wide);
+    p.o_b = take(n2 * 8);
+    p.o_b32 = take(n2 * wide);
+    p.o_list = take(lists * 4);
+    p.o_ovl = take(len * 4);
+    return p;
+}
+
+// Room for passes of min(n, kMaxBulkKeys) keys; false if there is none to be
+// had (the caller then inserts directly), which includes a stream under
+// capture.
+bool bulk_reserve(cf_filter *f, uint64_t n, hipStream_t s) {
+    const uint64_t want = bulk_plan(f, std::min(n, cfk::kMaxBulkKeys)).bytes;
+    if (want <= f->bulk_bytes) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (s && hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone) return false;
+    (void)hipDeviceSynchronize();
+    if (f->bulk) (void)hipFree(f->bulk);
+    f->bulk = nullptr;
+    f->bulk_bytes = 0;
+    if (hipMalloc(&f->bulk, want) != hipSuccess) {
+        (void)hipGetLastError();
+        f->bulk = nullptr;
+        return false;
+    }
+    f->bulk_bytes = want;
+    return true;
+}
+
+// Insert n keys in passes of equal size; the workspace is reserved.
+cf_status bulk_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *okv,
+                      uint32_t *kicks, hipStream_t s) {
+    const uint64_t passes = (n + cfk::kMaxBulkKeys - 1) / cfk::kMaxBulkKeys;
+    const cfk::LostLog log{f->lost_bucket, f->lost_tag, f->lost_cap};
+    for (uint64_t k = 0, lo = 0; k < passes; ++k) {
+        const uint64_t len = n * (k + 1) / passes - lo;
+        const BulkPlan p = bulk_plan(f, len);
+        const cfk::Ents a{reinterpret_cast<uint64_t *>(f->bulk + p.o_a),
+                          reinterpret_cast<uint32_t *>(f->bulk + p.o_a32)};
+        const cfk::Ents b{reinterpret_cast<uint64_t *>(f->bulk + p.o_b),
+                          reinterpret_cast<uint32_t *>(f->bulk + p.o_b32)};
+        uint32_t *cur1 = reinterpret_cast<uint32_t *>(f->bulk + p.o_cur);
+        uint32_t *cur2 = cur1 + uint64_t(p.bins) * cfk::kBulkSegs;
+        uint32_t *ovl_n = cur1 + p.cursors - 1;
+        uint32_t *list_n = reinterpret_cast<uint32_t *>(f->bulk + p.o_listn);
+        uint32_t *list = reinterpret_cast<uint32_t *>(f->bulk + p.o_list);
+        uint32_t *ovl = reinterpret_cast<uint32_t *>(f->bulk + p.o_ovl);
+        uint8_t *o = okv ? okv + lo : nullptr;
+        uint32_t *kk = kicks ? kicks + lo : nullptr;
+        cfk::zero_u32_kernel<<<grid_for(f, p.cursors), kBlock, 0, s>>>(cur1, p.cursors);
+        f->L.split(keys + lo, uint32_t(len), f->place, p.shift + p.fine, p.bins, cur1, a, p.cap1,
+                   o, kk, ovl, ovl_n, s);
+        if (p.fine) {
+            f->L.resplit(a, cur1, p.bins, p.cap1, p.shift, p.fine, cur2, b, p.cap2, ovl, ovl_n, s);
+            f->L.place(f->table, f->p.num_buckets, p.shift, b, cur2, 1, p.parts, p.cap2, list,
+                       list_n, p.list_cap, f->ctr, int(p.parts), s);
+        } else {
+            f->L.place(f->table, f->p.num_buckets, p.shift, a, cur1, cfk::kBulkSegs, p.bins,
+                       p.cap1, list, list_n, p.list_cap, f->ctr, int(p.parts), s);
+        }
+        // several blocks per list while there are few lists
+        const uint32_t split = std::max(1u, std::min(8u, 2048u / p.parts));
+        const cfk::Rest rest{list, list_n, ovl, ovl_n, p.list_cap, p.parts, split, kRestExtra};
+        f->L.ins(f->table, f->place, keys + lo, len, o, kk, f->ctr,
+                 reinterpret_cast<uint32_t *>(f->bulk + p.o_a), 0, log, f->p.max_evict, f->p.seed,
+                 rest, int(p.parts * split + kRestExtra), s);
+        const cf_status st = check_launch("insert (partitioned)");
+        if (st != CF_OK) return st;
+        lo += len;
+    }
     return CF_OK;
 }
 
@@ -249,11 +389,15 @@ static cf_status create_impl(const cf_params *params, void *table, cf_filter **o
     // per compute unit, then grid-stride), inserts with 128 blocks per
     // compute unit (fewer keys per block shorten each block's eviction tail;
     // still fewer leave too few keys to overlap it with).
+    f->may_partition = true;
     f->grid_cap = cus * 1024;
     f->insert_grid_cap = cus * 128;
     if (const char *env = getenv("CF_GRID_PER_CU")) {
         const int v = atoi(env);
-        if (v > 0 && v <= 1024) f->grid_cap = f->insert_grid_cap = cus * v;
+        if (v > 0 && v <= 1024) {
+            f->grid_cap = f->insert_grid_cap = cus * v;
+            f->may_partition = false;
+        }
     }
     f->owns_table = table == nullptr;
     f->table = table;
@@ -308,6 +452,7 @@ cf_status cf_destroy(cf_filter *f) {
     if (f->lost_bucket) (void)hipFree(f->lost_bucket);
     if (f->lost_tag) (void)hipFree(f->lost_tag);
     if (f->queue) (void)hipFree(f->queue);
+    if (f->bulk) (void)hipFree(f->bulk);
     delete f;
     return CF_OK;
 }
@@ -315,6 +460,9 @@ cf_status cf_destroy(cf_filter *f) {
 cf_status cf_reserve(cf_filter *f, uint64_t max_batch) {
     if (!f) return fail(CF_EINVAL, "filter is NULL");
     DeviceGuard g(f->device);
+    // batches that go partitioned need no queue; those below the rule do
+    if (bulk_wanted(f, max_batch) && bulk_reserve(f, max_batch, nullptr))
+        max_batch = std::min(max_batch, std::max(slots_of(f) / 8, kMinBulkKeys));
     return grow_queue(f, max_batch, nullptr);
 }
 
@@ -324,6 +472,7 @@ cf_status cf_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *okv
     if (st != CF_OK || n == 0) return st;
     DeviceGuard g(f->device);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (bulk_wanted(f, n) && bulk_reserve(f, n, s)) return bulk_insert(f, keys, n, okv, kicks, s);
     st = grow_queue(f, n, s);
     if (st != CF_OK) return st;
     const cfk::LostLog log{f->lost_bucket, f->lost_tag, f->lost_cap};
@@ -334,7 +483,7 @@ cf_status cf_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *okv
         const uint64_t seg = ((len + per - 1) / per) * kBlock;
         f->L.ins(f->table, f->place, keys + off, len, okv ? okv + off : nullptr,
                  kicks ? kicks + off : nullptr, f->ctr, f->queue, seg, log, f->p.max_evict,
-                 f->p.seed, grid, s);
+                 f->p.seed, cfk::Rest{}, grid, s);
         st = check_launch("insert");
         if (st != CF_OK) return st;
     }
@@ -366,7 +515,7 @@ cf_status cf_insert_noalloc(cf_filter *f, const uint64_t *keys, uint64_t n, uint
     const uint64_t seg = ((n + per - 1) / per) * kBlock;
     const cfk::LostLog log{f->lost_bucket, f->lost_tag, f->lost_cap};
     f->L.ins(f->table, f->place, keys, n, okv, kicks, f->ctr, q, seg, log, f->p.max_evict,
-             f->p.seed, grid, static_cast<hipStream_t>(stream));
+             f->p.seed, cfk::Rest{}, grid, static_cast<hipStream_t>(stream));
     return check_launch("insert (fixed queue)");
 }
 

@@ -49,11 +49,41 @@ struct InstI {
     using W = typename G::W;
     static void ins(void *t, const cfk::Place &pl, const uint64_t *k, uint64_t n, uint8_t *o,
                     uint32_t *kk, Counters *c, uint32_t *q, uint64_t seg, cfk::LostLog log,
-                    uint32_t me, uint64_t seed, int grid, hipStream_t s) {
+                    uint32_t me, uint64_t seed, const cfk::Rest &rest, int grid, hipStream_t s) {
         cfk::insert_kernel<G, HASH, EVICT, POL, PW><<<grid, kBlock, 0, s>>>(
-            static_cast<W *>(t), pl, k, n, o, kk, c, q, seg, log, me, seed);
+            static_cast<W *>(t), pl, k, n, o, kk, c, q, seg, log, me, seed, rest);
     }
 };
+
+// The partitioned insert: the splits know nothing of the bucket size, the
+// placement of entries in a part nothing of hash and placement policy.
+template <int F, int HASH, int POL>
+void split(const uint64_t *k, uint32_t n, const cfk::Place &pl, uint32_t shift, uint32_t nbins,
+           uint32_t *cur, cfk::Ents out, uint32_t cap, uint8_t *o, uint32_t *kk, uint32_t *ovl,
+           uint32_t *ovl_n, hipStream_t s) {
+    const uint32_t grid = (n + cfk::kSplitTile - 1) / cfk::kSplitTile;
+    cfk::bulk_split_kernel<F, HASH, POL><<<grid, cfk::kSplitBlock, cfk::split_lds(F, nbins), s>>>(
+        k, n, pl, shift, nbins, cur, out, cap, o, kk, ovl, ovl_n);
+}
+template <int F>
+void resplit(cfk::Ents in, const uint32_t *in_n, uint32_t nbins, uint32_t cap_in, uint32_t shift,
+             uint32_t fine, uint32_t *cur, cfk::Ents out, uint32_t cap, uint32_t *ovl,
+             uint32_t *ovl_n, hipStream_t s) {
+    const uint32_t tiles = (cap_in + cfk::kSplitTile - 1) / cfk::kSplitTile;
+    cfk::bulk_resplit_kernel<F>
+        <<<nbins * cfk::kBulkSegs * tiles, cfk::kSplitBlock, cfk::split_lds(F, 1u << fine), s>>>(
+            in, in_n, nbins, cap_in, tiles, shift, fine, cur, out, cap, ovl, ovl_n);
+}
+template <int F, int B>
+void place(void *t, uint64_t m, uint32_t shift, cfk::Ents in, const uint32_t *in_n, uint32_t runs,
+           uint32_t stride, uint32_t cap, uint32_t *list, uint32_t *list_n, uint32_t list_cap,
+           Counters *c, int parts, hipStream_t s) {
+    using G = cfk::Geom<F, B>;
+    cfk::bulk_insert_kernel<G>
+        <<<parts, cfk::kPlaceBlock, (size_t(B) * F / 8) << shift, s>>>(
+            static_cast<typename G::W *>(t), m, shift, in, in_n, runs, stride, cap, list, list_n,
+            list_cap, c);
+}
 
 // Tables of at most this many bytes get a breadth-first search that loads
 // each group of candidates' other buckets together (cfk::probe_width); the
@@ -73,6 +103,9 @@ void fill_qd(int hash, Launchers &L) {
 template <int F, int B, int POL>
 void fill_ins(int hash, int evict, bool grouped, Launchers &L) {
     constexpr int PW = cfk::probe_width<cfk::Geom<F, B>>();
+    L.split = hash == 0 ? &split<F, 0, POL> : &split<F, 1, POL>;
+    L.resplit = &resplit<F>;
+    L.place = &place<F, B>;
     if (evict == 0 && grouped)
         L.ins = hash == 0 ? &InstI<F, B, 0, 0, POL, PW>::ins : &InstI<F, B, 1, 0, POL, PW>::ins;
     else

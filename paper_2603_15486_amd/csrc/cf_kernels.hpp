@@ -13,7 +13,6 @@
 namespace cfk {
 
 constexpr int kBlock = 256;
-constexpr int kWaves = kBlock / 64;
 constexpr int kStripes = 32;  // occupancy counter stripes, one 128-byte line each
 
 // Device-side counters.  The occupancy count is striped over kStripes
@@ -33,6 +32,15 @@ struct Counters {
     unsigned long long total;  // sum of the stripes, written by sum_counts_kernel
 };
 
+// What a partitioned insert left over (see insert_kernel); list = NULL: none.
+struct Rest {
+    const uint32_t *list;    // part p's keys at list[p * cap ..]
+    const uint32_t *list_n;  // how many
+    const uint32_t *ovl;     // the overflow list
+    const uint32_t *ovl_n;
+    uint32_t cap, parts, split, extra;
+};
+
 struct LostLog {
     unsigned long long *bucket;
     uint32_t *tag;
@@ -41,8 +49,9 @@ struct LostLog {
 
 // Sum v over the block and add it to the block's count stripe with one
 // atomic.  Every thread of the block must call it.
+template <int BT = kBlock>
 __device__ __forceinline__ void block_add(Counters *ctr, unsigned long long v) {
-    __shared__ unsigned long long part[kWaves];
+    __shared__ unsigned long long part[BT / 64];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -51,7 +60,7 @@ __device__ __forceinline__ void block_add(Counters *ctr, unsigned long long v) {
     if (threadIdx.x == 0) {
         unsigned long long s = 0;
 #pragma unroll
-        for (int k = 0; k < kWaves; ++k) s += part[k];
+        for (int k = 0; k < BT / 64; ++k) s += part[k];
         if (s) atomicAdd(&ctr->count[blockIdx.x % kStripes].v, s);
     }
     __syncthreads();
@@ -268,32 +277,62 @@ __device__ __forceinline__ bool evict_dfs(typename G::W *table, const Place &pl,
 // paper's concurrent insert.  Deferring evictions keeps the common path's
 // wave64 lanes free of eviction-chain divergence, and blocks in different
 // passes overlap the read-heavy direct work with the atomic-heavy evictions.
+//
+// With rest.list set the launch takes the keys a partitioned insert left over
+// (cf_bulk.hpp) instead of keys [0, n): block b works on its share of one
+// part's list, whose keys are known to have a full i1, and the last
+// rest.extra blocks on shares of the overflow list.  The keys' flags and kick
+// counts already hold 1 and 0 then, so only what differs is written (single
+// bytes at random places cost a memory request each).
 template <class G, int HASH, int EVICT, int POL, int PW = 1>
 __global__ __launch_bounds__(kBlock) void insert_kernel(
     typename G::W *__restrict__ table, Place pl, const uint64_t *__restrict__ keys,
     uint64_t n, uint8_t *__restrict__ ok, uint32_t *__restrict__ kicks, Counters *ctr,
     uint32_t *__restrict__ queue, uint64_t seg, LostLog log, uint32_t max_evict,
-    uint64_t seed) {
+    uint64_t seed, Rest rest) {
     __shared__ uint32_t s_qn;
     if (threadIdx.x == 0) s_qn = 0;
     __syncthreads();
     uint32_t *myq = queue + uint64_t(blockIdx.x) * seg;
     unsigned long long placed = 0;
-    const uint64_t stride = uint64_t(gridDim.x) * kBlock;
+    uint64_t stride = uint64_t(gridDim.x) * kBlock;
+    uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x;
+    const uint32_t *list = rest.list;
+    bool i1_full = false;
+    if (list) {
+        const uint32_t lists = rest.parts * rest.split;
+        i1_full = blockIdx.x < lists;
+        const uint32_t part = i1_full ? blockIdx.x / rest.split : 0u;
+        const uint64_t share = i1_full ? blockIdx.x % rest.split : blockIdx.x - lists;
+        const uint64_t of = i1_full ? rest.split : rest.extra;
+        const uint64_t len = i1_full ? rest.list_n[part] : *rest.ovl_n;
+        const uint64_t lo = len * share / of;
+        list = (i1_full ? list + uint64_t(part) * rest.cap : rest.ovl) + lo;
+        myq = queue + (i1_full ? uint64_t(part) * rest.cap : uint64_t(rest.parts) * rest.cap) + lo;
+        seg = n = len * (share + 1) / of - lo;
+        i = threadIdx.x;
+        stride = kBlock;
+    }
     const int lane = threadIdx.x & 63;
-    for (uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += stride) {
-        const uint64_t key = __builtin_nontemporal_load(keys + i);
+    for (; i < n; i += stride) {
+        const uint64_t at = list ? list[i] : i;
+        const uint64_t key = __builtin_nontemporal_load(keys + at);
         const Derived d = derive<G, HASH, POL>(key, pl);
         Bucket<G> bk;
-        load_bucket<G>(table, d.i1, bk);
-        bool done = try_insert<G>(table, d.i1, d.t1, bk) >= 0;
+        bool done = false;
+        if (!i1_full) {
+            load_bucket<G>(table, d.i1, bk);
+            done = try_insert<G>(table, d.i1, d.t1, bk) >= 0;
+        }
         if (!done) {
             load_bucket<G>(table, d.i2, bk);
             done = try_insert<G>(table, d.i2, d.t2, bk) >= 0;
         }
         placed += done;
-        if (ok) ok[i] = uint8_t(done);
-        if (kicks) kicks[i] = 0;
+        if (!list) {
+            if (ok) ok[at] = uint8_t(done);
+            if (kicks) kicks[at] = 0;
+        }
         const uint64_t need = __ballot(!done);
         if (need) {
             const int leader = __builtin_ctzll(need);
@@ -301,7 +340,7 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
             if (lane == leader) base = atomicAdd(&s_qn, uint32_t(__popcll(need)));
             base = __shfl(base, leader, 64);
             const uint32_t pos = base + uint32_t(__popcll(need & ((1ull << lane) - 1ull)));
-            if (!done && pos < seg) myq[pos] = uint32_t(i);
+            if (!done && pos < seg) myq[pos] = uint32_t(at);
         }
     }
     __syncthreads();
@@ -328,8 +367,8 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
                 log.tag[slot] = lt;
             }
         }
-        if (ok) ok[idx] = uint8_t(done);
-        if (kicks) kicks[idx] = k;
+        if (ok && !(list && done)) ok[idx] = uint8_t(done);
+        if (kicks && !(list && k == 0)) kicks[idx] = k;
     }
     block_add(ctr, placed);
 }
@@ -370,6 +409,11 @@ static __global__ void sum_counts_kernel(Counters *ctr) {
 }
 
 static __global__ __launch_bounds__(kBlock) void zero_words_kernel(uint64_t *__restrict__ p, uint64_t n) {
+    const uint64_t stride = uint64_t(gridDim.x) * kBlock;
+    for (uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += stride) p[i] = 0;
+}
+
+static __global__ __launch_bounds__(kBlock) void zero_u32_kernel(uint32_t *__restrict__ p, uint64_t n) {
     const uint64_t stride = uint64_t(gridDim.x) * kBlock;
     for (uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += stride) p[i] = 0;
 }

@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include "cf.h"
+#include "cf_bulk.hpp"
 #include "cf_kernels.hpp"
 
 namespace cfl {
@@ -20,7 +21,18 @@ struct Launchers {
                 uint8_t *okv, cfk::Counters *ctr, int grid, hipStream_t s);
     void (*ins)(void *table, const cfk::Place &pl, const uint64_t *keys, uint64_t n,
                 uint8_t *okv, uint32_t *kicks, cfk::Counters *ctr, uint32_t *queue, uint64_t seg,
-                cfk::LostLog log, uint32_t max_evict, uint64_t seed, int grid, hipStream_t s);
+                cfk::LostLog log, uint32_t max_evict, uint64_t seed, const cfk::Rest &rest,
+                int grid, hipStream_t s);
+    // the partitioned insert (cf_bulk.hpp)
+    void (*split)(const uint64_t *keys, uint32_t n, const cfk::Place &pl, uint32_t shift,
+                  uint32_t nbins, uint32_t *cursor, cfk::Ents out, uint32_t cap, uint8_t *okv,
+                  uint32_t *kicks, uint32_t *ovl, uint32_t *ovl_n, hipStream_t s);
+    void (*resplit)(cfk::Ents in, const uint32_t *in_n, uint32_t nbins, uint32_t cap_in,
+                    uint32_t shift, uint32_t fine, uint32_t *cursor, cfk::Ents out, uint32_t cap,
+                    uint32_t *ovl, uint32_t *ovl_n, hipStream_t s);
+    void (*place)(void *table, uint64_t m, uint32_t shift, cfk::Ents in, const uint32_t *in_n,
+                  uint32_t runs, uint32_t stride, uint32_t cap, uint32_t *list, uint32_t *list_n,
+                  uint32_t list_cap, cfk::Counters *ctr, int parts, hipStream_t s);
     void (*recount)(const void *table, uint64_t nwords, cfk::Counters *ctr, int grid,
                     hipStream_t s);
     uint64_t words_per_bucket;  // in units of the geometry's word type
