@@ -13,6 +13,7 @@
 namespace cfk {
 
 constexpr int kBlock = 256;
+constexpr int kRefill = 16;  // free lanes of a wave that take new searches together
 constexpr int kStripes = 32;  // occupancy counter stripes, one 128-byte line each
 
 // Device-side counters.  The occupancy count is striped over kStripes
@@ -129,17 +130,17 @@ constexpr int probe_width() {
     return fit < G::B / 2 ? fit : G::B / 2;
 }
 
-// Sec. 4.6.1 breadth-first heuristic.  At each level the candidates are the
-// b/2 slots of the current bucket starting at a random slot; the first whose
-// fingerprint has an empty slot in its other bucket is moved there and the
-// carried fingerprint takes its place.  Failing that, the last candidate is
-// displaced and carried to its other bucket.  The move is done displacement
-// first: the carried fingerprint replaces the candidate with a CAS that only
-// succeeds while the slot still holds the candidate, then the candidate is
-// inserted into its other bucket.  If that bucket filled up in the meantime
-// the candidate is simply carried on, as after a displacement.  `tag` is
-// always the carried fingerprint as it is written in `cur` (the choice bit
-// of the offset policy flips with every move).
+// Sec. 4.6.1 breadth-first heuristic, one level at a time.  At each level the
+// candidates are the b/2 slots of the current bucket starting at a random
+// slot; the first whose fingerprint has an empty slot in its other bucket is
+// moved there and the carried fingerprint takes its place.  Failing that, the
+// last candidate is displaced and carried to its other bucket.  The move is
+// done displacement first: the carried fingerprint replaces the candidate
+// with a CAS that only succeeds while the slot still holds the candidate,
+// then the candidate is inserted into its other bucket.  If that bucket
+// filled up in the meantime the candidate is simply carried on, as after a
+// displacement.  `tag` is always the carried fingerprint as it is written in
+// `cur` (the choice bit of the offset policy flips with every move).
 // The insert kernels that use it are compiled at -O1: built at -O2 or -O3
 // they lost fingerprints under heavy contention (one-launch fills of a
 // 2^20-slot table), a loss that appears with the backend's Early Machine
@@ -155,110 +156,142 @@ constexpr int probe_width() {
 // on large tables, where it is bound by memory requests and whole groups
 // only add reads; tables of a few MiB measured faster with probe_width (the
 // launchers choose by table size).
-template <class G, int HASH, int POL, int PW = 1>
-__device__ __forceinline__ bool evict_bfs(typename G::W *table, const Place &pl, uint64_t rs, uint32_t cur,
-                          uint32_t tag, uint32_t max_evict, uint32_t &kicks,
-                          uint32_t &lost_bucket, uint32_t &lost_tag) {
+//
+// What bounds a search is its chain of dependent memory accesses (half a
+// microsecond and up for a load, more than one for a device-scope CAS), so a
+// level hands the bucket it ends in to the next one: the displaced last
+// candidate's other bucket was just probed and found full, and within an
+// insert launch a full bucket stays full, so neither it nor the next level's
+// current bucket is loaded again.  A level that displaces is then one round
+// of probes and one CAS.
+
+// One search in flight.
+template <class G>
+struct Search {
+    uint64_t rs;      // its stream of random draws
+    uint32_t cur;     // the bucket the carried fingerprint is to enter
+    uint32_t tag;     // ... as it is written there
+    uint32_t n;       // levels done
+    uint32_t kicks;
+    bool have;        // cb holds cur's words, seen full
+    Bucket<G> cb;
+};
+
+template <class G>
+__device__ __forceinline__ void search_start(Search<G> &st, Derived d, uint64_t rs) {
+    // masks, not selects: a select becomes an indexed access to d in memory
+    const uint32_t second = 0u - uint32_t(splitmix_at(rs, 0) & 1);
+    st.rs = rs;
+    st.cur = (d.i1 & ~second) | (d.i2 & second);
+    st.tag = (d.t1 & ~second) | (d.t2 & second);
+    st.n = 0;
+    st.kicks = 0;
+    st.have = false;
+}
+
+// One level; true once the carried fingerprint is stored.
+template <class G, int HASH, int POL, int PW>
+__device__ __forceinline__ bool bfs_level(typename G::W *table, const Place &pl, Search<G> &st) {
+    using W = typename G::W;
     constexpr int HALF = G::B / 2;
     static_assert(PW >= 1 && HALF % PW == 0, "probe width must divide b/2");
-    for (uint32_t n = 1; n <= max_evict; ++n) {
-        Bucket<G> cb;
-        load_bucket<G>(table, cur, cb);
-        if (cb.has_empty() && try_insert<G>(table, cur, tag, cb) >= 0) return true;
-        const int r0 = int(splitmix_at(rs, n) % uint64_t(G::B));
-        bool carried = false;
-        if constexpr (PW > 1) {
-            for (int j0 = 0; j0 < HALF && !carried; j0 += PW) {
-                // the group's other buckets, loaded together; only a bit per
-                // candidate (its other bucket has an empty slot) is kept
-                uint32_t ok = 0, cv[PW];
-#pragma unroll
-                for (int q = 0; q < PW; ++q) {
-                    cv[q] = cb.slot((r0 + j0 + q) % G::B);
-                    uint32_t moved = cv[q];
-                    const uint32_t a = move_tag<G, HASH, POL>(cur, moved, pl);
-                    if (cv[q] != 0 && a != cur) {
-                        Bucket<G> ab;
-                        load_bucket<G>(table, a, ab);
-                        if (ab.has_empty()) ok |= 1u << q;
-                    }
-                }
-                // then, in candidate order, the move of the first that takes it
-                // (the probed value: the move happens only while the slot holds it)
-                while (ok && !carried) {
-                    const int q = __builtin_ctz(ok);
-                    ok &= ok - 1u;
-                    const int s = (r0 + j0 + q) % G::B;
-                    uint32_t c = 0;
-#pragma unroll
-                    for (int k = 0; k < PW; ++k) c = k == q ? cv[k] : c;
-                    uint32_t moved = c;
-                    const uint32_t a = move_tag<G, HASH, POL>(cur, moved, pl);
-                    if (!replace_slot_if<G>(table, cur, s, c, tag, cb)) continue;
-                    ++kicks;
-                    Bucket<G> ab;
-                    load_bucket<G>(table, a, ab);
-                    if (try_insert<G>(table, a, moved, ab) >= 0) return true;
-                    tag = moved;  // `a` filled up meanwhile: carry the candidate from there
-                    cur = a;
-                    carried = true;
-                }
-            }
-        }
-        for (int j = 0; PW == 1 && j < HALF && !carried; ++j) {
-            const int s = (r0 + j) % G::B;
-            const uint32_t c = cb.slot(s);
-            if (c == 0) continue;
-            uint32_t moved = c;
-            const uint32_t a = move_tag<G, HASH, POL>(cur, moved, pl);
-            if (a == cur) continue;
-            Bucket<G> ab;
-            load_bucket<G>(table, a, ab);
-            if (!ab.has_empty()) continue;
-            if (!replace_slot_if<G>(table, cur, s, c, tag, cb)) continue;
-            ++kicks;
-            if (try_insert<G>(table, a, moved, ab) >= 0) return true;
-            tag = moved;  // `a` filled up meanwhile: carry the candidate from there
-            cur = a;
-            carried = true;
-        }
-        if (carried) continue;
-        const int s_last = (r0 + HALF - 1) % G::B;
-        const uint32_t ev = swap_slot<G>(table, cur, s_last, tag, cb);
-        ++kicks;
-        if (ev == 0) return true;
-        tag = ev;
-        cur = move_tag<G, HASH, POL>(cur, tag, pl);
-        Bucket<G> nb;
-        load_bucket<G>(table, cur, nb);
-        if (try_insert<G>(table, cur, tag, nb) >= 0) return true;
+    ++st.n;
+    if (!st.have) {
+        load_bucket<G>(table, st.cur, st.cb);
+        if (st.cb.has_empty() && try_insert<G>(table, st.cur, st.tag, st.cb) >= 0) return true;
     }
-    lost_bucket = cur;
-    lost_tag = tag;
+    const int r0 = int(splitmix_at(st.rs, st.n) % uint64_t(G::B));
+    Bucket<G> last;       // the last candidate's other bucket,
+    uint32_t last_c = 0;  // and the candidate (0: it has no other bucket)
+    for (int j0 = 0; j0 < HALF; j0 += PW) {
+        Bucket<G> ab[PW];  // the group's other buckets,
+        uint32_t cv[PW];   // and its candidates
+#pragma unroll
+        for (int q = 0; q < PW; ++q) {
+            cv[q] = st.cb.slot((r0 + j0 + q) % G::B);
+            uint32_t moved = cv[q];
+            uint32_t a = move_tag<G, HASH, POL>(st.cur, moved, pl);
+            if (a == st.cur) cv[q] = 0;
+            // no branch around the load, so that a group's loads go out together
+            load_bucket<G>(table, cv[q] != 0 ? a : st.cur, ab[q]);
+        }
+        uint32_t ok = 0;
+#pragma unroll
+        for (int q = 0; q < PW; ++q) ok |= (cv[q] != 0 && ab[q].has_empty() ? 1u : 0u) << q;
+        last = ab[PW - 1];
+        last_c = cv[PW - 1];
+        // in candidate order, the move of the first that takes it (the probed
+        // value: the move happens only while the slot holds it)
+        while (ok) {
+            const int q = __builtin_ctz(ok);
+            ok &= ok - 1u;
+            const int s = (r0 + j0 + q) % G::B;
+            uint32_t c = cv[0];
+            Bucket<G> mb = ab[0];
+#pragma unroll
+            for (int k = 1; k < PW; ++k) {
+                const uint32_t m32 = 0u - uint32_t(k == q);
+                c = (c & ~m32) | (cv[k] & m32);
+                const W mask = W(0) - W(k == q);
+#pragma unroll
+                for (int w = 0; w < G::WPB; ++w)
+                    mb.w[w] = (mb.w[w] & ~mask) | (ab[k].w[w] & mask);
+            }
+            uint32_t moved = c;
+            const uint32_t a = move_tag<G, HASH, POL>(st.cur, moved, pl);
+            if (!replace_slot_if<G>(table, st.cur, s, c, st.tag, st.cb)) continue;
+            ++st.kicks;
+            if (try_insert<G>(table, a, moved, mb) >= 0) return true;
+            st.tag = moved;  // `a` filled up meanwhile: carry the candidate from there
+            st.cur = a;
+            st.cb = mb;
+            st.have = true;
+            return false;
+        }
+    }
+    const uint32_t ev = swap_slot<G>(table, st.cur, (r0 + HALF - 1) % G::B, st.tag, st.cb);
+    ++st.kicks;
+    if (ev == 0) return true;
+    st.tag = ev;
+    st.cur = move_tag<G, HASH, POL>(st.cur, st.tag, pl);
+    st.have = true;
+    if (ev == last_c) st.cb = last;
+    else load_bucket<G>(table, st.cur, st.cb);
+    return st.cb.has_empty() && try_insert<G>(table, st.cur, st.tag, st.cb) >= 0;
+}
+
+// One step of Alg. 1's eviction chain: displace a random slot, carry the
+// displaced fingerprint to its other bucket, try there.
+template <class G, int HASH, int POL>
+__device__ __forceinline__ bool dfs_level(typename G::W *table, const Place &pl,
+                                          Search<G> &st) {
+    const int s = int(splitmix_at(st.rs, ++st.n) % uint64_t(G::B));
+    if (!st.have) load_bucket<G>(table, st.cur, st.cb);
+    const uint32_t ev = swap_slot<G>(table, st.cur, s, st.tag, st.cb);
+    ++st.kicks;
+    if (ev == 0) return true;
+    st.tag = ev;
+    st.cur = move_tag<G, HASH, POL>(st.cur, st.tag, pl);
+    st.have = true;
+    load_bucket<G>(table, st.cur, st.cb);
+    return try_insert<G>(table, st.cur, st.tag, st.cb) >= 0;
+}
+
+// A whole search by one lane; false: the bound was reached, and st.cur and
+// st.tag are the fingerprint dropped.
+template <class G, int HASH, int POL, int PW>
+__device__ __forceinline__ bool evict_bfs(typename G::W *table, const Place &pl,
+                                          Search<G> &st, uint32_t max_evict) {
+    while (st.n < max_evict)
+        if (bfs_level<G, HASH, POL, PW>(table, pl, st)) return true;
     return false;
 }
 
-// Alg. 1 eviction chain: displace a random slot, carry the displaced
-// fingerprint to its other bucket, try there.
 template <class G, int HASH, int POL>
-__device__ __forceinline__ bool evict_dfs(typename G::W *table, const Place &pl, uint64_t rs, uint32_t cur,
-                          uint32_t tag, uint32_t max_evict, uint32_t &kicks,
-                          uint32_t &lost_bucket, uint32_t &lost_tag) {
-    for (uint32_t n = 1; n <= max_evict; ++n) {
-        const int s = int(splitmix_at(rs, n) % uint64_t(G::B));
-        Bucket<G> cb;
-        load_bucket<G>(table, cur, cb);
-        const uint32_t ev = swap_slot<G>(table, cur, s, tag, cb);
-        ++kicks;
-        if (ev == 0) return true;
-        tag = ev;
-        cur = move_tag<G, HASH, POL>(cur, tag, pl);
-        Bucket<G> nb;
-        load_bucket<G>(table, cur, nb);
-        if (try_insert<G>(table, cur, tag, nb) >= 0) return true;
-    }
-    lost_bucket = cur;
-    lost_tag = tag;
+__device__ __forceinline__ bool evict_dfs(typename G::W *table, const Place &pl,
+                                          Search<G> &st, uint32_t max_evict) {
+    while (st.n < max_evict)
+        if (dfs_level<G, HASH, POL>(table, pl, st)) return true;
     return false;
 }
 
@@ -290,8 +323,8 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
     uint64_t n, uint8_t *__restrict__ ok, uint32_t *__restrict__ kicks, Counters *ctr,
     uint32_t *__restrict__ queue, uint64_t seg, LostLog log, uint32_t max_evict,
     uint64_t seed, Rest rest) {
-    __shared__ uint32_t s_qn;
-    if (threadIdx.x == 0) s_qn = 0;
+    __shared__ uint32_t s_qn, s_take;
+    if (threadIdx.x == 0) s_qn = s_take = 0;
     __syncthreads();
     uint32_t *myq = queue + uint64_t(blockIdx.x) * seg;
     unsigned long long placed = 0;
@@ -345,30 +378,50 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
     }
     __syncthreads();
     const uint32_t qn = s_qn < seg ? s_qn : uint32_t(seg);
-    for (uint32_t q = threadIdx.x; q < qn; q += kBlock) {
-        const uint32_t idx = myq[q];
-        const uint64_t key = keys[idx];
-        const Derived d = derive<G, HASH, POL>(key, pl);
-        const uint64_t rs = key ^ seed;
-        const bool second = (splitmix_at(rs, 0) & 1) != 0;
-        const uint32_t cur = second ? d.i2 : d.i1;
-        const uint32_t tag = second ? d.t2 : d.t1;
-        uint32_t k = 0, lb = 0, lt = 0;
-        bool done;
-        if constexpr (EVICT == 1)
-            done = evict_dfs<G, HASH, POL>(table, pl, rs, cur, tag, max_evict, k, lb, lt);
-        else
-            done = evict_bfs<G, HASH, POL, PW>(table, pl, rs, cur, tag, max_evict, k, lb, lt);
+    // The searches: a wave steps its lanes' searches level by level, and lanes
+    // whose search ended take the next queued keys together once a quarter of
+    // the wave is free (taking a key is two dependent loads, which the others
+    // wait for).  Searches differ in length by an order of magnitude; run to
+    // the end by 64 lanes side by side, most lanes wait for the longest.
+    Search<G> st;
+    uint32_t idx = 0;
+    bool busy = false, more = qn != 0;
+    while (true) {
+        const uint64_t idle = __ballot(!busy);
+        if (more && __popcll(idle) >= kRefill) {
+            const int leader = __builtin_ctzll(idle);
+            uint32_t base = 0;
+            if (lane == leader) base = atomicAdd(&s_take, uint32_t(__popcll(idle)));
+            base = __shfl(base, leader, 64);
+            more = base + uint32_t(__popcll(idle)) < qn;
+            const uint32_t q = base + uint32_t(__popcll(idle & ((1ull << lane) - 1ull)));
+            if (!busy && q < qn) {
+                idx = myq[q];
+                const uint64_t key = keys[idx];
+                search_start(st, derive<G, HASH, POL>(key, pl), key ^ seed);
+                busy = true;
+            }
+        }
+        if (__ballot(busy) == 0) break;  // nothing taken: the queue is empty
+        if (!busy) continue;
+        bool done = false, ended = st.n >= max_evict;
+        if (!ended) {
+            if constexpr (EVICT == 1) done = dfs_level<G, HASH, POL>(table, pl, st);
+            else done = bfs_level<G, HASH, POL, PW>(table, pl, st);
+            ended = done || st.n >= max_evict;
+        }
+        if (!ended) continue;
+        busy = false;
         placed += done;
         if (!done) {
             const unsigned long long slot = atomicAdd(&ctr->failures, 1ull);
             if (slot < log.cap) {
-                log.bucket[slot] = lb;
-                log.tag[slot] = lt;
+                log.bucket[slot] = st.cur;
+                log.tag[slot] = st.tag;
             }
         }
         if (ok && !(list && done)) ok[idx] = uint8_t(done);
-        if (kicks && !(list && k == 0)) kicks[idx] = k;
+        if (kicks && !(list && st.kicks == 0)) kicks[idx] = st.kicks;
     }
     block_add(ctr, placed);
 }

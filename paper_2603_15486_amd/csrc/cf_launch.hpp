@@ -22,7 +22,7 @@ struct Launchers {
     void (*ins)(void *table, const cfk::Place &pl, const uint64_t *keys, uint64_t n,
                 uint8_t *okv, uint32_t *kicks, cfk::Counters *ctr, uint32_t *queue, uint64_t seg,
                 cfk::LostLog log, uint32_t max_evict, uint64_t seed, const cfk::Rest &rest,
-                int grid, hipStream_t s);
+                bool grouped, int grid, hipStream_t s);
     // the partitioned insert (cf_bulk.hpp)
     void (*split)(const uint64_t *keys, uint32_t n, const cfk::Place &pl, uint32_t shift,
                   uint32_t nbins, uint32_t *cursor, cfk::Ents out, uint32_t cap, uint8_t *okv,
@@ -38,6 +38,20 @@ struct Launchers {
     uint64_t words_per_bucket;  // in units of the geometry's word type
     uint64_t word_bytes;
 };
+
+// Whether an insert launch of n keys on a table of that many bytes loads each
+// group of candidates' other buckets together (cfk::probe_width) in the
+// breadth-first search, or probes candidate by candidate.
+// By table size, measured on one-launch fills at load 0.95: 2 MiB 6.6 -> 7.25
+// Gops/s and 8 MiB 13.8 -> 14.3-14.7 grouped.  The 64 MiB eviction-stress
+// table (4-byte buckets, to load 0.98) was 2-5% slower grouped, and the
+// 512 MiB and 4 GiB tables, whose probes are HBM requests, 3% (the 4 GiB
+// step's inserts 15%).
+constexpr uint64_t kGroupedProbeBytes = uint64_t(16) << 20;
+constexpr uint64_t kGroupedKeys = uint64_t(1) << 19;
+inline bool grouped_probe(uint64_t table_bytes, uint64_t n) {
+    return table_bytes <= kGroupedProbeBytes || n <= kGroupedKeys;
+}
 
 // Launchers for p's geometry, hash, eviction policy and placement; false if
 // unsupported.  pick_launchers dispatches on f to the per-width tables

@@ -374,18 +374,18 @@ __device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__r
             W *table = static_cast<W *>(F.table);
             const uint64_t key = bt.keys[i];
             const Derived d = cfk::derive<G, HASH, POL>(key, F.place);
-            const uint64_t rs = key ^ F.seed;
-            const bool second = (cfk::splitmix_at(rs, 0) & 1) != 0;
-            const uint32_t cur = second ? d.i2 : d.i1;
-            const uint32_t tag = second ? d.t2 : d.t1;
-            uint32_t k = 0, lb = 0, lt = 0;
-            const bool done =
-                F.evict == CF_EVICT_DFS
-                    ? cfk::evict_dfs<G, HASH, POL>(table, F.place, rs, cur, tag, F.max_evict, k,
-                                                   lb, lt)
-                    : cfk::evict_bfs<G, HASH, POL, probe_width<G>()>(table, F.place, rs, cur, tag,
-                                                                    F.max_evict, k, lb, lt);
-            finish(F, fid, i, done, lb, lt);
+            if (F.evict == CF_EVICT_DFS) {
+                cfk::Search<G> st;
+                cfk::search_start(st, d, key ^ F.seed);
+                const bool done = cfk::evict_dfs<G, HASH, POL>(table, F.place, st, F.max_evict);
+                finish(F, fid, i, done, st.cur, st.tag);
+            } else {
+                cfk::Search<G> st;
+                cfk::search_start(st, d, key ^ F.seed);
+                const bool done = cfk::evict_bfs<G, HASH, POL, probe_width<G>()>(
+                    table, F.place, st, F.max_evict);
+                finish(F, fid, i, done, st.cur, st.tag);
+            }
         }
     } else {
         constexpr uint32_t NW = BT / 64;
@@ -407,13 +407,10 @@ __device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__r
                 W *table = static_cast<W *>(F.table);
                 const uint64_t key = bt.keys[i];
                 const Derived d = cfk::derive<G, HASH, POL>(key, F.place);
-                const uint64_t rs = key ^ F.seed;
-                const bool second = (cfk::splitmix_at(rs, 0) & 1) != 0;
-                uint32_t k = 0, lb = 0, lt = 0;
-                const bool done = cfk::evict_dfs<G, HASH, POL>(
-                    table, F.place, rs, second ? d.i2 : d.i1, second ? d.t2 : d.t1, F.max_evict,
-                    k, lb, lt);
-                finish(F, fid, i, done, lb, lt);
+                cfk::Search<G> st;
+                cfk::search_start(st, d, key ^ F.seed);
+                const bool done = cfk::evict_dfs<G, HASH, POL>(table, F.place, st, F.max_evict);
+                finish(F, fid, i, done, st.cur, st.tag);
             }
             uint64_t todo = __ballot(have && !walk);
             while (todo) {  // uniform: one key at a time, the whole wave on it
