@@ -199,7 +199,7 @@ struct BulkPlan {
     uint32_t bins, fine;        // bins of 2^fine parts; fine = 0: a bin is a part
     uint32_t cap1, cap2;        // entries per run of a bin, per part (fine > 0)
     uint32_t list_cap;
-    uint64_t cursors;           // words cleared before a pass: cursors, overflow count
+    uint64_t cursors;           // cursors and overflow count; zero between passes
     uint64_t o_cur, o_listn, o_a, o_a32, o_b, o_b32, o_list, o_ovl, bytes;
 };
 
@@ -247,7 +247,7 @@ BulkPlan bulk_plan(const cf_filter *f, uint64_t len) {
     };
     p.cursors = uint64_t(p.bins) * cfk::kBulkSegs + (p.fine ? p.parts : 0) + 1;
     p.o_cur = take(p.cursors * 4);
-    p.o_listn = take(uint64_t(p.parts) * 4);
+    p.o_listn = take((uint64_t(p.parts) + 1) * 4);
     // the first level's entries, and later (they are used up by then) the
     // eviction queues of the keys left over
     p.o_a = take(std::max(n1 * 8, (lists + len) * 4));
@@ -277,6 +277,15 @@ bool bulk_reserve(cf_filter *f, uint64_t n, hipStream_t s) {
         f->bulk = nullptr;
         return false;
     }
+    // Each pass leaves the cursors at zero.  Their number does not depend on
+    // the pass's length.
+    if (hipMemset(f->bulk, 0, bulk_plan(f, 1).cursors * 4) != hipSuccess ||
+        hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(f->bulk);
+        f->bulk = nullptr;
+        return false;
+    }
     f->bulk_bytes = want;
     return true;
 }
@@ -301,26 +310,29 @@ cf_status bulk_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *o
         uint32_t *ovl = reinterpret_cast<uint32_t *>(f->bulk + p.o_ovl);
         uint8_t *o = okv ? okv + lo : nullptr;
         uint32_t *kk = kicks ? kicks + lo : nullptr;
-        cfk::zero_u32_kernel<<<grid_for(f, p.cursors), kBlock, 0, s>>>(cur1, p.cursors);
         f->L.split(keys + lo, uint32_t(len), f->place, p.shift + p.fine, p.bins, cur1, a, p.cap1,
                    o, kk, ovl, ovl_n, s);
         if (p.fine) {
             f->L.resplit(a, cur1, p.bins, p.cap1, p.shift, p.fine, cur2, b, p.cap2, ovl, ovl_n, s);
             f->L.place(f->table, f->p.num_buckets, p.shift, b, cur2, 1, p.parts, p.cap2, list,
-                       list_n, p.list_cap, f->ctr, int(p.parts), s);
+                       list_n, p.list_cap, ovl_n, f->ctr, int(p.parts), s);
         } else {
             f->L.place(f->table, f->p.num_buckets, p.shift, a, cur1, cfk::kBulkSegs, p.bins,
-                       p.cap1, list, list_n, p.list_cap, f->ctr, int(p.parts), s);
+                       p.cap1, list, list_n, p.list_cap, ovl_n, f->ctr, int(p.parts), s);
         }
         // several blocks per list while there are few lists
         const uint32_t split = std::max(1u, std::min(8u, 2048u / p.parts));
-        const cfk::Rest rest{list, list_n, ovl, ovl_n, p.list_cap, p.parts, split, kRestExtra};
+        const cfk::Rest rest{list, list_n, ovl, p.list_cap, p.parts, split, kRestExtra,
+                             cur1, uint32_t(p.cursors)};
         f->L.ins(f->table, f->place, keys + lo, len, o, kk, f->ctr,
                  reinterpret_cast<uint32_t *>(f->bulk + p.o_a), 0, log, f->p.max_evict, f->p.seed,
                  rest, cfl::grouped_probe(f->table_bytes, len), int(p.parts * split + kRestExtra),
                  s);
         const cf_status st = check_launch("insert (partitioned)");
-        if (st != CF_OK) return st;
+        if (st != CF_OK) {
+            f->bulk_bytes = 0;  // the cursors may be left dirty: a new workspace next time
+            return st;
+        }
         lo += len;
     }
     return CF_OK;
@@ -618,12 +630,9 @@ cf_status cf_reset(cf_filter *f, void *stream) {
     DeviceGuard g(f->device);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint64_t n64 = f->table_bytes / 8;
-    cfk::zero_words_kernel<<<grid_for(f, n64), kBlock, 0, s>>>(static_cast<uint64_t *>(f->table),
-                                                               n64);
-    cf_status st = check_launch("reset (table)");
-    if (st != CF_OK) return st;
-    cfk::clear_counters_kernel<<<1, 64, 0, s>>>(f->ctr);
-    return check_launch("reset (counters)");
+    cfk::reset_kernel<<<grid_for(f, n64), kBlock, 0, s>>>(static_cast<uint64_t *>(f->table), n64,
+                                                          f->ctr);
+    return check_launch("reset");
 }
 
 cf_status cf_get_params(const cf_filter *f, cf_params *out) {

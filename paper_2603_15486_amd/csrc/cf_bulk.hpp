@@ -36,6 +36,7 @@ constexpr int kSplitTile = kSplitBlock * kSplitItems;
 constexpr uint32_t kMaxBulkBins = 1024;
 constexpr uint32_t kBulkSegs = 8;                         // one per XCD, see bulk_split_kernel
 constexpr int kPlaceBlock = 1024;
+constexpr int kPlaceItems = 4;
 constexpr uint32_t kBulkIdxBits = 27;                     // keys of one partitioned pass
 constexpr uint64_t kMaxBulkKeys = 1ull << kBulkIdxBits;
 
@@ -50,6 +51,11 @@ struct Ents {
 
 struct Ent {
     uint32_t tag, idx, bucket;
+};
+
+struct Raw {  // as loaded: a key, or an entry's words
+    uint64_t a;
+    uint32_t b;
 };
 
 template <int F>
@@ -80,15 +86,17 @@ __device__ __forceinline__ void append_wave(uint32_t *list, uint32_t *count, uin
     list[base + uint32_t(__popcll(on & ((1ull << lane) - 1ull)))] = v;
 }
 
-// Group a tile of up to kSplitTile entries by bin in LDS and copy each bin's
-// run to its place behind the bin's cursor.  item(k, e, bin) yields the
-// thread's k-th entry (false: none).  Every thread of the block calls it.
-// LDS: two tiles' worth of staging and three words per bin; the staging makes
-// the copies runs of consecutive addresses (tile / bins entries each).
-template <int F, class Item>
-__device__ __forceinline__ void split_tile(uint8_t *lds, uint32_t nbins, uint32_t *cursor,
-                                           const Ents &out, uint64_t first_run, uint32_t cap,
-                                           uint32_t *ovl, uint32_t *ovl_n, Item item) {
+// Group a tile of `have` <= kSplitTile entries by bin in LDS and copy each
+// bin's run to its place behind the bin's cursor.  read(j) loads entry j,
+// make(raw, j, bin) decodes it.  Every thread of the block calls it.
+// LDS: one tile of staging and three words per bin; the staging makes the
+// copies runs of consecutive addresses (tile / bins entries each).  All of a
+// thread's loads go out before the first is used.
+template <int F, class Read, class Make>
+__device__ __forceinline__ void split_tile(uint8_t *lds, uint32_t have, uint32_t nbins,
+                                           uint32_t *cursor, const Ents &out, uint64_t first_run,
+                                           uint32_t cap, uint32_t *ovl, uint32_t *ovl_n,
+                                           Read read, Make make) {
     uint64_t *sa = reinterpret_cast<uint64_t *>(lds);
     uint32_t *sb = reinterpret_cast<uint32_t *>(sa + kSplitTile);
     uint16_t *sbin = reinterpret_cast<uint16_t *>(sb + (F == 32 ? kSplitTile : 0));
@@ -97,14 +105,24 @@ __device__ __forceinline__ void split_tile(uint8_t *lds, uint32_t nbins, uint32_
     uint32_t *gb = off + nbins;
     __shared__ uint32_t wsum[kSplitBlock / 64];
     const uint32_t t = threadIdx.x;
+    Raw raw[kSplitItems];
+#pragma unroll
+    for (int k = 0; k < kSplitItems; ++k) {
+        const uint32_t j = uint32_t(k) * kSplitBlock + t;
+        raw[k] = read(j < have ? j : have - 1);
+    }
     for (uint32_t j = t; j < nbins; j += kSplitBlock) hist[j] = 0;
     __syncthreads();
     Ent e[kSplitItems];
     uint32_t bin[kSplitItems], rank[kSplitItems];
 #pragma unroll
     for (int k = 0; k < kSplitItems; ++k) {
+        const uint32_t j = uint32_t(k) * kSplitBlock + t;
         bin[k] = ~0u;
-        if (item(k, e[k], bin[k])) rank[k] = atomicAdd(&hist[bin[k]], 1u);
+        if (j < have) {
+            e[k] = make(raw[k], j, bin[k]);
+            rank[k] = atomicAdd(&hist[bin[k]], 1u);
+        }
     }
     __syncthreads();
     // exclusive scan of the counts: per thread `per` consecutive bins, then
@@ -174,19 +192,18 @@ __global__ __launch_bounds__(kSplitBlock) void bulk_split_kernel(
     uint32_t *__restrict__ kicks, uint32_t *__restrict__ ovl, uint32_t *__restrict__ ovl_n) {
     extern __shared__ __align__(16) uint8_t bulk_lds[];
     const uint32_t lo = blockIdx.x * uint32_t(kSplitTile);
+    const uint32_t have = n - lo < uint32_t(kSplitTile) ? n - lo : uint32_t(kSplitTile);
     const uint32_t x = blockIdx.x % kBulkSegs;
-    split_tile<F>(bulk_lds, nbins, cursor + x * nbins, out, uint64_t(x) * nbins, cap, ovl, ovl_n,
-                  [&](int k, Ent &e, uint32_t &bin) {
-                      const uint32_t i = lo + uint32_t(k) * kSplitBlock + threadIdx.x;
-                      if (i >= n) return false;
-                      const uint64_t key = __builtin_nontemporal_load(keys + i);
-                      const Derived d = derive<Geom<F, 32>, HASH, POL>(key, pl);
-                      if (ok) ok[i] = 1;
-                      if (kicks) kicks[i] = 0;
-                      bin = d.i1 >> shift;
-                      e = Ent{d.t1, i, d.i1 & ((1u << shift) - 1u)};
-                      return true;
-                  });
+    split_tile<F>(
+        bulk_lds, have, nbins, cursor + x * nbins, out, uint64_t(x) * nbins, cap, ovl, ovl_n,
+        [&](uint32_t j) { return Raw{__builtin_nontemporal_load(keys + lo + j), 0u}; },
+        [&](const Raw &r, uint32_t j, uint32_t &bin) {
+            const Derived d = derive<Geom<F, 32>, HASH, POL>(r.a, pl);
+            if (ok) ok[lo + j] = 1;
+            if (kicks) kicks[lo + j] = 0;
+            bin = d.i1 >> shift;
+            return Ent{d.t1, lo + j, d.i1 & ((1u << shift) - 1u)};
+        });
 }
 
 // Second level: the entries of bin c (its kBulkSegs runs of at most cap_in)
@@ -202,28 +219,32 @@ __global__ __launch_bounds__(kSplitBlock) void bulk_resplit_kernel(
     const uint32_t lo = (blockIdx.x % tiles) * uint32_t(kSplitTile);
     if (lo >= have) return;
     const uint32_t c = run % nbins;
-    const uint64_t base = uint64_t(run) * cap_in;
-    split_tile<F>(bulk_lds, 1u << fine, cursor + (c << fine), out, uint64_t(c) << fine, cap, ovl,
-                  ovl_n, [&](int k, Ent &e, uint32_t &bin) {
-                      const uint32_t i = lo + uint32_t(k) * kSplitBlock + threadIdx.x;
-                      if (i >= have) return false;
-                      e = unpack_ent<F>(__builtin_nontemporal_load(in.a + base + i),
-                                        F == 32 ? in.b[base + i] : 0u);
-                      bin = e.bucket >> shift;
-                      e.bucket &= (1u << shift) - 1u;
-                      return true;
-                  });
+    const uint64_t base = uint64_t(run) * cap_in + lo;
+    split_tile<F>(
+        bulk_lds, have - lo < uint32_t(kSplitTile) ? have - lo : uint32_t(kSplitTile), 1u << fine,
+        cursor + (c << fine), out, uint64_t(c) << fine, cap, ovl, ovl_n,
+        [&](uint32_t j) {
+            return Raw{__builtin_nontemporal_load(in.a + base + j), F == 32 ? in.b[base + j] : 0u};
+        },
+        [&](const Raw &r, uint32_t, uint32_t &bin) {
+            Ent e = unpack_ent<F>(r.a, r.b);
+            bin = e.bucket >> shift;
+            e.bucket &= (1u << shift) - 1u;
+            return e;
+        });
 }
 
 // One part (2^shift buckets from bucket part << shift on, the last part cut
 // at m) in LDS: load, try every entry's bucket, store.  An entry whose bucket
-// is full goes to the part's list.  runs / stride: the part's entries lie in
+// is full goes to the part's list; the overflow list's length goes behind the
+// lists' lengths, since the next launch clears the cursors.  runs / stride: the part's entries lie in
 // `runs` runs, run r at (r * stride + part) * cap with count in_n[same].
 template <class G>
 __global__ __launch_bounds__(kPlaceBlock) void bulk_insert_kernel(
     typename G::W *__restrict__ table, uint64_t m, uint32_t shift, Ents in,
     const uint32_t *__restrict__ in_n, uint32_t runs, uint32_t stride, uint32_t cap,
-    uint32_t *__restrict__ list, uint32_t *__restrict__ list_n, uint32_t list_cap, Counters *ctr) {
+    uint32_t *__restrict__ list, uint32_t *__restrict__ list_n, uint32_t list_cap,
+    const uint32_t *__restrict__ ovl_n, Counters *ctr) {
     using W = typename G::W;
     extern __shared__ __align__(16) uint8_t bulk_lds[];
     __shared__ uint32_t s_n;
@@ -249,20 +270,32 @@ __global__ __launch_bounds__(kPlaceBlock) void bulk_insert_kernel(
         const uint64_t run = uint64_t(r) * stride + blockIdx.x;
         const uint32_t have = in_n[run] < cap ? in_n[run] : cap;
         const uint64_t base = run * cap;
-        for (uint32_t i = threadIdx.x; i < have; i += kPlaceBlock) {
-            const Ent e = unpack_ent<G::F>(__builtin_nontemporal_load(in.a + base + i),
-                                           G::F == 32 ? in.b[base + i] : 0u);
-            Bucket<G> bk;
-            load_bucket<G>(part, e.bucket, bk);
-            const bool done = try_insert<G>(part, e.bucket, e.tag, bk) >= 0;
-            placed += done;
-            const uint64_t need = __ballot(!done);
-            if (need) {
-                const int leader = __builtin_ctzll(need);
-                uint32_t at = 0;
-                if (lane == leader) at = atomicAdd(&s_n, uint32_t(__popcll(need)));
-                at = __shfl(at, leader, 64);
-                if (!done) mylist[at + uint32_t(__popcll(need & ((1ull << lane) - 1ull)))] = e.idx;
+        // kPlaceItems entries of a thread are loaded before the first is used
+        for (uint32_t i0 = threadIdx.x; i0 < have; i0 += kPlaceItems * kPlaceBlock) {
+            Raw raw[kPlaceItems];
+#pragma unroll
+            for (int k = 0; k < kPlaceItems; ++k) {
+                const uint32_t i = i0 + uint32_t(k) * kPlaceBlock;
+                const uint64_t at = base + (i < have ? i : i0);
+                raw[k] = Raw{__builtin_nontemporal_load(in.a + at), G::F == 32 ? in.b[at] : 0u};
+            }
+#pragma unroll
+            for (int k = 0; k < kPlaceItems; ++k) {
+                if (i0 + uint32_t(k) * kPlaceBlock >= have) break;
+                const Ent e = unpack_ent<G::F>(raw[k].a, raw[k].b);
+                Bucket<G> bk;
+                load_bucket<G>(part, e.bucket, bk);
+                const bool done = try_insert<G>(part, e.bucket, e.tag, bk) >= 0;
+                placed += done;
+                const uint64_t need = __ballot(!done);
+                if (need) {
+                    const int leader = __builtin_ctzll(need);
+                    uint32_t at = 0;
+                    if (lane == leader) at = atomicAdd(&s_n, uint32_t(__popcll(need)));
+                    at = __shfl(at, leader, 64);
+                    if (!done)
+                        mylist[at + uint32_t(__popcll(need & ((1ull << lane) - 1ull)))] = e.idx;
+                }
             }
         }
     }
@@ -270,7 +303,10 @@ __global__ __launch_bounds__(kPlaceBlock) void bulk_insert_kernel(
     ulonglong2 *hv = reinterpret_cast<ulonglong2 *>(home);
     for (uint32_t j = threadIdx.x; j < vecs; j += kPlaceBlock) hv[j] = lv[j];
     for (uint32_t j = vecs * WPV + threadIdx.x; j < words; j += kPlaceBlock) home[j] = part[j];
-    if (threadIdx.x == 0) list_n[blockIdx.x] = s_n;
+    if (threadIdx.x == 0) {
+        list_n[blockIdx.x] = s_n;
+        if (blockIdx.x == 0) list_n[gridDim.x] = *ovl_n;
+    }
     block_add<kPlaceBlock>(ctr, placed);
 }
 

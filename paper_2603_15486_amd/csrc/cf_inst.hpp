@@ -82,12 +82,12 @@ void resplit(cfk::Ents in, const uint32_t *in_n, uint32_t nbins, uint32_t cap_in
 template <int F, int B>
 void place(void *t, uint64_t m, uint32_t shift, cfk::Ents in, const uint32_t *in_n, uint32_t runs,
            uint32_t stride, uint32_t cap, uint32_t *list, uint32_t *list_n, uint32_t list_cap,
-           Counters *c, int parts, hipStream_t s) {
+           const uint32_t *ovl_n, Counters *c, int parts, hipStream_t s) {
     using G = cfk::Geom<F, B>;
     cfk::bulk_insert_kernel<G>
         <<<parts, cfk::kPlaceBlock, (size_t(B) * F / 8) << shift, s>>>(
             static_cast<typename G::W *>(t), m, shift, in, in_n, runs, stride, cap, list, list_n,
-            list_cap, c);
+            list_cap, ovl_n, c);
 }
 
 template <int F, int B, int POL>

@@ -36,10 +36,11 @@ struct Counters {
 // What a partitioned insert left over (see insert_kernel); list = NULL: none.
 struct Rest {
     const uint32_t *list;    // part p's keys at list[p * cap ..]
-    const uint32_t *list_n;  // how many
+    const uint32_t *list_n;  // how many; behind them the overflow list's length
     const uint32_t *ovl;     // the overflow list
-    const uint32_t *ovl_n;
     uint32_t cap, parts, split, extra;
+    uint32_t *cursors;       // the pass's cursors, to be cleared for the next one
+    uint32_t ncursors;
 };
 
 struct LostLog {
@@ -338,11 +339,12 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
         const uint32_t part = i1_full ? blockIdx.x / rest.split : 0u;
         const uint64_t share = i1_full ? blockIdx.x % rest.split : blockIdx.x - lists;
         const uint64_t of = i1_full ? rest.split : rest.extra;
-        const uint64_t len = i1_full ? rest.list_n[part] : *rest.ovl_n;
+        const uint64_t len = rest.list_n[i1_full ? part : rest.parts];
         const uint64_t lo = len * share / of;
         list = (i1_full ? list + uint64_t(part) * rest.cap : rest.ovl) + lo;
         myq = queue + (i1_full ? uint64_t(part) * rest.cap : uint64_t(rest.parts) * rest.cap) + lo;
         seg = n = len * (share + 1) / of - lo;
+        for (; i < rest.ncursors; i += stride) rest.cursors[i] = 0;
         i = threadIdx.x;
         stride = kBlock;
     }
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(kBlock) void recount_kernel(const typename G::W *__
     block_add(ctr, c);
 }
 
-static __global__ void clear_counters_kernel(Counters *ctr) {
+__device__ __forceinline__ void clear_counters(Counters *ctr) {
     const int t = threadIdx.x;
     if (t < kStripes) ctr->count[t].v = 0;
     if (t == 0) {
@@ -452,6 +454,8 @@ static __global__ void clear_counters_kernel(Counters *ctr) {
         ctr->total = 0;
     }
 }
+
+static __global__ void clear_counters_kernel(Counters *ctr) { clear_counters(ctr); }
 
 // total = sum of the count stripes (one wave).
 static __global__ void sum_counts_kernel(Counters *ctr) {
@@ -461,13 +465,11 @@ static __global__ void sum_counts_kernel(Counters *ctr) {
     if (threadIdx.x == 0) ctr->total = v;
 }
 
-static __global__ __launch_bounds__(kBlock) void zero_words_kernel(uint64_t *__restrict__ p, uint64_t n) {
+// An empty filter: table and counters.
+static __global__ __launch_bounds__(kBlock) void reset_kernel(uint64_t *__restrict__ p, uint64_t n,
+                                                              Counters *ctr) {
     const uint64_t stride = uint64_t(gridDim.x) * kBlock;
-    for (uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += stride) p[i] = 0;
-}
-
-static __global__ __launch_bounds__(kBlock) void zero_u32_kernel(uint32_t *__restrict__ p, uint64_t n) {
-    const uint64_t stride = uint64_t(gridDim.x) * kBlock;
+    if (blockIdx.x == 0) clear_counters(ctr);
     for (uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += stride) p[i] = 0;
 }
 

@@ -32,7 +32,8 @@ struct Launchers {
                     uint32_t *ovl, uint32_t *ovl_n, hipStream_t s);
     void (*place)(void *table, uint64_t m, uint32_t shift, cfk::Ents in, const uint32_t *in_n,
                   uint32_t runs, uint32_t stride, uint32_t cap, uint32_t *list, uint32_t *list_n,
-                  uint32_t list_cap, cfk::Counters *ctr, int parts, hipStream_t s);
+                  uint32_t list_cap, const uint32_t *ovl_n, cfk::Counters *ctr, int parts,
+                  hipStream_t s);
     void (*recount)(const void *table, uint64_t nwords, cfk::Counters *ctr, int grid,
                     hipStream_t s);
     uint64_t words_per_bucket;  // in units of the geometry's word type
