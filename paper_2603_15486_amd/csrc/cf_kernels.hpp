@@ -190,8 +190,13 @@ __device__ __forceinline__ void search_start(Search<G> &st, Derived d, uint64_t 
     st.have = false;
 }
 
-// One level; true once the carried fingerprint is stored.
-template <class G, int HASH, int POL, int PW>
+// One level; true once the carried fingerprint is stored.  KEEP: probed
+// buckets stay in registers, for the move that follows and for the next
+// level.  Without it they are loaded again where they are needed: the set's
+// kernels hold the code of several bucket sizes and measured no gain, and
+// their persistent form would fit fewer blocks (256 threads, 16-bit
+// fingerprints: 5 waves per SIMD for 6).
+template <class G, int HASH, int POL, int PW, bool KEEP>
 __device__ __forceinline__ bool bfs_level(typename G::W *table, const Place &pl, Search<G> &st) {
     using W = typename G::W;
     constexpr int HALF = G::B / 2;
@@ -207,46 +212,57 @@ __device__ __forceinline__ bool bfs_level(typename G::W *table, const Place &pl,
     for (int j0 = 0; j0 < HALF; j0 += PW) {
         Bucket<G> ab[PW];  // the group's other buckets,
         uint32_t cv[PW];   // and its candidates
+        uint32_t ok = 0;
 #pragma unroll
         for (int q = 0; q < PW; ++q) {
             cv[q] = st.cb.slot((r0 + j0 + q) % G::B);
             uint32_t moved = cv[q];
-            uint32_t a = move_tag<G, HASH, POL>(st.cur, moved, pl);
-            if (a == st.cur) cv[q] = 0;
-            // no branch around the load, so that a group's loads go out together
-            load_bucket<G>(table, cv[q] != 0 ? a : st.cur, ab[q]);
+            const uint32_t a = move_tag<G, HASH, POL>(st.cur, moved, pl);
+            if constexpr (KEEP) {
+                // no branch around the load, so that a group's loads go out together
+                if (a == st.cur) cv[q] = 0;
+                load_bucket<G>(table, cv[q] != 0 ? a : st.cur, ab[q]);
+            } else if (cv[q] != 0 && a != st.cur) {
+                Bucket<G> b;
+                load_bucket<G>(table, a, b);
+                if (b.has_empty()) ok |= 1u << q;
+            }
         }
-        uint32_t ok = 0;
+        if constexpr (KEEP) {
 #pragma unroll
-        for (int q = 0; q < PW; ++q) ok |= (cv[q] != 0 && ab[q].has_empty() ? 1u : 0u) << q;
-        last = ab[PW - 1];
-        last_c = cv[PW - 1];
+            for (int q = 0; q < PW; ++q) ok |= (cv[q] != 0 && ab[q].has_empty() ? 1u : 0u) << q;
+        }
+        if constexpr (KEEP) {
+            last = ab[PW - 1];
+            last_c = cv[PW - 1];
+        }
         // in candidate order, the move of the first that takes it (the probed
         // value: the move happens only while the slot holds it)
         while (ok) {
             const int q = __builtin_ctz(ok);
             ok &= ok - 1u;
             const int s = (r0 + j0 + q) % G::B;
-            uint32_t c = cv[0];
-            Bucket<G> mb = ab[0];
+            uint32_t c = 0;
+            Bucket<G> mb{};
 #pragma unroll
-            for (int k = 1; k < PW; ++k) {
-                const uint32_t m32 = 0u - uint32_t(k == q);
-                c = (c & ~m32) | (cv[k] & m32);
-                const W mask = W(0) - W(k == q);
+            for (int k = 0; k < PW; ++k) {
+                c |= cv[k] & (0u - uint32_t(k == q));
+                if constexpr (KEEP) {
+                    const W mask = W(0) - W(k == q);
 #pragma unroll
-                for (int w = 0; w < G::WPB; ++w)
-                    mb.w[w] = (mb.w[w] & ~mask) | (ab[k].w[w] & mask);
+                    for (int w = 0; w < G::WPB; ++w) mb.w[w] |= ab[k].w[w] & mask;
+                }
             }
             uint32_t moved = c;
             const uint32_t a = move_tag<G, HASH, POL>(st.cur, moved, pl);
             if (!replace_slot_if<G>(table, st.cur, s, c, st.tag, st.cb)) continue;
             ++st.kicks;
+            if constexpr (!KEEP) load_bucket<G>(table, a, mb);
             if (try_insert<G>(table, a, moved, mb) >= 0) return true;
             st.tag = moved;  // `a` filled up meanwhile: carry the candidate from there
             st.cur = a;
             st.cb = mb;
-            st.have = true;
+            st.have = KEEP;
             return false;
         }
     }
@@ -255,15 +271,15 @@ __device__ __forceinline__ bool bfs_level(typename G::W *table, const Place &pl,
     if (ev == 0) return true;
     st.tag = ev;
     st.cur = move_tag<G, HASH, POL>(st.cur, st.tag, pl);
-    st.have = true;
-    if (ev == last_c) st.cb = last;
+    st.have = KEEP;
+    if (KEEP && ev == last_c) st.cb = last;
     else load_bucket<G>(table, st.cur, st.cb);
     return st.cb.has_empty() && try_insert<G>(table, st.cur, st.tag, st.cb) >= 0;
 }
 
 // One step of Alg. 1's eviction chain: displace a random slot, carry the
 // displaced fingerprint to its other bucket, try there.
-template <class G, int HASH, int POL>
+template <class G, int HASH, int POL, bool KEEP>
 __device__ __forceinline__ bool dfs_level(typename G::W *table, const Place &pl,
                                           Search<G> &st) {
     const int s = int(splitmix_at(st.rs, ++st.n) % uint64_t(G::B));
@@ -273,26 +289,26 @@ __device__ __forceinline__ bool dfs_level(typename G::W *table, const Place &pl,
     if (ev == 0) return true;
     st.tag = ev;
     st.cur = move_tag<G, HASH, POL>(st.cur, st.tag, pl);
-    st.have = true;
+    st.have = KEEP;
     load_bucket<G>(table, st.cur, st.cb);
     return try_insert<G>(table, st.cur, st.tag, st.cb) >= 0;
 }
 
 // A whole search by one lane; false: the bound was reached, and st.cur and
 // st.tag are the fingerprint dropped.
-template <class G, int HASH, int POL, int PW>
+template <class G, int HASH, int POL, int PW, bool KEEP>
 __device__ __forceinline__ bool evict_bfs(typename G::W *table, const Place &pl,
                                           Search<G> &st, uint32_t max_evict) {
     while (st.n < max_evict)
-        if (bfs_level<G, HASH, POL, PW>(table, pl, st)) return true;
+        if (bfs_level<G, HASH, POL, PW, KEEP>(table, pl, st)) return true;
     return false;
 }
 
-template <class G, int HASH, int POL>
+template <class G, int HASH, int POL, bool KEEP>
 __device__ __forceinline__ bool evict_dfs(typename G::W *table, const Place &pl,
                                           Search<G> &st, uint32_t max_evict) {
     while (st.n < max_evict)
-        if (dfs_level<G, HASH, POL>(table, pl, st)) return true;
+        if (dfs_level<G, HASH, POL, KEEP>(table, pl, st)) return true;
     return false;
 }
 
@@ -408,8 +424,8 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
         if (!busy) continue;
         bool done = false, ended = st.n >= max_evict;
         if (!ended) {
-            if constexpr (EVICT == 1) done = dfs_level<G, HASH, POL>(table, pl, st);
-            else done = bfs_level<G, HASH, POL, PW>(table, pl, st);
+            if constexpr (EVICT == 1) done = dfs_level<G, HASH, POL, true>(table, pl, st);
+            else done = bfs_level<G, HASH, POL, PW, true>(table, pl, st);
             ended = done || st.n >= max_evict;
         }
         if (!ended) continue;

@@ -377,12 +377,12 @@ __device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__r
             if (F.evict == CF_EVICT_DFS) {
                 cfk::Search<G> st;
                 cfk::search_start(st, d, key ^ F.seed);
-                const bool done = cfk::evict_dfs<G, HASH, POL>(table, F.place, st, F.max_evict);
+                const bool done = cfk::evict_dfs<G, HASH, POL, false>(table, F.place, st, F.max_evict);
                 finish(F, fid, i, done, st.cur, st.tag);
             } else {
                 cfk::Search<G> st;
                 cfk::search_start(st, d, key ^ F.seed);
-                const bool done = cfk::evict_bfs<G, HASH, POL, probe_width<G>()>(
+                const bool done = cfk::evict_bfs<G, HASH, POL, probe_width<G>(), false>(
                     table, F.place, st, F.max_evict);
                 finish(F, fid, i, done, st.cur, st.tag);
             }
@@ -409,7 +409,7 @@ __device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__r
                 const Derived d = cfk::derive<G, HASH, POL>(key, F.place);
                 cfk::Search<G> st;
                 cfk::search_start(st, d, key ^ F.seed);
-                const bool done = cfk::evict_dfs<G, HASH, POL>(table, F.place, st, F.max_evict);
+                const bool done = cfk::evict_dfs<G, HASH, POL, false>(table, F.place, st, F.max_evict);
                 finish(F, fid, i, done, st.cur, st.tag);
             }
             uint64_t todo = __ballot(have && !walk);
