@@ -56,7 +56,8 @@ enum { CF_OP_QUERY = 0, CF_OP_DELETE = 1, CF_OP_INSERT = 2 };
  *    barriers.  Only for sets whose filters all share f, hash and placement
  *    (b may differ); others get CF_EUNSUPPORTED.
  * chunk: operations per chunk; a block works on whole chunks (64..4096, a
- * multiple of 64; 0 = default 2048).
+ * multiple of 64; 0 = default 2048).  Batches that would leave compute units
+ * without a block are cut into smaller chunks (not in the persistent form).
  * streams (class kernels): on how many streams the classes run their
  * query-delete-insert chains at the same time (filters of different classes
  * share no state, so only each chain is ordered).  Classes go round-robin
@@ -82,7 +83,11 @@ enum { CF_OP_QUERY = 0, CF_OP_DELETE = 1, CF_OP_INSERT = 2 };
  * delete and one insert launch, all on the caller's stream (streams is then
  * unused).  Same results; needs the same as the persistent form (every
  * filter sharing f, hash and placement), else CF_EUNSUPPORTED.  0 = one
- * launch per (phase, class). */
+ * launch per (phase, class), except that batches (for a graph: max_batch) of
+ * up to 2^15 operations, and of up to 2^18 or 2^20 on sets of few classes,
+ * run one launch per phase and group of classes that share f, hash and
+ * placement on the caller's stream, whatever `streams` says: such batches
+ * last as long as issuing their launches does. */
 typedef struct {
     uint32_t chunk;
     uint32_t streams;

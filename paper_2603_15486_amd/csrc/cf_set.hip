@@ -140,6 +140,12 @@ struct DeviceGuard {
     }
 };
 
+// Classes that share f, hash and placement, and their phase launchers.
+struct PhaseGroup {
+    ClassB classes;
+    PhaseLaunch launch;
+};
+
 }  // namespace cfs
 
 struct cf_set {
@@ -182,9 +188,9 @@ struct cf_set {
     cfs::PersistCtl *d_ctl = nullptr;
     uint32_t persistent = 0, pblock = 256, pblocks_per_cu = 0;
     uint32_t wave_bfs = 0;  // breadth-first search one wave per key
-    // one launch per phase over every class (cf_set_persist.hpp); available
-    // exactly when the persistent form is
-    cfs::PhaseLaunch phase;
+    // one launch per phase (cf_set_persist.hpp) and group of classes that
+    // share f, hash and placement
+    std::vector<cfs::PhaseGroup> groups;
     uint32_t fused = 0;
     std::vector<cfs::Scratch> lanes;  // scratch lanes 1.. (lane 0 is sc)
 };
@@ -217,8 +223,6 @@ struct cf_graph {
 };
 
 namespace cfs {
-
-int grid_of(const cf_set *s, uint64_t n) { return int((n + s->chunk - 1) / s->chunk); }
 
 uint32_t streams_of(const cf_set *s) {
     const uint32_t ncls = uint32_t(s->classes.size());
@@ -266,6 +270,30 @@ cf_status enqueue_persistent(cf_set *s, const Batch &bt, hipStream_t st) {
     return CF_OK;
 }
 
+// Operations per chunk for a batch of n: the shape's, or less for a batch
+// that would leave compute units without a block (a chunk is one block's
+// work in every launch; results do not depend on it).
+uint32_t chunk_for(const cf_set *s, uint64_t n) {
+    uint32_t c = s->chunk;
+    while (c > kSmallChunk && (n + c - 1) / c < uint64_t(s->cus)) c /= 2;
+    return c % 64 ? s->chunk : c;
+}
+
+// Whether a batch of n runs one launch per phase and group of classes (the
+// phase form) although the shape asks for class kernels: up to 2^20
+// operations a batch of class kernels lasts as long as the host takes to
+// issue its launches and events, 15 us per class.  Measured (24 filters,
+// classes / groups, class kernels -> phases): 20 000 operations, 2/1 64 -> 18
+// us, 4/2 110 -> 32, 8/4 151 -> 59; 2^20 operations 84 -> 76, 118 -> 100,
+// 160 -> 145.  Beyond (2^22: 257 -> 287 us at 4/2) the groups' launches one
+// behind another leave more idle than streams do, and so do many groups
+// (12/12: 2^15 operations even, 200 000 182 -> 216 us).
+bool small_batch(const cf_set *s, uint64_t n) {
+    const uint64_t ncls = s->classes.size(), ng = s->groups.size();
+    return n <= (1ull << 15) ||
+           (ng <= 6 && n <= (ncls >= 2 * ng ? 1ull << 20 : 1ull << 18));
+}
+
 // Partition, then per class its query, delete and insert launches in that
 // order.  The phase order only binds operations on one filter and every
 // filter belongs to exactly one class, so chains of different classes may
@@ -274,11 +302,13 @@ cf_status enqueue_persistent(cf_set *s, const Batch &bt, hipStream_t st) {
 // and are waited for at the end.  Concurrent insert launches keep apart in
 // the eviction queue because each uses the slice of its own bin.
 // The class-kernel form on scratch `sc`, with at most max_streams streams.
-cf_status enqueue_classes(cf_set *s, const Batch &bt, int grid, hipStream_t st, const Scratch &sc,
-                          uint32_t max_streams) {
+cf_status enqueue_classes(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st,
+                          const Scratch &sc, uint32_t max_streams) {
     const uint32_t ncls = uint32_t(s->classes.size());
     const uint32_t nb = 3 * ncls;
-    partition_kernel<<<grid, kBlock, 0, st>>>(bt, s->d_cls, s->nfilters, ncls, s->chunk, sc);
+    const uint32_t chunk = chunk_for(s, n);
+    const int grid = int((n + chunk - 1) / chunk);
+    partition_kernel<<<grid, kBlock, 0, st>>>(bt, s->d_cls, s->nfilters, ncls, chunk, sc);
     cf_status r = check_launch("set partition");
     if (r != CF_OK) return r;
     uint32_t L = std::min(streams_of(s), max_streams);
@@ -296,11 +326,11 @@ cf_status enqueue_classes(cf_set *s, const Batch &bt, int grid, hipStream_t st, 
         const uint32_t l = c % L;
         hipStream_t cs = l ? s->side[l - 1] : st;
         const ClassLaunch &k = s->classes[c];
-        k.query(bt, s->d_filters, s->chunk, nb, c, sc, grid, cs);
+        k.query(bt, s->d_filters, chunk, nb, c, sc, grid, cs);
         if ((r = check_launch("set query")) != CF_OK) break;
-        k.del(bt, s->d_filters, s->nfilters, s->chunk, nb, ncls + c, sc, grid, cs);
+        k.del(bt, s->d_filters, s->nfilters, chunk, nb, ncls + c, sc, grid, cs);
         if ((r = check_launch("set delete")) != CF_OK) break;
-        k.ins(bt, s->d_filters, s->nfilters, s->chunk, nb, 2 * ncls + c, sc, s->wave_bfs, grid,
+        k.ins(bt, s->d_filters, s->nfilters, chunk, nb, 2 * ncls + c, sc, s->wave_bfs, grid,
               cs);
         r = check_launch("set insert");
     }
@@ -368,27 +398,39 @@ int verified_fit(cf_set *s, int k) {
 }
 
 // The phase form on scratch `sc`: the partition, then one launch per phase
-// covering every class (grid x classes blocks), all on `st`.
-cf_status enqueue_phases(cf_set *s, const Batch &bt, int grid, hipStream_t st, const Scratch &sc) {
+// and group of classes, all on `st`.
+cf_status enqueue_phases(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st,
+                         const Scratch &sc) {
     const uint32_t ncls = uint32_t(s->classes.size());
-    partition_kernel<<<grid, kBlock, 0, st>>>(bt, s->d_cls, s->nfilters, ncls, s->chunk, sc);
+    const uint32_t chunk = chunk_for(s, n);
+    const int grid = int((n + chunk - 1) / chunk);
+    partition_kernel<<<grid, kBlock, 0, st>>>(bt, s->d_cls, s->nfilters, ncls, chunk, sc);
     cf_status r = check_launch("set partition");
-    if (r != CF_OK) return r;
-    const int pgrid = grid * int(ncls);
-    s->phase.query(bt, s->d_filters, s->class_b, ncls, s->chunk, sc, pgrid, st);
-    if ((r = check_launch("set query phase")) != CF_OK) return r;
-    s->phase.del(bt, s->d_filters, s->class_b, s->nfilters, ncls, s->chunk, sc, pgrid, st);
-    if ((r = check_launch("set delete phase")) != CF_OK) return r;
-    s->phase.ins(bt, s->d_filters, s->class_b, s->nfilters, ncls, s->chunk, sc, s->wave_bfs,
-                 pgrid, st);
-    return check_launch("set insert phase");
+    for (const PhaseGroup &g : s->groups) {
+        if (r != CF_OK) return r;
+        g.launch.query(bt, s->d_filters, g.classes, ncls, chunk, sc, grid * int(g.classes.n), st);
+        r = check_launch("set query phase");
+    }
+    for (const PhaseGroup &g : s->groups) {
+        if (r != CF_OK) return r;
+        g.launch.del(bt, s->d_filters, g.classes, s->nfilters, ncls, chunk, sc,
+                     grid * int(g.classes.n), st);
+        r = check_launch("set delete phase");
+    }
+    for (const PhaseGroup &g : s->groups) {
+        if (r != CF_OK) return r;
+        g.launch.ins(bt, s->d_filters, g.classes, s->nfilters, ncls, chunk, sc, s->wave_bfs,
+                     grid * int(g.classes.n), st);
+        r = check_launch("set insert phase");
+    }
+    return r;
 }
 
 // A batch in the set's current shape, on the set's own scratch.
-cf_status enqueue(cf_set *s, const Batch &bt, int grid, hipStream_t st) {
+cf_status enqueue(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st) {
     if (s->persistent) return enqueue_persistent(s, bt, st);
-    if (s->fused) return enqueue_phases(s, bt, grid, st, s->sc);
-    return enqueue_classes(s, bt, grid, st, s->sc, kMaxStreams);
+    if (s->fused || small_batch(s, n)) return enqueue_phases(s, bt, n, st, s->sc);
+    return enqueue_classes(s, bt, n, st, s->sc, kMaxStreams);
 }
 
 // The persistent form's graph: one kernel node, marked cooperative (a
@@ -563,8 +605,8 @@ cf_status cfs::execute_lane(cf_set *s, uint32_t lane, const uint8_t *ops, const 
         return cferr::fail(CF_EINVAL, "keys not 8-byte aligned");
     DeviceGuard g(s->device);
     const Batch bt{ops, fids, keys, results, n, nullptr, s->max_batch};
-    if (s->fused) return enqueue_phases(s, bt, grid_of(s, n), st, lane_of(s, lane));
-    return enqueue_classes(s, bt, grid_of(s, n), st, lane_of(s, lane), 1);
+    if (s->fused || small_batch(s, n)) return enqueue_phases(s, bt, n, st, lane_of(s, lane));
+    return enqueue_classes(s, bt, n, st, lane_of(s, lane), 1);
 }
 
 cf_status cfs::apply_lane(cf_set *s, uint32_t lane, uint32_t fid, uint32_t op,
@@ -667,21 +709,48 @@ cf_status cf_set_create(const cf_params *params, uint32_t nfilters, uint64_t max
         const cf_params &p = params[i], &q = params[0];
         if (p.fp_bits != q.fp_bits || p.hash != q.hash || p.placement != q.placement)
             s->persist_ok = false;
-        s->class_b.b[s->cls_of[i]] = uint8_t(p.slots_per_bucket);
     }
-    if (s->persist_ok) {
-        const uint32_t f = params[0].fp_bits, h = params[0].hash, pl = params[0].placement;
-        uint32_t bm = 0;  // the largest bucket of the set picks the kernels' b range
-        for (uint32_t i = 0; i < nfilters; ++i) bm = std::max(bm, params[i].slots_per_bucket);
-        s->persist_ok = f == 8    ? cfs::pick_persist_f8(h, pl, bm, s->persist) &&
-                                     cfs::pick_phase_f8(h, pl, bm, s->phase) &&
-                                     cfs::pick_phase_insert_f8(h, pl, bm, s->phase)
-                        : f == 16 ? cfs::pick_persist_f16(h, pl, bm, s->persist) &&
-                                     cfs::pick_phase_f16(h, pl, bm, s->phase) &&
-                                     cfs::pick_phase_insert_f16(h, pl, bm, s->phase)
-                                  : cfs::pick_persist_f32(h, pl, bm, s->persist) &&
-                                     cfs::pick_phase_f32(h, pl, bm, s->phase) &&
-                                     cfs::pick_phase_insert_f32(h, pl, bm, s->phase);
+    // groups: classes that differ in b only
+    std::vector<uint32_t> first;  // a filter of each group
+    for (uint32_t c = 0; c < keys.size(); ++c) {
+        const uint32_t i = uint32_t(std::find(s->cls_of.begin(), s->cls_of.end(), c) -
+                                    s->cls_of.begin());
+        const cf_params &p = params[i];
+        uint32_t g = 0;
+        while (g < first.size() && (params[first[g]].fp_bits != p.fp_bits ||
+                                    params[first[g]].hash != p.hash ||
+                                    params[first[g]].placement != p.placement))
+            ++g;
+        if (g == first.size()) {
+            first.push_back(i);
+            s->groups.push_back({});
+        }
+        cfs::ClassB &cb = s->groups[g].classes;
+        cb.b[cb.n] = uint8_t(p.slots_per_bucket);
+        cb.id[cb.n++] = uint8_t(c);
+    }
+    for (uint32_t g = 0; g < first.size(); ++g) {
+        const uint32_t f = params[first[g]].fp_bits, h = params[first[g]].hash,
+                       pl = params[first[g]].placement;
+        const cfs::ClassB &cb = s->groups[g].classes;
+        // the largest bucket of the group picks the kernels' b range
+        const uint32_t bm = *std::max_element(cb.b, cb.b + cb.n);
+        cfs::PhaseLaunch &L = s->groups[g].launch;
+        const bool got =
+            f == 8 ? cfs::pick_phase_f8(h, pl, bm, L) && cfs::pick_phase_insert_f8(h, pl, bm, L)
+            : f == 16
+                ? cfs::pick_phase_f16(h, pl, bm, L) && cfs::pick_phase_insert_f16(h, pl, bm, L)
+                : cfs::pick_phase_f32(h, pl, bm, L) && cfs::pick_phase_insert_f32(h, pl, bm, L);
+        if (!got) {
+            delete s;
+            return fail(CF_EUNSUPPORTED, "no kernels for f=%u", f);
+        }
+        if (s->persist_ok) {
+            s->class_b = cb;
+            s->persist_ok = f == 8    ? cfs::pick_persist_f8(h, pl, bm, s->persist)
+                            : f == 16 ? cfs::pick_persist_f16(h, pl, bm, s->persist)
+                                      : cfs::pick_persist_f32(h, pl, bm, s->persist);
+        }
     }
     for (int k = 0; s->persist_ok && k < 2; ++k) {
         int fit = 0;
@@ -823,7 +892,7 @@ cf_status cf_set_execute(cf_set *s, const uint8_t *ops, const uint32_t *fids, co
     if (reinterpret_cast<uintptr_t>(keys) & 7u) return fail(CF_EINVAL, "keys not 8-byte aligned");
     cfs::DeviceGuard g(s->device);
     const cfs::Batch bt{ops, fids, keys, results, n, nullptr, s->max_batch};
-    return cfs::enqueue(s, bt, cfs::grid_of(s, n), static_cast<hipStream_t>(stream));
+    return cfs::enqueue(s, bt, n, static_cast<hipStream_t>(stream));
 }
 
 cf_status cf_set_apply(cf_set *s, uint32_t fid, uint32_t op, const uint64_t *keys, uint64_t n,
@@ -861,7 +930,7 @@ cf_status cf_set_graph_create(cf_set *s, const uint8_t *ops, const uint32_t *fid
     if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess) {
         r = fail(CF_EDEVICE, "begin capture failed");
     } else {
-        r = cfs::enqueue(s, bt, cfs::grid_of(s, s->max_batch), st);
+        r = cfs::enqueue(s, bt, s->max_batch, st);
         const hipError_t e = hipStreamEndCapture(st, &gr->graph);
         if (r == CF_OK && e != hipSuccess)
             r = fail(CF_EDEVICE, "end capture: %s", hipGetErrorString(e));

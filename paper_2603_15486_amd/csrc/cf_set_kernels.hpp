@@ -21,6 +21,7 @@ using cfk::kBlock;
 constexpr uint32_t kMaxChunk = 4096;
 constexpr uint32_t kMinChunk = 64;
 constexpr uint32_t kDefaultChunk = 2048;
+constexpr uint32_t kSmallChunk = 256;          // see chunk_for
 constexpr uint32_t kMaxClasses = 16;
 constexpr uint32_t kMaxBins = 3 * kMaxClasses;
 constexpr uint32_t kLdsFilters = 4096;  // per-filter count deltas in LDS up to this many

@@ -64,10 +64,12 @@ struct PersistCtl {
     CtlStamps stamp;
 };
 
-// Bucket size b of each class of the set (all classes share f, hash and
-// placement on this path).
+// The classes a launch covers (all of one f, hash and placement): their
+// numbers in the set and bucket sizes b.
 struct ClassB {
     uint8_t b[kMaxClasses];
+    uint8_t id[kMaxClasses];
+    uint32_t n;
 };
 
 __device__ __forceinline__ unsigned int ld_relaxed(const unsigned int *p) {
@@ -241,13 +243,14 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
 
 // ------------------------------------------------ one launch per phase
 // The class-kernel form with the classes of each phase fused into one
-// launch: grid = chunks x classes, block k working on bin (phase, k mod
-// ncls) of chunk k / ncls with that class's b chosen at run time (with_b).
+// launch: grid = chunks x classes, block k working on the bin of the launch's
+// class k mod cb.n in chunk k / cb.n, with that class's b chosen at run time
+// (with_b).  A set whose classes differ in f, hash or placement has one such
+// launch per phase and group of classes that agree.
 // The queries of every class run side by side in one launch, then every
 // delete, then every insert, all on the caller's stream: no side streams,
 // and a captured batch is a straight chain of four kernels (partition and
-// three phases).  Same qualification as the persistent form (one f, hash and
-// placement, any mix of b).  Bins beyond the batch's chunks are empty (the
+// three phases) if all classes agree.  Bins beyond the batch's chunks are empty (the
 // partition writes empty offsets for them), and a block with an empty bin
 // returns at once, before any barrier.
 
@@ -256,10 +259,10 @@ __global__ __launch_bounds__(kBlock) void phase_query_kernel(Batch bt,
                                                              const SetFilter *__restrict__ filters,
                                                              ClassB cb, uint32_t ncls,
                                                              uint32_t chunk, Scratch sc) {
-    const uint64_t cid = blockIdx.x / ncls;
-    const uint32_t c = blockIdx.x % ncls;
+    const uint64_t cid = blockIdx.x / cb.n;
+    const uint32_t c = blockIdx.x % cb.n;
     uint32_t b0, b1;
-    bin_range(sc, 3 * ncls, cid, c, b0, b1);
+    bin_range(sc, 3 * ncls, cid, cb.id[c], b0, b1);
     if (b0 >= b1) return;
     const uint32_t *seg = sc.sorted + cid * chunk;
     with_b<F, BMAX>(cb.b[c], [&](auto g) {
@@ -274,10 +277,10 @@ __global__ __launch_bounds__(kBlock) void phase_delete_kernel(Batch bt,
                                                               uint32_t ncls, uint32_t chunk,
                                                               Scratch sc) {
     __shared__ int lds[kLdsFilters];
-    const uint64_t cid = blockIdx.x / ncls;
-    const uint32_t c = blockIdx.x % ncls;
+    const uint64_t cid = blockIdx.x / cb.n;
+    const uint32_t c = blockIdx.x % cb.n;
     uint32_t b0, b1;
-    bin_range(sc, 3 * ncls, cid, ncls + c, b0, b1);
+    bin_range(sc, 3 * ncls, cid, ncls + cb.id[c], b0, b1);
     if (b0 >= b1) return;  // the same in every thread of the block
     Tally<kBlock> tally{lds, nfilters};
     tally.init();
@@ -296,10 +299,10 @@ __global__ __launch_bounds__(kBlock) void phase_insert_kernel(Batch bt,
                                                               Scratch sc, uint32_t wave_bfs) {
     __shared__ int lds[kLdsFilters];
     __shared__ uint32_t s_qn;
-    const uint64_t cid = blockIdx.x / ncls;
-    const uint32_t c = blockIdx.x % ncls;
+    const uint64_t cid = blockIdx.x / cb.n;
+    const uint32_t c = blockIdx.x % cb.n;
     uint32_t b0, b1;
-    bin_range(sc, 3 * ncls, cid, 2 * ncls + c, b0, b1);
+    bin_range(sc, 3 * ncls, cid, 2 * ncls + cb.id[c], b0, b1);
     if (b0 >= b1) return;  // the same in every thread of the block
     Tally<kBlock> tally{lds, nfilters};
     tally.init();
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(kBlock) void phase_insert_kernel(Batch bt,
 }
 
 // Host launchers of the three phase kernels for one (f, hash, placement).
-// grid = chunks x classes.
+// grid = chunks x classes of the launch; ncls = classes of the set.
 struct PhaseLaunch {
     void (*query)(Batch, const SetFilter *, ClassB, uint32_t ncls, uint32_t chunk, Scratch,
                   int grid, hipStream_t) = nullptr;
