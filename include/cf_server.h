@@ -9,13 +9,14 @@
  * any thread; a scheduler thread owned by the server forms batches
  * continuously: whenever a batch slot is free it takes the pending requests,
  * in arrival order, that fit the batch (max_batch operations, max_requests
- * requests) and executes them as one mixed batch of the filter set, while
- * the previous batches are still on the device.  Each of the `depth` slots
+ * requests) and executes them together on the filter set (one launch per
+ * phase for the filters that share f, hash and placement, reading keys and
+ * writing results in the requests' own arrays), while the previous batches
+ * are still on the device.  Each of the `depth` slots
  * has a stream and a scratch lane of its own, so batches in different slots
  * run on the device at the same time; a batch waits (on the device, by
  * event) only for the in-flight batches that touch one of its filters.
- * Server batches always run the set's class-kernel form with the class
- * chains on the slot's stream (the persistent form takes the whole device).
+ * The set's launch shape does not apply to them, except wave_bfs.
  * Each operation is the filter operation of Cuckoo-GPU (arXiv 2603.15486):
  * Alg. 2 query, Alg. 3 delete, Alg. 1 insert with the eviction search of
  * Sec. 4.6.1.
@@ -29,8 +30,8 @@
  * Modes.  CF_SERVE_BATCHED is the loop above.  CF_SERVE_PER_REQUEST runs
  * each request alone as one kernel launch on its filter (cf_set_apply), in
  * arrival order, with up to `depth` requests in flight: the baseline.  A
- * mixed batch costs a fixed chain of launches (table copy, gather, the set's
- * partition and phase kernels, scatter), so batched mode adapts to the load
+ * batch costs a fixed chain (table copy and phase kernels), so batched mode
+ * adapts to the load
  * (direct_below): while fewer than direct_below requests are pending, each
  * free slot takes one request and runs it as one launch, so a light load is
  * served with the per-request latency and requests still run side by side

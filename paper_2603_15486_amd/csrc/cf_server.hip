@@ -4,11 +4,10 @@
 // One scheduler thread owns `depth` batch slots, each with a HIP stream of
 // its own and a scratch lane of the filter set.  Whenever a slot is free it
 // takes pending requests in arrival order that fit the batch and keep
-// per-filter arrival order (see cf_server.h), copies the request table to
-// the device, and enqueues on the slot's stream: a gather kernel that lays
-// the requests' keys out as one mixed batch, the filter set's batch
-// kernels, and a scatter kernel that writes each request's results back,
-// then records the slot's event.  Batches in different slots run at the
+// per-filter arrival order (see cf_server.h), copies a table of them to the
+// device ordered by phase and class, and enqueues the set's request kernels
+// on the slot's stream, which read keys and write results in the requests'
+// own arrays, then records the slot's event.  Batches in different slots run at the
 // same time on the device; a batch waits (by event, on the device) only for
 // the in-flight batches that touch one of its filters, which keeps each
 // filter's arrival order.  A slot retires as soon as its event completes,
@@ -51,49 +50,6 @@ struct Req {
     bool done = false;
 };
 
-// Device-side request table entry; `off` is the request's first operation
-// in the batch, entries sorted by `off`.
-struct Entry {
-    const uint64_t *keys;
-    uint8_t *results;
-    uint64_t off;
-    uint32_t fid;
-    uint32_t op;
-};
-
-__device__ __forceinline__ uint32_t find_entry(const Entry *tab, uint32_t nreq, uint64_t j) {
-    uint32_t lo = 0, hi = nreq;  // last entry with off <= j
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (tab[mid].off <= j) lo = mid;
-        else hi = mid;
-    }
-    return lo;
-}
-
-__global__ __launch_bounds__(kBlock) void gather_kernel(const Entry *__restrict__ tab, uint32_t nreq,
-                                                        uint64_t total, uint8_t *__restrict__ ops,
-                                                        uint32_t *__restrict__ fids,
-                                                        uint64_t *__restrict__ keys) {
-    const uint64_t stride = uint64_t(gridDim.x) * kBlock;
-    for (uint64_t j = uint64_t(blockIdx.x) * kBlock + threadIdx.x; j < total; j += stride) {
-        const Entry &e = tab[find_entry(tab, nreq, j)];
-        ops[j] = uint8_t(e.op);
-        fids[j] = e.fid;
-        keys[j] = e.keys[j - e.off];
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void scatter_kernel(const Entry *__restrict__ tab, uint32_t nreq,
-                                                         uint64_t total,
-                                                         const uint8_t *__restrict__ res) {
-    const uint64_t stride = uint64_t(gridDim.x) * kBlock;
-    for (uint64_t j = uint64_t(blockIdx.x) * kBlock + threadIdx.x; j < total; j += stride) {
-        const Entry &e = tab[find_entry(tab, nreq, j)];
-        e.results[j - e.off] = res[j];
-    }
-}
-
 __global__ __launch_bounds__(kBlock) void fill_kernel(uint8_t *__restrict__ p, uint64_t n,
                                                       uint8_t v) {
     const uint64_t stride = uint64_t(gridDim.x) * kBlock;
@@ -106,12 +62,8 @@ int grid_for(uint64_t n) {
 }
 
 struct Slot {
-    uint8_t *d_ops = nullptr;
-    uint32_t *d_fids = nullptr;
-    uint64_t *d_keys = nullptr;
-    uint8_t *d_res = nullptr;
-    Entry *h_tab = nullptr;  // pinned
-    Entry *d_tab = nullptr;
+    cfs::ReqEntry *h_tab = nullptr;  // the batch's request table, pinned,
+    cfs::ReqEntry *d_tab = nullptr;  // and its copy on the device
     hipStream_t stream = nullptr;  // the slot's own stream (default priority)
     hipEvent_t done = nullptr;
     std::vector<Req *> reqs;
@@ -150,6 +102,7 @@ struct cf_server {
     std::vector<int8_t> fb_maxph;
     std::vector<uint8_t> fb_blocked;
     std::vector<uint32_t> fb_touched;
+    std::vector<cfs::Request> batch;  // the batch being launched (scheduler thread only)
 
     std::mutex mu;
     std::condition_variable cv_sched, cv_done;
@@ -350,24 +303,11 @@ cf_status launch(cf_server *s, int slot_idx, std::vector<Req *> &take) {
             if (st != CF_OK) break;
         }
     } else {
-        uint64_t off = 0;
-        for (size_t k = 0; k < take.size(); ++k) {
-            sl.h_tab[k] = Entry{take[k]->keys, take[k]->results, off, take[k]->fid, take[k]->op};
-            off += take[k]->n;
-        }
-        const uint32_t nreq = uint32_t(take.size());
-        if (hipMemcpyAsync(sl.d_tab, sl.h_tab, nreq * sizeof(Entry), hipMemcpyHostToDevice,
-                           sl.stream) != hipSuccess) {
-            st = fail(CF_EDEVICE, "request table copy failed");
-        } else {
-            gather_kernel<<<grid_for(off), kBlock, 0, sl.stream>>>(sl.d_tab, nreq, off, sl.d_ops,
-                                                                   sl.d_fids, sl.d_keys);
-            st = cfs::execute_lane(s->set, lane_of(slot_idx), sl.d_ops, sl.d_fids, sl.d_keys,
-                                   off, sl.d_res, sl.stream);
-            if (st == CF_OK)
-                scatter_kernel<<<grid_for(off), kBlock, 0, sl.stream>>>(sl.d_tab, nreq, off,
-                                                                        sl.d_res);
-        }
+        std::vector<cfs::Request> &rq = s->batch;
+        rq.clear();
+        for (const Req *r : take) rq.push_back({r->fid, r->op, r->keys, r->results, r->n});
+        st = cfs::requests_lane(s->set, lane_of(slot_idx), rq.data(), uint32_t(rq.size()),
+                                sl.h_tab, sl.d_tab, sl.stream);
     }
     if (st == CF_OK && hipGetLastError() != hipSuccess) st = fail(CF_EDEVICE, "batch launch failed");
     // Every path records the slot's event and hands the requests to the slot,
@@ -455,10 +395,6 @@ void scheduler(cf_server *s) {
 
 void free_slots_mem(cf_server *s) {
     for (Slot &sl : s->slots) {
-        if (sl.d_ops) (void)hipFree(sl.d_ops);
-        if (sl.d_fids) (void)hipFree(sl.d_fids);
-        if (sl.d_keys) (void)hipFree(sl.d_keys);
-        if (sl.d_res) (void)hipFree(sl.d_res);
         if (sl.d_tab) (void)hipFree(sl.d_tab);
         if (sl.h_tab) (void)hipHostFree(sl.h_tab);
         if (sl.done) (void)hipEventDestroy(sl.done);
@@ -520,12 +456,9 @@ cf_status cf_server_create(const cf_params *params, uint32_t nfilters,
         okall = hipEventCreateWithFlags(&sl.done, hipEventDisableTiming) == hipSuccess &&
                 hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking) == hipSuccess;
         if (okall && batched)
-            okall = hipMalloc(&sl.d_ops, cfg->max_batch) == hipSuccess &&
-                    hipMalloc(&sl.d_fids, cfg->max_batch * 4) == hipSuccess &&
-                    hipMalloc(&sl.d_keys, cfg->max_batch * 8) == hipSuccess &&
-                    hipMalloc(&sl.d_res, cfg->max_batch) == hipSuccess &&
-                    hipMalloc(&sl.d_tab, cfg->max_requests * sizeof(cfv::Entry)) == hipSuccess &&
-                    hipHostMalloc(&sl.h_tab, cfg->max_requests * sizeof(cfv::Entry)) == hipSuccess;
+            okall = hipMalloc(&sl.d_tab, cfg->max_requests * cfs::req_entry_bytes()) == hipSuccess &&
+                    hipHostMalloc(&sl.h_tab, cfg->max_requests * cfs::req_entry_bytes()) ==
+                        hipSuccess;
         s->free_slots.push_back(int(k));
     }
     if (!okall) {

@@ -32,6 +32,8 @@
 #include "cf_set_internal.hpp"
 #include "cf_set_kernels.hpp"
 #include "cf_set_persist.hpp"
+#include "cf_set_requests.hpp"
+
 namespace cfs {
 
 // ------------------------------------------------------------- partition
@@ -301,9 +303,8 @@ bool small_batch(const cf_set *s, uint64_t n) {
 // the caller's and the others side streams that wait for the partition
 // and are waited for at the end.  Concurrent insert launches keep apart in
 // the eviction queue because each uses the slice of its own bin.
-// The class-kernel form on scratch `sc`, with at most max_streams streams.
-cf_status enqueue_classes(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st,
-                          const Scratch &sc, uint32_t max_streams) {
+cf_status enqueue_classes(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st) {
+    const Scratch &sc = s->sc;
     const uint32_t ncls = uint32_t(s->classes.size());
     const uint32_t nb = 3 * ncls;
     const uint32_t chunk = chunk_for(s, n);
@@ -311,7 +312,7 @@ cf_status enqueue_classes(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st
     partition_kernel<<<grid, kBlock, 0, st>>>(bt, s->d_cls, s->nfilters, ncls, chunk, sc);
     cf_status r = check_launch("set partition");
     if (r != CF_OK) return r;
-    uint32_t L = std::min(streams_of(s), max_streams);
+    uint32_t L = streams_of(s);
     if (L > 1 && hipEventRecord(s->fork, st) != hipSuccess) {
         (void)hipGetLastError();
         L = 1;  // no fork recorded: every chain on the caller's stream
@@ -397,10 +398,10 @@ int verified_fit(cf_set *s, int k) {
     return fit;
 }
 
-// The phase form on scratch `sc`: the partition, then one launch per phase
-// and group of classes, all on `st`.
-cf_status enqueue_phases(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st,
-                         const Scratch &sc) {
+// The phase form: the partition, then one launch per phase and group of
+// classes, all on `st`.
+cf_status enqueue_phases(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st) {
+    const Scratch &sc = s->sc;
     const uint32_t ncls = uint32_t(s->classes.size());
     const uint32_t chunk = chunk_for(s, n);
     const int grid = int((n + chunk - 1) / chunk);
@@ -429,8 +430,8 @@ cf_status enqueue_phases(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st,
 // A batch in the set's current shape, on the set's own scratch.
 cf_status enqueue(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st) {
     if (s->persistent) return enqueue_persistent(s, bt, st);
-    if (s->fused || small_batch(s, n)) return enqueue_phases(s, bt, n, st, s->sc);
-    return enqueue_classes(s, bt, n, st, s->sc, kMaxStreams);
+    if (s->fused || small_batch(s, n)) return enqueue_phases(s, bt, n, st);
+    return enqueue_classes(s, bt, n, st);
 }
 
 // The persistent form's graph: one kernel node, marked cooperative (a
@@ -532,11 +533,8 @@ void free_all(cf_set *s) {
                     s->sc.binoff,   s->d_ctl};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
-    for (const Scratch &l : s->lanes) {
-        if (l.sorted) (void)hipFree(l.sorted);
+    for (const Scratch &l : s->lanes)
         if (l.queue) (void)hipFree(l.queue);
-        if (l.binoff) (void)hipFree(l.binoff);
-    }
     s->lanes.clear();
     for (hipStream_t t : s->side) (void)hipStreamDestroy(t);
     for (hipEvent_t e : s->join) (void)hipEventDestroy(e);
@@ -572,16 +570,9 @@ cf_status cfs::reserve_lanes(cf_set *s, uint32_t n) {
     if (!s || n == 0 || n > 64) return cferr::fail(CF_EINVAL, "lanes must be in [1, 64]");
     DeviceGuard g(s->device);
     while (lane_count(s) < n) {
-        Scratch l{};
-        const Layout &L = s->layout;
-        const bool ok = hipMalloc(&l.sorted, L.sorted_entries * 4) == hipSuccess &&
-                        hipMalloc(&l.queue, L.queue_entries * 4) == hipSuccess &&
-                        hipMalloc(&l.binoff, L.binoff_entries * 4) == hipSuccess;
-        if (!ok) {
+        Scratch l{};  // requests need no more than the eviction queue
+        if (hipMalloc(&l.queue, s->layout.queue_entries * 4) != hipSuccess) {
             (void)hipGetLastError();
-            if (l.sorted) (void)hipFree(l.sorted);
-            if (l.queue) (void)hipFree(l.queue);
-            if (l.binoff) (void)hipFree(l.binoff);
             return cferr::fail(CF_ENOMEM, "cannot allocate a scratch lane");
         }
         s->lanes.push_back(l);
@@ -593,20 +584,82 @@ static const cfs::Scratch &lane_of(const cf_set *s, uint32_t lane) {
     return lane == 0 ? s->sc : s->lanes[lane - 1];
 }
 
-cf_status cfs::execute_lane(cf_set *s, uint32_t lane, const uint8_t *ops, const uint32_t *fids,
-                            const uint64_t *keys, uint64_t n, uint8_t *results, hipStream_t st) {
-    if (!s || lane >= lane_count(s)) return cferr::fail(CF_EINVAL, "bad set or lane");
-    if (n == 0) return CF_OK;
-    if (n > s->max_batch)
-        return cferr::fail(CF_EINVAL, "batch of %llu exceeds max_batch %llu",
-                           (unsigned long long)n, (unsigned long long)s->max_batch);
-    if (!ops || !fids || !keys || !results) return cferr::fail(CF_EINVAL, "NULL batch buffer");
-    if (reinterpret_cast<uintptr_t>(keys) & 7u)
-        return cferr::fail(CF_EINVAL, "keys not 8-byte aligned");
-    DeviceGuard g(s->device);
-    const Batch bt{ops, fids, keys, results, n, nullptr, s->max_batch};
-    if (s->fused || small_batch(s, n)) return enqueue_phases(s, bt, n, st, lane_of(s, lane));
-    return enqueue_classes(s, bt, n, st, lane_of(s, lane), 1);
+uint64_t cfs::req_entry_bytes() { return sizeof(ReqEntry); }
+
+cf_status cfs::requests_lane(cf_set *s, uint32_t lane, const Request *reqs, uint32_t count,
+                             ReqEntry *h_tab, ReqEntry *d_tab, hipStream_t st) {
+    using cferr::fail;
+    if (!s || lane >= lane_count(s) || !reqs || !h_tab || !d_tab)
+        return fail(CF_EINVAL, "bad argument");
+    const uint32_t ncls = uint32_t(s->classes.size());
+    // requests and operations per (phase, class), then their first table
+    // entries and positions: phase by phase, the classes of a group together
+    uint32_t ne[kMaxBins] = {}, e0[kMaxBins];
+    uint64_t nj[kMaxBins] = {}, j0[kMaxBins], total = 0;
+    for (uint32_t k = 0; k < count; ++k) {
+        const Request &r = reqs[k];
+        if (r.fid >= s->nfilters || r.op > CF_OP_INSERT || !r.keys || !r.results ||
+            !s->tables[r.fid])
+            return fail(CF_EINVAL, "bad request");
+        const uint32_t bin = r.op * ncls + s->cls_of[r.fid];
+        ne[bin]++;
+        nj[bin] += r.n;
+        total += r.n;
+    }
+    if (total > s->max_batch) return fail(CF_EINVAL, "requests exceed max_batch");
+    uint32_t e = 0;
+    uint64_t j = 0;
+    for (uint32_t op = 0; op < 3; ++op)
+        for (const PhaseGroup &g : s->groups)
+            for (uint32_t c = 0; c < g.classes.n; ++c) {
+                const uint32_t bin = op * ncls + g.classes.id[c];
+                e0[bin] = e;
+                j0[bin] = j;
+                e += ne[bin];
+                j += nj[bin];
+            }
+    uint32_t ce[kMaxBins];
+    uint64_t cj[kMaxBins];
+    std::copy(e0, e0 + 3 * ncls, ce);
+    std::copy(j0, j0 + 3 * ncls, cj);
+    for (uint32_t k = 0; k < count; ++k) {
+        const Request &r = reqs[k];
+        const uint32_t bin = r.op * ncls + s->cls_of[r.fid];
+        h_tab[ce[bin]++] = ReqEntry{r.keys, r.results, uint32_t(cj[bin]), r.fid};
+        cj[bin] += r.n;
+    }
+    DeviceGuard dg(s->device);
+    if (hipMemcpyAsync(d_tab, h_tab, count * sizeof(ReqEntry), hipMemcpyHostToDevice, st) !=
+        hipSuccess)
+        return fail(CF_EDEVICE, "request table copy failed");
+    for (uint32_t op = 0; op < 3; ++op)
+        for (const PhaseGroup &g : s->groups) {
+            ReqSpan sp{};
+            uint32_t blocks = 0;
+            for (uint32_t c = 0; c < g.classes.n; ++c) {
+                const uint32_t bin = op * ncls + g.classes.id[c];
+                if (nj[bin] == 0) continue;
+                sp.b[sp.n] = g.classes.b[c];
+                sp.blk[sp.n] = blocks;
+                sp.j0[sp.n] = uint32_t(j0[bin]);
+                sp.j1[sp.n] = uint32_t(j0[bin] + nj[bin]);
+                sp.e0[sp.n] = e0[bin];
+                sp.e1[sp.n] = e0[bin] + ne[bin];
+                sp.n++;
+                blocks += uint32_t((nj[bin] + kReqOps - 1) / kReqOps);
+            }
+            if (blocks == 0) continue;
+            if (op == CF_OP_QUERY)
+                g.launch.req_query(sp, d_tab, s->d_filters, int(blocks), st);
+            else if (op == CF_OP_DELETE)
+                g.launch.req_del(sp, d_tab, s->d_filters, s->nfilters, int(blocks), st);
+            else
+                g.launch.req_ins(sp, d_tab, s->d_filters, s->nfilters, lane_of(s, lane).queue,
+                                 s->wave_bfs, int(blocks), st);
+            const cf_status r = check_launch("set requests");
+            if (r != CF_OK) return r;
+        }
+    return CF_OK;
 }
 
 cf_status cfs::apply_lane(cf_set *s, uint32_t lane, uint32_t fid, uint32_t op,

@@ -154,21 +154,39 @@ struct Tally {
     }
 };
 
-// The per-bin work of the three phases, for the operations seg[b0 .. b1) of
-// one chunk (seg = the chunk's sorted operation indices), done by one block
-// of BT threads.  The class kernels below run one bin per block; the
-// persistent kernel (cf_set_persist.hpp) runs every bin of its chunks.
+// One operation as the phases see it, and where its flag goes.
+struct Op {
+    uint32_t fid;
+    uint64_t key;
+    uint8_t *result;
+};
+
+// A chunk's operations in bin order: position p is operation seg[p].
+struct ChunkSrc {
+    const Batch &bt;
+    const uint32_t *seg;
+    __device__ __forceinline__ Op get(uint32_t p) const {
+        const uint32_t i = seg[p];
+        return Op{bt.fids[i], bt.keys[i], bt.results + i};
+    }
+};
+
+// The per-bin work of the three phases, for the operations at positions
+// [b0, b1) of a source, done by one block of BT threads.  The class kernels
+// below run one bin of a chunk per block; the persistent kernel
+// (cf_set_persist.hpp) runs every bin of its chunks, the request kernels
+// (cf_set_requests.hpp) a stretch of requests.
 
 // Alg. 2: probe i1, and i2 only when i1 misses.
-template <class G, int HASH, int POL, int BT>
-__device__ __forceinline__ void query_bin(const Batch &bt, const SetFilter *__restrict__ filters,
-                                          const uint32_t *seg, uint32_t b0, uint32_t b1) {
+template <class G, int HASH, int POL, int BT, class Src>
+__device__ __forceinline__ void query_bin(const Src &src, const SetFilter *__restrict__ filters,
+                                          uint32_t b0, uint32_t b1) {
     using W = typename G::W;
     for (uint32_t p = b0 + threadIdx.x; p < b1; p += BT) {
-        const uint32_t i = seg[p];
-        const SetFilter &F = filters[bt.fids[i]];
+        const Op o = src.get(p);
+        const SetFilter &F = filters[o.fid];
         const W *table = static_cast<const W *>(F.table);
-        const Derived d = cfk::derive<G, HASH, POL>(bt.keys[i], F.place);
+        const Derived d = cfk::derive<G, HASH, POL>(o.key, F.place);
         cfk::Bucket<G> bk;
         cfk::load_bucket<G>(table, d.i1, bk);
         bool hit = bk.contains(d.t1);
@@ -176,22 +194,20 @@ __device__ __forceinline__ void query_bin(const Batch &bt, const SetFilter *__re
             cfk::load_bucket<G>(table, d.i2, bk);
             hit = bk.contains(d.t2);
         }
-        bt.results[i] = uint8_t(hit);
+        *o.result = uint8_t(hit);
     }
 }
 
 // Alg. 3: remove one copy from i1, else from i2.
-template <class G, int HASH, int POL, int BT>
-__device__ __forceinline__ void delete_bin(const Batch &bt, const SetFilter *__restrict__ filters,
-                                           const uint32_t *seg, uint32_t b0, uint32_t b1,
-                                           Tally<BT> &tally) {
+template <class G, int HASH, int POL, int BT, class Src>
+__device__ __forceinline__ void delete_bin(const Src &src, const SetFilter *__restrict__ filters,
+                                           uint32_t b0, uint32_t b1, Tally<BT> &tally) {
     using W = typename G::W;
     for (uint32_t p = b0 + threadIdx.x; p < b1; p += BT) {
-        const uint32_t i = seg[p];
-        const uint32_t fid = bt.fids[i];
-        const SetFilter &F = filters[fid];
+        const Op o = src.get(p);
+        const SetFilter &F = filters[o.fid];
         W *table = static_cast<W *>(F.table);
-        const Derived d = cfk::derive<G, HASH, POL>(bt.keys[i], F.place);
+        const Derived d = cfk::derive<G, HASH, POL>(o.key, F.place);
         cfk::Bucket<G> bk;
         cfk::load_bucket<G>(table, d.i1, bk);
         bool done = cfk::try_remove<G>(table, d.i1, d.t1, bk);
@@ -199,8 +215,8 @@ __device__ __forceinline__ void delete_bin(const Batch &bt, const SetFilter *__r
             cfk::load_bucket<G>(table, d.i2, bk);
             done = cfk::try_remove<G>(table, d.i2, d.t2, bk);
         }
-        if (done) tally.add(F, fid, -1);
-        bt.results[i] = uint8_t(done);
+        if (done) tally.add(F, o.fid, -1);
+        *o.result = uint8_t(done);
     }
 }
 
@@ -307,11 +323,10 @@ __device__ bool evict_bfs_wave(typename G::W *table, const cfk::Place &pl, uint6
 // key (wave_bfs = 1, evict_bfs_wave; the queued keys are dealt to the
 // block's waves in turn).  s_qn is an LDS counter of the block; every thread
 // of the block calls this (it has block barriers).
-template <class G, int HASH, int POL, int BT>
-__device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__restrict__ filters,
-                                           const uint32_t *seg, uint32_t b0, uint32_t b1,
-                                           uint32_t *myq, uint32_t *s_qn, Tally<BT> &tally,
-                                           uint32_t wave_bfs) {
+template <class G, int HASH, int POL, int BT, class Src>
+__device__ __forceinline__ void insert_bin(const Src &src, const SetFilter *__restrict__ filters,
+                                           uint32_t b0, uint32_t b1, uint32_t *myq, uint32_t *s_qn,
+                                           Tally<BT> &tally, uint32_t wave_bfs) {
     using W = typename G::W;
     if (threadIdx.x == 0) *s_qn = 0;
     __syncthreads();  // s_qn = 0 before any wave adds to it
@@ -323,11 +338,10 @@ __device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__r
         const uint32_t p = p0 + threadIdx.x;
         bool need_evict = false;
         if (p < b1) {
-            const uint32_t i = seg[p];
-            const uint32_t fid = bt.fids[i];
-            const SetFilter &F = filters[fid];
+            const Op o = src.get(p);
+            const SetFilter &F = filters[o.fid];
             W *table = static_cast<W *>(F.table);
-            const Derived d = cfk::derive<G, HASH, POL>(bt.keys[i], F.place);
+            const Derived d = cfk::derive<G, HASH, POL>(o.key, F.place);
             cfk::Bucket<G> bk;
             cfk::load_bucket<G>(table, d.i1, bk);
             bool done = cfk::try_insert<G>(table, d.i1, d.t1, bk) >= 0;
@@ -336,8 +350,8 @@ __device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__r
                 done = cfk::try_insert<G>(table, d.i2, d.t2, bk) >= 0;
             }
             if (done) {
-                tally.add(F, fid, 1);
-                bt.results[i] = 1;
+                tally.add(F, o.fid, 1);
+                *o.result = 1;
             }
             need_evict = !done;
         }
@@ -354,10 +368,9 @@ __device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__r
     __syncthreads();
     const uint32_t qn = *s_qn < qcap ? *s_qn : qcap;
     // the outcome of one queued key's search
-    auto finish = [&](const SetFilter &F, uint32_t fid, uint32_t i, bool done, uint32_t lb,
-                      uint32_t lt) {
+    auto finish = [&](const SetFilter &F, const Op &o, bool done, uint32_t lb, uint32_t lt) {
         if (done) {
-            tally.add(F, fid, 1);
+            tally.add(F, o.fid, 1);
         } else {
             const unsigned long long slot = atomicAdd(&F.ctr->failures, 1ull);
             if (slot < F.lost_cap) {
@@ -365,27 +378,25 @@ __device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__r
                 F.lost_tag[slot] = lt;
             }
         }
-        bt.results[i] = uint8_t(done);
+        *o.result = uint8_t(done);
     };
     if (!wave_bfs) {
         for (uint32_t q = threadIdx.x; q < qn; q += BT) {
-            const uint32_t i = seg[myq[q]];
-            const uint32_t fid = bt.fids[i];
-            const SetFilter &F = filters[fid];
+            const Op o = src.get(myq[q]);
+            const SetFilter &F = filters[o.fid];
             W *table = static_cast<W *>(F.table);
-            const uint64_t key = bt.keys[i];
-            const Derived d = cfk::derive<G, HASH, POL>(key, F.place);
+            const Derived d = cfk::derive<G, HASH, POL>(o.key, F.place);
             if (F.evict == CF_EVICT_DFS) {
                 cfk::Search<G> st;
-                cfk::search_start(st, d, key ^ F.seed);
+                cfk::search_start(st, d, o.key ^ F.seed);
                 const bool done = cfk::evict_dfs<G, HASH, POL, false>(table, F.place, st, F.max_evict);
-                finish(F, fid, i, done, st.cur, st.tag);
+                finish(F, o, done, st.cur, st.tag);
             } else {
                 cfk::Search<G> st;
-                cfk::search_start(st, d, key ^ F.seed);
+                cfk::search_start(st, d, o.key ^ F.seed);
                 const bool done = cfk::evict_bfs<G, HASH, POL, probe_width<G>(), false>(
                     table, F.place, st, F.max_evict);
-                finish(F, fid, i, done, st.cur, st.tag);
+                finish(F, o, done, st.cur, st.tag);
             }
         }
     } else {
@@ -396,39 +407,37 @@ __device__ __forceinline__ void insert_bin(const Batch &bt, const SetFilter *__r
         for (uint32_t base = 0; wave + NW * base < qn; base += 64) {  // uniform per wave
             const uint32_t q = wave + NW * (base + uint32_t(lane));
             const bool have = q < qn;
-            uint32_t i = 0, fid = 0;
+            uint32_t p = 0;
             bool walk = false;
             if (have) {
-                i = seg[myq[q]];
-                fid = bt.fids[i];
-                walk = filters[fid].evict == CF_EVICT_DFS;
+                p = myq[q];
+                walk = filters[src.get(p).fid].evict == CF_EVICT_DFS;
             }
             if (walk) {  // the random walk stays one lane per key
-                const SetFilter &F = filters[fid];
+                const Op o = src.get(p);
+                const SetFilter &F = filters[o.fid];
                 W *table = static_cast<W *>(F.table);
-                const uint64_t key = bt.keys[i];
-                const Derived d = cfk::derive<G, HASH, POL>(key, F.place);
+                const Derived d = cfk::derive<G, HASH, POL>(o.key, F.place);
                 cfk::Search<G> st;
-                cfk::search_start(st, d, key ^ F.seed);
+                cfk::search_start(st, d, o.key ^ F.seed);
                 const bool done = cfk::evict_dfs<G, HASH, POL, false>(table, F.place, st, F.max_evict);
-                finish(F, fid, i, done, st.cur, st.tag);
+                finish(F, o, done, st.cur, st.tag);
             }
             uint64_t todo = __ballot(have && !walk);
             while (todo) {  // uniform: one key at a time, the whole wave on it
                 const int l = __builtin_ctzll(todo);
                 todo &= todo - 1;
-                const uint32_t il = __shfl(i, l), fl = __shfl(fid, l);
-                const SetFilter &F = filters[fl];
+                const Op o = src.get(__shfl(p, l));
+                const SetFilter &F = filters[o.fid];
                 W *table = static_cast<W *>(F.table);
-                const uint64_t key = bt.keys[il];
-                const Derived d = cfk::derive<G, HASH, POL>(key, F.place);
-                const uint64_t rs = key ^ F.seed;
+                const Derived d = cfk::derive<G, HASH, POL>(o.key, F.place);
+                const uint64_t rs = o.key ^ F.seed;
                 const bool second = (cfk::splitmix_at(rs, 0) & 1) != 0;
                 uint32_t k = 0, lb = 0, lt = 0;
                 const bool done = evict_bfs_wave<G, HASH, POL>(
                     table, F.place, rs, second ? d.i2 : d.i1, second ? d.t2 : d.t1, F.max_evict,
                     k, lb, lt);
-                if (lane == 0) finish(F, fl, il, done, lb, lt);
+                if (lane == 0) finish(F, o, done, lb, lt);
             }
         }
     }
@@ -445,7 +454,8 @@ __global__ __launch_bounds__(kBlock) void set_query_kernel(Batch bt,
                                                            uint32_t bin, Scratch sc) {
     uint32_t b0, b1;
     bin_range(sc, nb, blockIdx.x, bin, b0, b1);
-    query_bin<G, HASH, POL, kBlock>(bt, filters, sc.sorted + uint64_t(blockIdx.x) * chunk, b0, b1);
+    query_bin<G, HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + uint64_t(blockIdx.x) * chunk}, filters,
+                                    b0, b1);
 }
 
 template <class G, int HASH, int POL>
@@ -458,8 +468,8 @@ __global__ __launch_bounds__(kBlock) void set_delete_kernel(Batch bt,
     tally.init();
     uint32_t b0, b1;
     bin_range(sc, nb, blockIdx.x, bin, b0, b1);
-    delete_bin<G, HASH, POL, kBlock>(bt, filters, sc.sorted + uint64_t(blockIdx.x) * chunk, b0,
-                                     b1, tally);
+    delete_bin<G, HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + uint64_t(blockIdx.x) * chunk},
+                                     filters, b0, b1, tally);
     tally.flush(filters);
 }
 
@@ -476,8 +486,8 @@ __global__ __launch_bounds__(kBlock) void set_insert_kernel(Batch bt,
     uint32_t b0, b1;
     bin_range(sc, nb, blockIdx.x, bin, b0, b1);
     const uint64_t base = uint64_t(blockIdx.x) * chunk;
-    insert_bin<G, HASH, POL, kBlock>(bt, filters, sc.sorted + base, b0, b1, sc.queue + base + b0,
-                                     &s_qn, tally, wave_bfs);
+    insert_bin<G, HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + base}, filters, b0, b1,
+                                     sc.queue + base + b0, &s_qn, tally, wave_bfs);
     tally.flush(filters);
 }
 

@@ -36,6 +36,7 @@
 #pragma once
 
 #include "cf_set_kernels.hpp"
+#include "cf_set_requests.hpp"
 
 namespace cfs {
 
@@ -145,24 +146,6 @@ __device__ __forceinline__ bool grid_sync(PersistCtl *ctl, unsigned int &gen, ui
     return s_ok != 0;
 }
 
-// Run fn(Geom<F, b>{}) for the bucket sizes the library compiles, up to
-// BMAX slots.  A kernel holds the code of every bucket size it may meet and
-// takes the registers of the largest: the 32-slot insert path alone limits
-// a kernel to 4 waves per SIMD, so sets whose buckets have at most 16 slots
-// get kernels without it (BMAX = 16).
-template <int F, int BMAX, class Fn>
-__device__ __forceinline__ void with_b(uint32_t b, Fn &&fn) {
-    switch (b) {
-        case 4: fn(cfk::Geom<F, 4>{}); break;
-        case 8: fn(cfk::Geom<F, 8>{}); break;
-        case 16: fn(cfk::Geom<F, 16>{}); break;
-        case 32:
-            if constexpr (BMAX >= 32) fn(cfk::Geom<F, 32>{});
-            break;
-        default: break;
-    }
-}
-
 template <int F, int HASH, int POL, int BT, int BMAX>
 __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *__restrict__ filters,
                                                      const uint8_t *__restrict__ cls, ClassB cb,
@@ -201,7 +184,7 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
             bin_range(sc, nb, cid, c, b0, b1);
             if (b0 < b1)
                 with_b<F, BMAX>(cb.b[c], [&](auto g) {
-                    query_bin<decltype(g), HASH, POL, BT>(bt, filters, seg, b0, b1);
+                    query_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, seg}, filters, b0, b1);
                 });
         }
     }
@@ -216,7 +199,7 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
             bin_range(sc, nb, cid, ncls + c, b0, b1);
             if (b0 < b1)
                 with_b<F, BMAX>(cb.b[c], [&](auto g) {
-                    delete_bin<decltype(g), HASH, POL, BT>(bt, filters, seg, b0, b1, tally);
+                    delete_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, seg}, filters, b0, b1, tally);
                 });
         }
     }
@@ -232,9 +215,9 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
             bin_range(sc, nb, cid, 2 * ncls + c, b0, b1);
             if (b0 < b1)  // uniform across the block: insert_bin has block barriers
                 with_b<F, BMAX>(cb.b[c], [&](auto g) {
-                    insert_bin<decltype(g), HASH, POL, BT>(bt, filters, sc.sorted + at, b0, b1,
-                                                           sc.queue + at + b0, &s_qn, tally,
-                                                           wave_bfs);
+                    insert_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, sc.sorted + at}, filters,
+                                                           b0, b1, sc.queue + at + b0, &s_qn,
+                                                           tally, wave_bfs);
                 });
         }
     }
@@ -266,7 +249,7 @@ __global__ __launch_bounds__(kBlock) void phase_query_kernel(Batch bt,
     if (b0 >= b1) return;
     const uint32_t *seg = sc.sorted + cid * chunk;
     with_b<F, BMAX>(cb.b[c], [&](auto g) {
-        query_bin<decltype(g), HASH, POL, kBlock>(bt, filters, seg, b0, b1);
+        query_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, seg}, filters, b0, b1);
     });
 }
 
@@ -286,7 +269,7 @@ __global__ __launch_bounds__(kBlock) void phase_delete_kernel(Batch bt,
     tally.init();
     const uint32_t *seg = sc.sorted + cid * chunk;
     with_b<F, BMAX>(cb.b[c], [&](auto g) {
-        delete_bin<decltype(g), HASH, POL, kBlock>(bt, filters, seg, b0, b1, tally);
+        delete_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, seg}, filters, b0, b1, tally);
     });
     tally.flush(filters);
 }
@@ -308,7 +291,7 @@ __global__ __launch_bounds__(kBlock) void phase_insert_kernel(Batch bt,
     tally.init();
     const uint64_t at = cid * chunk;
     with_b<F, BMAX>(cb.b[c], [&](auto g) {
-        insert_bin<decltype(g), HASH, POL, kBlock>(bt, filters, sc.sorted + at, b0, b1,
+        insert_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + at}, filters, b0, b1,
                                                    sc.queue + at + b0, &s_qn, tally, wave_bfs);
     });
     tally.flush(filters);
@@ -323,6 +306,12 @@ struct PhaseLaunch {
                 uint32_t chunk, Scratch, int grid, hipStream_t) = nullptr;
     void (*ins)(Batch, const SetFilter *, ClassB, uint32_t nfilters, uint32_t ncls,
                 uint32_t chunk, Scratch, uint32_t wave_bfs, int grid, hipStream_t) = nullptr;
+    void (*req_query)(const ReqSpan &, const ReqEntry *, const SetFilter *, int grid,
+                      hipStream_t) = nullptr;
+    void (*req_del)(const ReqSpan &, const ReqEntry *, const SetFilter *, uint32_t nfilters,
+                    int grid, hipStream_t) = nullptr;
+    void (*req_ins)(const ReqSpan &, const ReqEntry *, const SetFilter *, uint32_t nfilters,
+                    uint32_t *queue, uint32_t wave_bfs, int grid, hipStream_t) = nullptr;
 };
 
 template <int F, int HASH, int POL, int BMAX>
@@ -340,6 +329,19 @@ struct PhaseInst {
         phase_insert_kernel<F, HASH, POL, BMAX>
             <<<grid, kBlock, 0, s>>>(bt, fl, cb, nf, ncls, chunk, sc, wave_bfs);
     }
+    static void req_query(const ReqSpan &sp, const ReqEntry *tab, const SetFilter *fl, int grid,
+                          hipStream_t s) {
+        req_query_kernel<F, HASH, POL, BMAX><<<grid, kBlock, 0, s>>>(sp, tab, fl);
+    }
+    static void req_del(const ReqSpan &sp, const ReqEntry *tab, const SetFilter *fl, uint32_t nf,
+                        int grid, hipStream_t s) {
+        req_delete_kernel<F, HASH, POL, BMAX><<<grid, kBlock, 0, s>>>(sp, tab, fl, nf);
+    }
+    static void req_ins(const ReqSpan &sp, const ReqEntry *tab, const SetFilter *fl, uint32_t nf,
+                        uint32_t *queue, uint32_t wave_bfs, int grid, hipStream_t s) {
+        req_insert_kernel<F, HASH, POL, BMAX>
+            <<<grid, kBlock, 0, s>>>(sp, tab, fl, nf, queue, wave_bfs);
+    }
 };
 
 // Fills the query and delete launchers (INSERT = false) or the insert
@@ -352,9 +354,12 @@ bool pick_phase_fb(uint32_t hash, uint32_t placement, PhaseLaunch &L) {
         using I = decltype(inst);
         if constexpr (INSERT) {
             L.ins = &I::ins;
+            L.req_ins = &I::req_ins;
         } else {
             L.query = &I::query;
             L.del = &I::del;
+            L.req_query = &I::req_query;
+            L.req_del = &I::req_del;
         }
     };
     if (hash == 0)
@@ -371,7 +376,8 @@ bool pick_phase_f(uint32_t hash, uint32_t placement, uint32_t bmax, PhaseLaunch 
 }
 
 // Per fingerprint width: query and delete in cf_set_inst_f*.hip, insert in
-// cf_set_persist_insi_f*.hip (built at -O1).
+// cf_set_persist_insi_f*.hip (built at -O1).  The request kernels' launchers
+// (cf_set_requests.hpp) come with them.
 bool pick_phase_f8(uint32_t hash, uint32_t placement, uint32_t bmax, PhaseLaunch &out);
 bool pick_phase_f16(uint32_t hash, uint32_t placement, uint32_t bmax, PhaseLaunch &out);
 bool pick_phase_f32(uint32_t hash, uint32_t placement, uint32_t bmax, PhaseLaunch &out);
