@@ -398,18 +398,22 @@ int verified_fit(cf_set *s, int k) {
     return fit;
 }
 
-// The phase form: the partition, then one launch per phase and group of
-// classes, all on `st`.
+// The phase form: one launch per phase and group of classes, all on `st`;
+// the first sorts the batch as well.
 cf_status enqueue_phases(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st) {
     const Scratch &sc = s->sc;
     const uint32_t ncls = uint32_t(s->classes.size());
     const uint32_t chunk = chunk_for(s, n);
     const int grid = int((n + chunk - 1) / chunk);
-    partition_kernel<<<grid, kBlock, 0, st>>>(bt, s->d_cls, s->nfilters, ncls, chunk, sc);
-    cf_status r = check_launch("set partition");
+    cf_status r = CF_OK;
     for (const PhaseGroup &g : s->groups) {
         if (r != CF_OK) return r;
-        g.launch.query(bt, s->d_filters, g.classes, ncls, chunk, sc, grid * int(g.classes.n), st);
+        if (&g == &s->groups[0])  // it sorts the batch for the others too
+            g.launch.front(bt, s->d_filters, s->d_cls, g.classes, s->nfilters, ncls, chunk, sc,
+                           grid, st);
+        else
+            g.launch.query(bt, s->d_filters, g.classes, ncls, chunk, sc,
+                           grid * int(g.classes.n), st);
         r = check_launch("set query phase");
     }
     for (const PhaseGroup &g : s->groups) {

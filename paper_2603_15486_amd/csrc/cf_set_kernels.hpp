@@ -56,7 +56,9 @@ struct Batch {
 // Batch scratch, laid out per chunk of `chunk` operations (chunk c covers
 // operations [c * chunk, (c + 1) * chunk)).
 struct Scratch {
-    uint32_t *sorted;  // per chunk: its operation indices grouped by bin
+    uint32_t *sorted;  // per chunk: its operations grouped by bin, each as
+                       // filter id * kMaxChunk + place in the chunk (16 + 12
+                       // bits, so a phase need not fetch the id again)
     uint32_t *binoff;  // per chunk: nbins + 1 bin starts within the chunk
     uint32_t *queue;   // per chunk: keys deferred to the eviction pass, each bin
                        // in the slice [b0, b1) of its own range
@@ -68,9 +70,13 @@ __device__ __forceinline__ uint64_t batch_n(const Batch &bt) {
     return n < bt.cap ? n : bt.cap;
 }
 
+__device__ __forceinline__ uint32_t sorted_entry(uint32_t fid, uint32_t place) {
+    return fid * kMaxChunk + place;  // an invalid id may wrap: its entry is never used
+}
+
 // Sort chunk `cid` of the batch by bin = (kind, class) with a block of BT
 // threads: count in LDS, store the bin starts at binoff[cid * (nb + 1) ..]
-// and the operations' indices bin by bin at sorted[cid * chunk ..].  Invalid
+// and the operations bin by bin at sorted[cid * chunk ..].  Invalid
 // kinds and ids, and detached filters (class 0xFF), go to bin nb with result
 // 0xFF.  No global atomics; each operation's kind and filter id are read
 // twice (count, then place), its key never.  hist and base: LDS arrays of
@@ -112,7 +118,7 @@ __device__ __forceinline__ void partition_chunk(const Batch &bt, uint64_t n,
     for (uint64_t i = lo + threadIdx.x; i < hi; i += BT) {
         const uint32_t bin = bin_of(i);
         const uint32_t pos = atomicAdd(&hist[bin], 1u);
-        seg[pos] = uint32_t(i);
+        seg[pos] = sorted_entry(bt.fids[i], uint32_t(i - lo));
         if (bin == nb) bt.results[i] = 0xFF;
     }
     __syncthreads();  // hist and base are free again
@@ -161,13 +167,15 @@ struct Op {
     uint8_t *result;
 };
 
-// A chunk's operations in bin order: position p is operation seg[p].
+// A chunk's operations in bin order (see Scratch::sorted); lo: its first.
 struct ChunkSrc {
     const Batch &bt;
     const uint32_t *seg;
+    uint64_t lo;
     __device__ __forceinline__ Op get(uint32_t p) const {
-        const uint32_t i = seg[p];
-        return Op{bt.fids[i], bt.keys[i], bt.results + i};
+        const uint32_t v = seg[p];
+        const uint64_t i = lo + (v & (kMaxChunk - 1));
+        return Op{v / kMaxChunk, bt.keys[i], bt.results + i};
     }
 };
 
@@ -178,23 +186,27 @@ struct ChunkSrc {
 // (cf_set_requests.hpp) a stretch of requests.
 
 // Alg. 2: probe i1, and i2 only when i1 misses.
+template <class G, int HASH, int POL>
+__device__ __forceinline__ bool query_one(const SetFilter &F, uint64_t key) {
+    using W = typename G::W;
+    const W *table = static_cast<const W *>(F.table);
+    const Derived d = cfk::derive<G, HASH, POL>(key, F.place);
+    cfk::Bucket<G> bk;
+    cfk::load_bucket<G>(table, d.i1, bk);
+    bool hit = bk.contains(d.t1);
+    if (!hit) {
+        cfk::load_bucket<G>(table, d.i2, bk);
+        hit = bk.contains(d.t2);
+    }
+    return hit;
+}
+
 template <class G, int HASH, int POL, int BT, class Src>
 __device__ __forceinline__ void query_bin(const Src &src, const SetFilter *__restrict__ filters,
                                           uint32_t b0, uint32_t b1) {
-    using W = typename G::W;
     for (uint32_t p = b0 + threadIdx.x; p < b1; p += BT) {
         const Op o = src.get(p);
-        const SetFilter &F = filters[o.fid];
-        const W *table = static_cast<const W *>(F.table);
-        const Derived d = cfk::derive<G, HASH, POL>(o.key, F.place);
-        cfk::Bucket<G> bk;
-        cfk::load_bucket<G>(table, d.i1, bk);
-        bool hit = bk.contains(d.t1);
-        if (!hit) {
-            cfk::load_bucket<G>(table, d.i2, bk);
-            hit = bk.contains(d.t2);
-        }
-        *o.result = uint8_t(hit);
+        *o.result = uint8_t(query_one<G, HASH, POL>(filters[o.fid], o.key));
     }
 }
 
@@ -454,8 +466,9 @@ __global__ __launch_bounds__(kBlock) void set_query_kernel(Batch bt,
                                                            uint32_t bin, Scratch sc) {
     uint32_t b0, b1;
     bin_range(sc, nb, blockIdx.x, bin, b0, b1);
-    query_bin<G, HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + uint64_t(blockIdx.x) * chunk}, filters,
-                                    b0, b1);
+    query_bin<G, HASH, POL, kBlock>(
+        ChunkSrc{bt, sc.sorted + uint64_t(blockIdx.x) * chunk, uint64_t(blockIdx.x) * chunk},
+        filters, b0, b1);
 }
 
 template <class G, int HASH, int POL>
@@ -468,8 +481,9 @@ __global__ __launch_bounds__(kBlock) void set_delete_kernel(Batch bt,
     tally.init();
     uint32_t b0, b1;
     bin_range(sc, nb, blockIdx.x, bin, b0, b1);
-    delete_bin<G, HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + uint64_t(blockIdx.x) * chunk},
-                                     filters, b0, b1, tally);
+    delete_bin<G, HASH, POL, kBlock>(
+        ChunkSrc{bt, sc.sorted + uint64_t(blockIdx.x) * chunk, uint64_t(blockIdx.x) * chunk},
+        filters, b0, b1, tally);
     tally.flush(filters);
 }
 
@@ -486,7 +500,7 @@ __global__ __launch_bounds__(kBlock) void set_insert_kernel(Batch bt,
     uint32_t b0, b1;
     bin_range(sc, nb, blockIdx.x, bin, b0, b1);
     const uint64_t base = uint64_t(blockIdx.x) * chunk;
-    insert_bin<G, HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + base}, filters, b0, b1,
+    insert_bin<G, HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + base, base}, filters, b0, b1,
                                      sc.queue + base + b0, &s_qn, tally, wave_bfs);
     tally.flush(filters);
 }

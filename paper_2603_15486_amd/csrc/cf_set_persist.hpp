@@ -184,7 +184,7 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
             bin_range(sc, nb, cid, c, b0, b1);
             if (b0 < b1)
                 with_b<F, BMAX>(cb.b[c], [&](auto g) {
-                    query_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, seg}, filters, b0, b1);
+                    query_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, seg, cid * chunk}, filters, b0, b1);
                 });
         }
     }
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
             bin_range(sc, nb, cid, ncls + c, b0, b1);
             if (b0 < b1)
                 with_b<F, BMAX>(cb.b[c], [&](auto g) {
-                    delete_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, seg}, filters, b0, b1, tally);
+                    delete_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, seg, cid * chunk}, filters, b0, b1, tally);
                 });
         }
     }
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
             bin_range(sc, nb, cid, 2 * ncls + c, b0, b1);
             if (b0 < b1)  // uniform across the block: insert_bin has block barriers
                 with_b<F, BMAX>(cb.b[c], [&](auto g) {
-                    insert_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, sc.sorted + at}, filters,
+                    insert_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, sc.sorted + at, at}, filters,
                                                            b0, b1, sc.queue + at + b0, &s_qn,
                                                            tally, wave_bfs);
                 });
@@ -237,6 +237,105 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
 // partition writes empty offsets for them), and a block with an empty bin
 // returns at once, before any barrier.
 
+// The partition and the queries of the launch's classes in one: a chunk's
+// operations are loaded once, in order, and sorted by bin in LDS; the queries
+// run from LDS, their flags are collected there and written in order, and
+// what the later launches need (every other operation's entry and the bin
+// starts) goes to the scratch as in partition_chunk.  Apart, the partition
+// read every kind and id twice and the queries then fetched entry, id and key
+// one behind another from scattered places before their first probe.
+// LDS per block: 13 bytes per operation of the chunk.
+constexpr int kFrontBlock = 512;
+constexpr int kFrontItems = int(kMaxChunk) / kFrontBlock;
+inline size_t front_lds(uint32_t chunk) { return size_t(chunk) * 13; }
+
+template <int F, int HASH, int POL, int BMAX>
+__global__ __launch_bounds__(kFrontBlock) void phase_front_kernel(
+    Batch bt, const SetFilter *__restrict__ filters, const uint8_t *__restrict__ cls, ClassB cb,
+    uint32_t nfilters, uint32_t ncls, uint32_t chunk, Scratch sc) {
+    extern __shared__ __align__(16) uint8_t front_mem[];
+    uint64_t *s_key = reinterpret_cast<uint64_t *>(front_mem);
+    uint32_t *s_ent = reinterpret_cast<uint32_t *>(s_key + chunk);
+    uint8_t *s_res = reinterpret_cast<uint8_t *>(s_ent + chunk);
+    __shared__ uint32_t hist[kMaxBins + 1], base[kMaxBins + 2];
+    __shared__ uint8_t s_b[kMaxClasses];  // b of the launch's classes, 0: not one of them
+    const uint64_t n = batch_n(bt);
+    const uint64_t lo = uint64_t(blockIdx.x) * chunk;
+    const uint32_t have = lo >= n ? 0u : n - lo < chunk ? uint32_t(n - lo) : chunk;
+    const uint32_t nb = 3 * ncls, t = threadIdx.x;
+    for (uint32_t j = t; j <= nb; j += kFrontBlock) hist[j] = 0;
+    if (t < kMaxClasses) s_b[t] = 0;
+    __syncthreads();
+    if (t < cb.n) s_b[cb.id[t]] = cb.b[t];
+    uint64_t key[kFrontItems];
+    uint32_t fid[kFrontItems], bin[kFrontItems], rank[kFrontItems];
+#pragma unroll
+    for (int k = 0; k < kFrontItems; ++k) {
+        const uint32_t j = uint32_t(k) * kFrontBlock + t;
+        bin[k] = ~0u;
+        if (j < have) {
+            bin[k] = bt.ops[lo + j];
+            fid[k] = bt.fids[lo + j];
+            key[k] = bt.keys[lo + j];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kFrontItems; ++k)
+        if (bin[k] != ~0u) {
+            uint32_t x = nb;
+            if (bin[k] <= 2u && fid[k] < nfilters) {
+                const uint32_t c = cls[fid[k]];
+                if (c < ncls) x = bin[k] * ncls + c;  // 0xFF: filter detached
+            }
+            bin[k] = x;
+            rank[k] = atomicAdd(&hist[x], 1u);
+        }
+    __syncthreads();
+    if (t < 64) {  // bin starts: one wave, at most 49 bins
+        const uint32_t mine = t <= nb ? hist[t] : 0u;
+        uint32_t inc = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(inc, d, 64);
+            if (t >= uint32_t(d)) inc += o;
+        }
+        if (t <= nb) {
+            base[t] = inc - mine;
+            sc.binoff[uint64_t(blockIdx.x) * (nb + 1) + t] = inc - mine;
+        }
+    }
+    __syncthreads();
+    const uint32_t nq = base[ncls];  // queries come first
+#pragma unroll
+    for (int k = 0; k < kFrontItems; ++k)
+        if (bin[k] != ~0u) {
+            const uint32_t j = uint32_t(k) * kFrontBlock + t;
+            const uint32_t p = base[bin[k]] + rank[k];
+            s_ent[p] = sorted_entry(fid[k], j);
+            if (p < nq) s_key[p] = key[k];
+        }
+    __syncthreads();
+    for (uint32_t p = t; p < have; p += kFrontBlock) sc.sorted[lo + p] = s_ent[p];
+    uint32_t c = 0;
+    for (uint32_t p = t; p < nq; p += kFrontBlock) {
+        while (p >= base[c + 1]) ++c;
+        const uint32_t v = s_ent[p];
+        bool hit = false;
+        with_b<F, BMAX>(s_b[c], [&](auto g) {
+            hit = query_one<decltype(g), HASH, POL>(filters[v / kMaxChunk], s_key[p]);
+        });
+        s_res[v & (kMaxChunk - 1)] = uint8_t(hit);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kFrontItems; ++k) {
+        if (bin[k] == ~0u) continue;
+        const uint32_t j = uint32_t(k) * kFrontBlock + t;
+        if (bin[k] == nb) bt.results[lo + j] = 0xFF;
+        else if (bin[k] < ncls && s_b[bin[k]]) bt.results[lo + j] = s_res[j];
+    }
+}
+
 template <int F, int HASH, int POL, int BMAX>
 __global__ __launch_bounds__(kBlock) void phase_query_kernel(Batch bt,
                                                              const SetFilter *__restrict__ filters,
@@ -249,7 +348,7 @@ __global__ __launch_bounds__(kBlock) void phase_query_kernel(Batch bt,
     if (b0 >= b1) return;
     const uint32_t *seg = sc.sorted + cid * chunk;
     with_b<F, BMAX>(cb.b[c], [&](auto g) {
-        query_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, seg}, filters, b0, b1);
+        query_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, seg, cid * chunk}, filters, b0, b1);
     });
 }
 
@@ -269,7 +368,7 @@ __global__ __launch_bounds__(kBlock) void phase_delete_kernel(Batch bt,
     tally.init();
     const uint32_t *seg = sc.sorted + cid * chunk;
     with_b<F, BMAX>(cb.b[c], [&](auto g) {
-        delete_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, seg}, filters, b0, b1, tally);
+        delete_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, seg, cid * chunk}, filters, b0, b1, tally);
     });
     tally.flush(filters);
 }
@@ -291,7 +390,7 @@ __global__ __launch_bounds__(kBlock) void phase_insert_kernel(Batch bt,
     tally.init();
     const uint64_t at = cid * chunk;
     with_b<F, BMAX>(cb.b[c], [&](auto g) {
-        insert_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + at}, filters, b0, b1,
+        insert_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + at, at}, filters, b0, b1,
                                                    sc.queue + at + b0, &s_qn, tally, wave_bfs);
     });
     tally.flush(filters);
@@ -300,6 +399,8 @@ __global__ __launch_bounds__(kBlock) void phase_insert_kernel(Batch bt,
 // Host launchers of the three phase kernels for one (f, hash, placement).
 // grid = chunks x classes of the launch; ncls = classes of the set.
 struct PhaseLaunch {
+    void (*front)(Batch, const SetFilter *, const uint8_t *cls, ClassB, uint32_t nfilters,
+                  uint32_t ncls, uint32_t chunk, Scratch, int chunks, hipStream_t) = nullptr;
     void (*query)(Batch, const SetFilter *, ClassB, uint32_t ncls, uint32_t chunk, Scratch,
                   int grid, hipStream_t) = nullptr;
     void (*del)(Batch, const SetFilter *, ClassB, uint32_t nfilters, uint32_t ncls,
@@ -316,6 +417,11 @@ struct PhaseLaunch {
 
 template <int F, int HASH, int POL, int BMAX>
 struct PhaseInst {
+    static void front(Batch bt, const SetFilter *fl, const uint8_t *cls, ClassB cb, uint32_t nf,
+                      uint32_t ncls, uint32_t chunk, Scratch sc, int chunks, hipStream_t s) {
+        phase_front_kernel<F, HASH, POL, BMAX><<<chunks, kFrontBlock, front_lds(chunk), s>>>(
+            bt, fl, cls, cb, nf, ncls, chunk, sc);
+    }
     static void query(Batch bt, const SetFilter *fl, ClassB cb, uint32_t ncls, uint32_t chunk,
                       Scratch sc, int grid, hipStream_t s) {
         phase_query_kernel<F, HASH, POL, BMAX><<<grid, kBlock, 0, s>>>(bt, fl, cb, ncls, chunk, sc);
@@ -356,6 +462,7 @@ bool pick_phase_fb(uint32_t hash, uint32_t placement, PhaseLaunch &L) {
             L.ins = &I::ins;
             L.req_ins = &I::req_ins;
         } else {
+            L.front = &I::front;
             L.query = &I::query;
             L.del = &I::del;
             L.req_query = &I::req_query;
