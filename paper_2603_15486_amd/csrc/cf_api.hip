@@ -200,7 +200,7 @@ struct BulkPlan {
     uint32_t cap1, cap2;        // entries per run of a bin, per part (fine > 0)
     uint32_t list_cap;
     uint64_t cursors;           // cursors and overflow count; zero between passes
-    uint64_t o_cur, o_listn, o_a, o_a32, o_b, o_b32, o_list, o_ovl, bytes;
+    uint64_t o_cur, o_listn, o_a, o_a32, o_b, o_b32, o_list, o_list32, o_ovl, bytes;
 };
 
 constexpr uint64_t kPartBytes = 64 << 10;
@@ -245,16 +245,17 @@ BulkPlan bulk_plan(const cf_filter *f, uint64_t len) {
         p.bytes += (bytes + 255) & ~uint64_t(255);
         return o;
     };
-    p.cursors = uint64_t(p.bins) * cfk::kBulkSegs + (p.fine ? p.parts : 0) + 1;
+    p.cursors = 2 * (uint64_t(p.bins) * cfk::kBulkSegs + (p.fine ? p.parts : 0)) + 1;
     p.o_cur = take(p.cursors * 4);
     p.o_listn = take((uint64_t(p.parts) + 1) * 4);
     // the first level's entries, and later (they are used up by then) the
-    // eviction queues of the keys left over
-    p.o_a = take(std::max(n1 * 8, (lists + len) * 4));
+    // eviction queue of the overflow list
+    p.o_a = take(n1 * 8);  // n1 >= len
     p.o_a32 = take(n1 * wide);
     p.o_b = take(n2 * 8);
     p.o_b32 = take(n2 * wide);
-    p.o_list = take(lists * 4);
+    p.o_list = take(lists * 8);
+    p.o_list32 = take(lists * wide);
     p.o_ovl = take(len * 4);
     return p;
 }
@@ -302,32 +303,38 @@ cf_status bulk_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *o
                           reinterpret_cast<uint32_t *>(f->bulk + p.o_a32)};
         const cfk::Ents b{reinterpret_cast<uint64_t *>(f->bulk + p.o_b),
                           reinterpret_cast<uint32_t *>(f->bulk + p.o_b32)};
-        uint32_t *cur1 = reinterpret_cast<uint32_t *>(f->bulk + p.o_cur);
-        uint32_t *cur2 = cur1 + uint64_t(p.bins) * cfk::kBulkSegs;
-        uint32_t *ovl_n = cur1 + p.cursors - 1;
+        const cfk::Ents list{reinterpret_cast<uint64_t *>(f->bulk + p.o_list),
+                             reinterpret_cast<uint32_t *>(f->bulk + p.o_list32)};
+        uint32_t *cursors = reinterpret_cast<uint32_t *>(f->bulk + p.o_cur);
+        uint32_t *ovl_n = cursors + p.cursors - 1;
         uint32_t *list_n = reinterpret_cast<uint32_t *>(f->bulk + p.o_listn);
-        uint32_t *list = reinterpret_cast<uint32_t *>(f->bulk + p.o_list);
         uint32_t *ovl = reinterpret_cast<uint32_t *>(f->bulk + p.o_ovl);
         uint8_t *o = okv ? okv + lo : nullptr;
         uint32_t *kk = kicks ? kicks + lo : nullptr;
-        f->L.split(keys + lo, uint32_t(len), f->place, p.shift + p.fine, p.bins, cur1, a, p.cap1,
-                   o, kk, ovl, ovl_n, s);
-        if (p.fine) {
-            f->L.resplit(a, cur1, p.bins, p.cap1, p.shift, p.fine, cur2, b, p.cap2, ovl, ovl_n, s);
-            f->L.place(f->table, f->p.num_buckets, p.shift, b, cur2, 1, p.parts, p.cap2, list,
+        // round 0: every key in its i1; round 1: those left over in their i2
+        for (uint32_t round = 0; round < 2; ++round) {
+            uint32_t *cur1 = cursors + round * ((p.cursors - 1) / 2);
+            uint32_t *cur2 = cur1 + uint64_t(p.bins) * cfk::kBulkSegs;
+            if (round == 0)
+                f->L.split(keys + lo, uint32_t(len), f->place, p.shift + p.fine, p.bins, cur1, a,
+                           p.cap1, o, kk, ovl, ovl_n, s);
+            else
+                f->L.move(list, list_n, p.list_cap, f->place, p.shift, p.shift + p.fine, p.bins,
+                          cur1, a, p.cap1, ovl, ovl_n, int(p.parts), s);
+            if (p.fine)
+                f->L.resplit(a, cur1, p.bins, p.cap1, p.shift, p.fine, cur2, b, p.cap2, ovl,
+                             ovl_n, s);
+            f->L.place(f->table, f->p.num_buckets, p.shift, p.fine ? b : a, p.fine ? cur2 : cur1,
+                       p.fine ? 1 : cfk::kBulkSegs, p.parts, p.fine ? p.cap2 : p.cap1, list,
                        list_n, p.list_cap, ovl_n, f->ctr, int(p.parts), s);
-        } else {
-            f->L.place(f->table, f->p.num_buckets, p.shift, a, cur1, cfk::kBulkSegs, p.bins,
-                       p.cap1, list, list_n, p.list_cap, ovl_n, f->ctr, int(p.parts), s);
         }
         // several blocks per list while there are few lists
         const uint32_t split = std::max(1u, std::min(8u, 2048u / p.parts));
-        const cfk::Rest rest{list, list_n, ovl, p.list_cap, p.parts, split, kRestExtra,
-                             cur1, uint32_t(p.cursors)};
+        const cfk::Rest rest{list,    list_n, ovl, p.list_cap, p.parts, split, kRestExtra,
+                             p.shift, uint32_t(p.cursors), cursors};
         f->L.ins(f->table, f->place, keys + lo, len, o, kk, f->ctr,
-                 reinterpret_cast<uint32_t *>(f->bulk + p.o_a), 0, log, f->p.max_evict, f->p.seed,
-                 rest, cfl::grouped_probe(f->table_bytes, len), int(p.parts * split + kRestExtra),
-                 s);
+                 reinterpret_cast<uint32_t *>(a.a), 0, log, f->p.max_evict, f->p.seed, rest,
+                 cfl::grouped_probe(f->table_bytes, len), int(p.parts * split + kRestExtra), s);
         const cf_status st = check_launch("insert (partitioned)");
         if (st != CF_OK) {
             f->bulk_bytes = 0;  // the cursors may be left dirty: a new workspace next time

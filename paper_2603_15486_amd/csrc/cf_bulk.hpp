@@ -9,15 +9,18 @@
 // loads the part, tries every key's primary bucket with LDS compare-and-swaps
 // and stores the part back: the direct attempt of Alg. 1 in i1 without a
 // single global atomic and with the table read and written once, in order.
-// Keys whose i1 was full go to the part's list, and insert_kernel takes those
-// lists through i2 and the eviction search.  For the table this is one legal
-// interleaving of the concurrent insert: every attempt in an i1 happens
-// before any attempt in an i2.
+// Keys whose i1 was full are grouped again by the part of their i2 and tried
+// there the same way, and insert_kernel takes those left over through the
+// eviction search.  For the table this is one legal interleaving of the
+// concurrent insert: every attempt in an i1 happens before any attempt in an
+// i2, and those before any eviction.
 //
 //  bulk_split_kernel    keys -> entries grouped by bin (bin = i1 >> shift)
 //  bulk_resplit_kernel  (tables of many parts) entries of one bin -> parts
-//  bulk_insert_kernel    one part in LDS: the attempts in i1
-//  insert_kernel        the lists left over (Rest)
+//  bulk_insert_kernel   one part in LDS: the attempts in its buckets
+//  bulk_move_kernel     entries left over -> grouped by bin of their i2;
+//                       then resplit and insert again
+//  insert_kernel        the searches of the entries left over (Rest)
 //
 // Bins and parts hold a fixed number of entries, sized by the host from the
 // mean of a uniform hash plus eight standard deviations.  Entries beyond it
@@ -37,43 +40,6 @@ constexpr uint32_t kMaxBulkBins = 1024;
 constexpr uint32_t kBulkSegs = 8;                         // one per XCD, see bulk_split_kernel
 constexpr int kPlaceBlock = 1024;
 constexpr int kPlaceItems = 4;
-constexpr uint32_t kBulkIdxBits = 27;                     // keys of one partitioned pass
-constexpr uint64_t kMaxBulkKeys = 1ull << kBulkIdxBits;
-
-// One entry: the tag as written in i1, the key's index in the pass, and the
-// low bits of i1 (its place within the bin).  8 bytes for fingerprints of 8
-// and 16 bits (tag | index | bucket bits, so 64 - 27 - f of the latter), and
-// 12 bytes in two arrays for 32-bit ones.
-struct Ents {
-    uint64_t *a;
-    uint32_t *b;  // f = 32 only: the index
-};
-
-struct Ent {
-    uint32_t tag, idx, bucket;
-};
-
-struct Raw {  // as loaded: a key, or an entry's words
-    uint64_t a;
-    uint32_t b;
-};
-
-template <int F>
-__device__ __forceinline__ uint64_t pack_ent(const Ent &e) {
-    if constexpr (F == 32) return uint64_t(e.tag) | (uint64_t(e.bucket) << 32);
-    else
-        return uint64_t(e.tag) | (uint64_t(e.idx) << F) |
-               (uint64_t(e.bucket) << (F + kBulkIdxBits));
-}
-
-template <int F>
-__device__ __forceinline__ Ent unpack_ent(uint64_t a, uint32_t b) {
-    if constexpr (F == 32) return Ent{uint32_t(a), b, uint32_t(a >> 32)};
-    else
-        return Ent{uint32_t(a) & ((1u << F) - 1u),
-                   uint32_t(a >> F) & ((1u << kBulkIdxBits) - 1u),
-                   uint32_t(a >> (F + kBulkIdxBits))};
-}
 
 // Append one index per active lane to a list behind a global counter.
 __device__ __forceinline__ void append_wave(uint32_t *list, uint32_t *count, uint32_t v) {
@@ -234,6 +200,61 @@ __global__ __launch_bounds__(kSplitBlock) void bulk_resplit_kernel(
         });
 }
 
+// Entries left over in the parts' lists, moved to their other bucket and
+// grouped by its bin.  Block = one part's list.
+template <int F, int HASH, int POL>
+__global__ __launch_bounds__(kSplitBlock) void bulk_move_kernel(
+    Ents list, const uint32_t *__restrict__ list_n, uint32_t list_cap, Place pl,
+    uint32_t part_shift, uint32_t shift, uint32_t nbins, uint32_t *__restrict__ cursor, Ents out,
+    uint32_t cap, uint32_t *__restrict__ ovl, uint32_t *__restrict__ ovl_n) {
+    extern __shared__ __align__(16) uint8_t bulk_lds[];
+    const uint32_t have = list_n[blockIdx.x];
+    const uint32_t x = blockIdx.x % kBulkSegs;
+    const uint32_t b0 = blockIdx.x << part_shift;
+    for (uint32_t lo = 0; lo < have; lo += kSplitTile) {
+        const uint64_t base = uint64_t(blockIdx.x) * list_cap + lo;
+        split_tile<F>(
+            bulk_lds, have - lo < uint32_t(kSplitTile) ? have - lo : uint32_t(kSplitTile), nbins,
+            cursor + x * nbins, out, uint64_t(x) * nbins, cap, ovl, ovl_n,
+            [&](uint32_t j) { return Raw{list.a[base + j], F == 32 ? list.b[base + j] : 0u}; },
+            [&](const Raw &r, uint32_t, uint32_t &bin) {
+                Ent e = unpack_ent<F>(r.a, r.b);
+                const uint32_t b = move_tag<Geom<F, 32>, HASH, POL>(b0 + e.bucket, e.tag, pl);
+                bin = b >> shift;
+                e.bucket = b & ((1u << shift) - 1u);
+                return e;
+            });
+        __syncthreads();
+    }
+}
+
+// Alg. 1's TryInsert in LDS, word by word from the scan's start (the slots are
+// those try_insert takes): a bucket read whole costs a wave 64 x 32 bytes of
+// LDS bandwidth where the first word mostly has room.
+template <class G>
+__device__ __forceinline__ bool lds_insert(typename G::W *part, uint32_t bucket, uint32_t tag) {
+    using W = typename G::W;
+    W *base = part + bucket * G::WPB;
+    const int start = scan_start<G>(tag);
+    for (int k = 0; k < G::WPB; ++k) {
+        W *at = base + ((start + k) & (G::WPB - 1));
+        W w = *at;
+        for (W z = zero_lanes<W, G::F>(w); z; z = zero_lanes<W, G::F>(w)) {
+            const int sh = lowest_bit(z) / G::F * G::F;
+            const W old = cas_word(at, w, W(w | (W(tag) << sh)));
+            if (old == w) return true;
+            w = old;
+        }
+    }
+    return false;
+}
+
+// A part that gets fewer entries than one per so many bytes is not staged:
+// its entries (no other block has any in it) are tried in place.  Staging
+// costs its bytes twice at the streaming rate, an entry in place a line read
+// and a CAS, 70 ps.
+constexpr uint32_t kStageBytes = 160;
+
 // One part (2^shift buckets from bucket part << shift on, the last part cut
 // at m) in LDS: load, try every entry's bucket, store.  An entry whose bucket
 // is full goes to the part's list; the overflow list's length goes behind the
@@ -243,7 +264,7 @@ template <class G>
 __global__ __launch_bounds__(kPlaceBlock) void bulk_insert_kernel(
     typename G::W *__restrict__ table, uint64_t m, uint32_t shift, Ents in,
     const uint32_t *__restrict__ in_n, uint32_t runs, uint32_t stride, uint32_t cap,
-    uint32_t *__restrict__ list, uint32_t *__restrict__ list_n, uint32_t list_cap,
+    Ents list, uint32_t *__restrict__ list_n, uint32_t list_cap,
     const uint32_t *__restrict__ ovl_n, Counters *ctr) {
     using W = typename G::W;
     extern __shared__ __align__(16) uint8_t bulk_lds[];
@@ -253,39 +274,61 @@ __global__ __launch_bounds__(kPlaceBlock) void bulk_insert_kernel(
     const uint32_t nb = uint32_t(m - b0 < (1ull << shift) ? m - b0 : (1ull << shift));
     const uint32_t words = nb * G::WPB;
     W *home = table + b0 * G::WPB;
+    // the runs end to end: run r holds the part's entries [s_run[r], s_run[r + 1])
+    __shared__ uint32_t s_run[kBulkSegs + 1];
+    if (threadIdx.x == 0) {
+        uint32_t acc = 0;
+        for (uint32_t r = 0; r < runs; ++r) {
+            s_run[r] = acc;
+            const uint32_t c = in_n[uint64_t(r) * stride + blockIdx.x];
+            acc += c < cap ? c : cap;
+        }
+        s_run[runs] = acc;
+        s_n = 0;
+    }
+    __syncthreads();
+    const uint32_t total = s_run[runs];
     // 16-byte moves (parts start at multiples of 16 bytes: 2^shift buckets of
     // at least 4 bytes, shift >= 2), then what is left of a cut last part
     constexpr uint32_t WPV = 16 / sizeof(W);
     const uint32_t vecs = words / WPV;
-    const ulonglong2 *gv = reinterpret_cast<const ulonglong2 *>(home);
+    ulonglong2 *hv = reinterpret_cast<ulonglong2 *>(home);
     ulonglong2 *lv = reinterpret_cast<ulonglong2 *>(part);
-    for (uint32_t j = threadIdx.x; j < vecs; j += kPlaceBlock) lv[j] = gv[j];
-    for (uint32_t j = vecs * WPV + threadIdx.x; j < words; j += kPlaceBlock) part[j] = home[j];
-    if (threadIdx.x == 0) s_n = 0;
+    const bool staged = uint64_t(total) * kStageBytes >= uint64_t(words) * sizeof(W);
+    if (staged) {
+        for (uint32_t j = threadIdx.x; j < vecs; j += kPlaceBlock) lv[j] = hv[j];
+        for (uint32_t j = vecs * WPV + threadIdx.x; j < words; j += kPlaceBlock)
+            part[j] = home[j];
+    }
     __syncthreads();
     unsigned long long placed = 0;
     const int lane = threadIdx.x & 63;
-    uint32_t *mylist = list + uint64_t(blockIdx.x) * list_cap;
-    for (uint32_t r = 0; r < runs; ++r) {
-        const uint64_t run = uint64_t(r) * stride + blockIdx.x;
-        const uint32_t have = in_n[run] < cap ? in_n[run] : cap;
-        const uint64_t base = run * cap;
+    const uint64_t mine = uint64_t(blockIdx.x) * list_cap;
+    auto place = [&](auto in_lds) {
         // kPlaceItems entries of a thread are loaded before the first is used
-        for (uint32_t i0 = threadIdx.x; i0 < have; i0 += kPlaceItems * kPlaceBlock) {
+        for (uint32_t i0 = threadIdx.x; i0 < total; i0 += kPlaceItems * kPlaceBlock) {
             Raw raw[kPlaceItems];
 #pragma unroll
             for (int k = 0; k < kPlaceItems; ++k) {
-                const uint32_t i = i0 + uint32_t(k) * kPlaceBlock;
-                const uint64_t at = base + (i < have ? i : i0);
+                const uint32_t j = i0 + uint32_t(k) * kPlaceBlock;
+                const uint32_t i = j < total ? j : i0;
+                uint32_t r = 0;
+                while (i >= s_run[r + 1]) ++r;
+                const uint64_t at = (uint64_t(r) * stride + blockIdx.x) * cap + (i - s_run[r]);
                 raw[k] = Raw{__builtin_nontemporal_load(in.a + at), G::F == 32 ? in.b[at] : 0u};
             }
 #pragma unroll
             for (int k = 0; k < kPlaceItems; ++k) {
-                if (i0 + uint32_t(k) * kPlaceBlock >= have) break;
+                if (i0 + uint32_t(k) * kPlaceBlock >= total) break;
                 const Ent e = unpack_ent<G::F>(raw[k].a, raw[k].b);
-                Bucket<G> bk;
-                load_bucket<G>(part, e.bucket, bk);
-                const bool done = try_insert<G>(part, e.bucket, e.tag, bk) >= 0;
+                bool done;
+                if constexpr (decltype(in_lds)::value) {
+                    done = lds_insert<G>(part, e.bucket, e.tag);
+                } else {
+                    Bucket<G> bk;
+                    load_bucket<G>(home, e.bucket, bk);
+                    done = try_insert<G>(home, e.bucket, e.tag, bk) >= 0;
+                }
                 placed += done;
                 const uint64_t need = __ballot(!done);
                 if (need) {
@@ -293,16 +336,24 @@ __global__ __launch_bounds__(kPlaceBlock) void bulk_insert_kernel(
                     uint32_t at = 0;
                     if (lane == leader) at = atomicAdd(&s_n, uint32_t(__popcll(need)));
                     at = __shfl(at, leader, 64);
-                    if (!done)
-                        mylist[at + uint32_t(__popcll(need & ((1ull << lane) - 1ull)))] = e.idx;
+                    if (!done) {
+                        const uint64_t to =
+                            mine + at + uint32_t(__popcll(need & ((1ull << lane) - 1ull)));
+                        list.a[to] = raw[k].a;
+                        if constexpr (G::F == 32) list.b[to] = raw[k].b;
+                    }
                 }
             }
         }
-    }
+    };
+    if (staged) place(std::true_type{});
+    else place(std::false_type{});
     __syncthreads();
-    ulonglong2 *hv = reinterpret_cast<ulonglong2 *>(home);
-    for (uint32_t j = threadIdx.x; j < vecs; j += kPlaceBlock) hv[j] = lv[j];
-    for (uint32_t j = vecs * WPV + threadIdx.x; j < words; j += kPlaceBlock) home[j] = part[j];
+    if (staged) {
+        for (uint32_t j = threadIdx.x; j < vecs; j += kPlaceBlock) hv[j] = lv[j];
+        for (uint32_t j = vecs * WPV + threadIdx.x; j < words; j += kPlaceBlock)
+            home[j] = part[j];
+    }
     if (threadIdx.x == 0) {
         list_n[blockIdx.x] = s_n;
         if (blockIdx.x == 0) list_n[gridDim.x] = *ovl_n;

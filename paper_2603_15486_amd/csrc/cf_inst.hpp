@@ -60,8 +60,8 @@ struct InstI {
     }
 };
 
-// The partitioned insert: the splits know nothing of the bucket size, the
-// placement of entries in a part nothing of hash and placement policy.
+// The partitioned insert: the splits and the move know nothing of the bucket
+// size, the placement of entries in a part nothing of hash and policy.
 template <int F, int HASH, int POL>
 void split(const uint64_t *k, uint32_t n, const cfk::Place &pl, uint32_t shift, uint32_t nbins,
            uint32_t *cur, cfk::Ents out, uint32_t cap, uint8_t *o, uint32_t *kk, uint32_t *ovl,
@@ -79,9 +79,17 @@ void resplit(cfk::Ents in, const uint32_t *in_n, uint32_t nbins, uint32_t cap_in
         <<<nbins * cfk::kBulkSegs * tiles, cfk::kSplitBlock, cfk::split_lds(F, 1u << fine), s>>>(
             in, in_n, nbins, cap_in, tiles, shift, fine, cur, out, cap, ovl, ovl_n);
 }
+template <int F, int HASH, int POL>
+void move(cfk::Ents list, const uint32_t *list_n, uint32_t list_cap, const cfk::Place &pl,
+          uint32_t part_shift, uint32_t shift, uint32_t nbins, uint32_t *cur, cfk::Ents out,
+          uint32_t cap, uint32_t *ovl, uint32_t *ovl_n, int parts, hipStream_t s) {
+    cfk::bulk_move_kernel<F, HASH, POL>
+        <<<parts, cfk::kSplitBlock, cfk::split_lds(F, nbins), s>>>(
+            list, list_n, list_cap, pl, part_shift, shift, nbins, cur, out, cap, ovl, ovl_n);
+}
 template <int F, int B>
 void place(void *t, uint64_t m, uint32_t shift, cfk::Ents in, const uint32_t *in_n, uint32_t runs,
-           uint32_t stride, uint32_t cap, uint32_t *list, uint32_t *list_n, uint32_t list_cap,
+           uint32_t stride, uint32_t cap, cfk::Ents list, uint32_t *list_n, uint32_t list_cap,
            const uint32_t *ovl_n, Counters *c, int parts, hipStream_t s) {
     using G = cfk::Geom<F, B>;
     cfk::bulk_insert_kernel<G>
@@ -100,6 +108,7 @@ template <int F, int B, int POL>
 void fill_ins(int hash, int evict, Launchers &L) {
     L.split = hash == 0 ? &split<F, 0, POL> : &split<F, 1, POL>;
     L.resplit = &resplit<F>;
+    L.move = hash == 0 ? &move<F, 0, POL> : &move<F, 1, POL>;
     L.place = &place<F, B>;
     L.ins = hash == 0 ? (evict == 0 ? &InstI<F, B, 0, 0, POL>::ins : &InstI<F, B, 0, 1, POL>::ins)
                       : (evict == 0 ? &InstI<F, B, 1, 0, POL>::ins : &InstI<F, B, 1, 1, POL>::ins);

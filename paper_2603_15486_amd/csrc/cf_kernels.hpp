@@ -33,14 +33,55 @@ struct Counters {
     unsigned long long total;  // sum of the stripes, written by sum_counts_kernel
 };
 
-// What a partitioned insert left over (see insert_kernel); list = NULL: none.
+// ------------------------------------------ entries of a partitioned insert
+// (cf_bulk.hpp)
+constexpr uint32_t kBulkIdxBits = 27;  // keys of one pass
+constexpr uint64_t kMaxBulkKeys = 1ull << kBulkIdxBits;
+
+// One entry: the tag as written in its bucket, the key's index in the pass, and
+// the low bits of the bucket (its place within the bin).  8 bytes for fingerprints of 8
+// and 16 bits (tag | index | bucket bits, so 64 - 27 - f of the latter), and
+// 12 bytes in two arrays for 32-bit ones.
+struct Ents {
+    uint64_t *a;
+    uint32_t *b;  // f = 32 only: the index
+};
+
+struct Ent {
+    uint32_t tag, idx, bucket;
+};
+
+struct Raw {  // as loaded: a key, or an entry's words
+    uint64_t a;
+    uint32_t b;
+};
+
+template <int F>
+__device__ __forceinline__ uint64_t pack_ent(const Ent &e) {
+    if constexpr (F == 32) return uint64_t(e.tag) | (uint64_t(e.bucket) << 32);
+    else
+        return uint64_t(e.tag) | (uint64_t(e.idx) << F) |
+               (uint64_t(e.bucket) << (F + kBulkIdxBits));
+}
+
+template <int F>
+__device__ __forceinline__ Ent unpack_ent(uint64_t a, uint32_t b) {
+    if constexpr (F == 32) return Ent{uint32_t(a), b, uint32_t(a >> 32)};
+    else
+        return Ent{uint32_t(a) & ((1u << F) - 1u),
+                   uint32_t(a >> F) & ((1u << kBulkIdxBits) - 1u),
+                   uint32_t(a >> (F + kBulkIdxBits))};
+}
+
+// What a partitioned insert left over (see insert_kernel); list.a = NULL: none.
 struct Rest {
-    const uint32_t *list;    // part p's keys at list[p * cap ..]
+    Ents list;               // part p's entries at p * cap
     const uint32_t *list_n;  // how many; behind them the overflow list's length
-    const uint32_t *ovl;     // the overflow list
+    const uint32_t *ovl;     // the overflow list: keys' indices
     uint32_t cap, parts, split, extra;
-    uint32_t *cursors;       // the pass's cursors, to be cleared for the next one
+    uint32_t shift;          // parts of 2^shift buckets
     uint32_t ncursors;
+    uint32_t *cursors;       // the pass's cursors, to be cleared for the next one
 };
 
 struct LostLog {
@@ -328,12 +369,14 @@ __device__ __forceinline__ bool evict_dfs(typename G::W *table, const Place &pl,
 // wave64 lanes free of eviction-chain divergence, and blocks in different
 // passes overlap the read-heavy direct work with the atomic-heavy evictions.
 //
-// With rest.list set the launch takes the keys a partitioned insert left over
-// (cf_bulk.hpp) instead of keys [0, n): block b works on its share of one
-// part's list, whose keys are known to have a full i1, and the last
-// rest.extra blocks on shares of the overflow list.  The keys' flags and kick
-// counts already hold 1 and 0 then, so only what differs is written (single
-// bytes at random places cost a memory request each).
+// With rest.list set the launch takes what a partitioned insert left over
+// (cf_bulk.hpp) instead of keys [0, n): block b runs the searches of its share
+// of one part's list, entries in a full i2 whose i1 is full too, and the last
+// rest.extra blocks take shares of the overflow list from the start.  The
+// entries' draws come from index, bucket and tag (their keys lie scattered
+// in memory, a request each).  The keys' flags and kick counts already hold
+// 1 and 0 then, so only what differs is written (single bytes at random
+// places cost a request each as well).
 template <class G, int HASH, int EVICT, int POL, int PW = 1>
 __global__ __launch_bounds__(kBlock) void insert_kernel(
     typename G::W *__restrict__ table, Place pl, const uint64_t *__restrict__ keys,
@@ -347,40 +390,46 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
     unsigned long long placed = 0;
     uint64_t stride = uint64_t(gridDim.x) * kBlock;
     uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x;
-    const uint32_t *list = rest.list;
-    bool i1_full = false;
-    if (list) {
-        const uint32_t lists = rest.parts * rest.split;
-        i1_full = blockIdx.x < lists;
-        const uint32_t part = i1_full ? blockIdx.x / rest.split : 0u;
-        const uint64_t share = i1_full ? blockIdx.x % rest.split : blockIdx.x - lists;
-        const uint64_t of = i1_full ? rest.split : rest.extra;
-        const uint64_t len = rest.list_n[i1_full ? part : rest.parts];
-        const uint64_t lo = len * share / of;
-        list = (i1_full ? list + uint64_t(part) * rest.cap : rest.ovl) + lo;
-        myq = queue + (i1_full ? uint64_t(part) * rest.cap : uint64_t(rest.parts) * rest.cap) + lo;
-        seg = n = len * (share + 1) / of - lo;
+    const bool left = rest.list.a != nullptr;
+    const uint32_t *ovl = nullptr;  // a share of the overflow list
+    uint32_t part = 0;
+    uint64_t ent0 = 0, ents = 0;    // a share of a part's list
+    if (left) {
         for (; i < rest.ncursors; i += stride) rest.cursors[i] = 0;
+        const uint32_t lists = rest.parts * rest.split;
+        const bool searches = blockIdx.x < lists;
+        part = searches ? blockIdx.x / rest.split : rest.parts;
+        const uint64_t share = searches ? blockIdx.x % rest.split : blockIdx.x - lists;
+        const uint64_t of = searches ? rest.split : rest.extra;
+        const uint64_t len = rest.list_n[part];
+        const uint64_t lo = len * share / of;
+        const uint64_t have = len * (share + 1) / of - lo;
         i = threadIdx.x;
         stride = kBlock;
+        if (searches) {
+            ent0 = uint64_t(part) * rest.cap + lo;
+            ents = have;
+            n = 0;
+        } else {
+            ovl = rest.ovl + lo;
+            myq = queue + lo;
+            seg = n = have;
+        }
     }
     const int lane = threadIdx.x & 63;
     for (; i < n; i += stride) {
-        const uint64_t at = list ? list[i] : i;
+        const uint64_t at = ovl ? ovl[i] : i;
         const uint64_t key = __builtin_nontemporal_load(keys + at);
         const Derived d = derive<G, HASH, POL>(key, pl);
         Bucket<G> bk;
-        bool done = false;
-        if (!i1_full) {
-            load_bucket<G>(table, d.i1, bk);
-            done = try_insert<G>(table, d.i1, d.t1, bk) >= 0;
-        }
+        load_bucket<G>(table, d.i1, bk);
+        bool done = try_insert<G>(table, d.i1, d.t1, bk) >= 0;
         if (!done) {
             load_bucket<G>(table, d.i2, bk);
             done = try_insert<G>(table, d.i2, d.t2, bk) >= 0;
         }
         placed += done;
-        if (!list) {
+        if (!left) {
             if (ok) ok[at] = uint8_t(done);
             if (kicks) kicks[at] = 0;
         }
@@ -395,7 +444,7 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
         }
     }
     __syncthreads();
-    const uint32_t qn = s_qn < seg ? s_qn : uint32_t(seg);
+    const uint32_t qn = ents ? uint32_t(ents) : s_qn < seg ? s_qn : uint32_t(seg);
     // The searches: a wave steps its lanes' searches level by level, and lanes
     // whose search ended take the next queued keys together once a quarter of
     // the wave is free (taking a key is two dependent loads, which the others
@@ -414,9 +463,22 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
             more = base + uint32_t(__popcll(idle)) < qn;
             const uint32_t q = base + uint32_t(__popcll(idle & ((1ull << lane) - 1ull)));
             if (!busy && q < qn) {
-                idx = myq[q];
-                const uint64_t key = keys[idx];
-                search_start(st, derive<G, HASH, POL>(key, pl), key ^ seed);
+                Derived d;
+                uint64_t draws;
+                if (ents) {
+                    const Ent e = unpack_ent<G::F>(rest.list.a[ent0 + q],
+                                                   G::F == 32 ? rest.list.b[ent0 + q] : 0u);
+                    idx = e.idx;
+                    d.i2 = (part << rest.shift) + e.bucket;
+                    d.t1 = d.t2 = e.tag;
+                    d.i1 = move_tag<G, HASH, POL>(d.i2, d.t1, pl);
+                    draws = (uint64_t(e.tag) << 32) ^ (uint64_t(d.i2) << 20) ^ idx;
+                } else {
+                    idx = myq[q];
+                    draws = keys[idx];
+                    d = derive<G, HASH, POL>(draws, pl);
+                }
+                search_start(st, d, draws ^ seed);
                 busy = true;
             }
         }
@@ -438,8 +500,8 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
                 log.tag[slot] = st.tag;
             }
         }
-        if (ok && !(list && done)) ok[idx] = uint8_t(done);
-        if (kicks && !(list && st.kicks == 0)) kicks[idx] = st.kicks;
+        if (ok && !(left && done)) ok[idx] = uint8_t(done);
+        if (kicks && !(left && st.kicks == 0)) kicks[idx] = st.kicks;
     }
     block_add(ctr, placed);
 }

@@ -30,8 +30,12 @@ struct Launchers {
     void (*resplit)(cfk::Ents in, const uint32_t *in_n, uint32_t nbins, uint32_t cap_in,
                     uint32_t shift, uint32_t fine, uint32_t *cursor, cfk::Ents out, uint32_t cap,
                     uint32_t *ovl, uint32_t *ovl_n, hipStream_t s);
+    void (*move)(cfk::Ents list, const uint32_t *list_n, uint32_t list_cap, const cfk::Place &pl,
+                 uint32_t part_shift, uint32_t shift, uint32_t nbins, uint32_t *cursor,
+                 cfk::Ents out, uint32_t cap, uint32_t *ovl, uint32_t *ovl_n, int parts,
+                 hipStream_t s);
     void (*place)(void *table, uint64_t m, uint32_t shift, cfk::Ents in, const uint32_t *in_n,
-                  uint32_t runs, uint32_t stride, uint32_t cap, uint32_t *list, uint32_t *list_n,
+                  uint32_t runs, uint32_t stride, uint32_t cap, cfk::Ents list, uint32_t *list_n,
                   uint32_t list_cap, const uint32_t *ovl_n, cfk::Counters *ctr, int parts,
                   hipStream_t s);
     void (*recount)(const void *table, uint64_t nwords, cfk::Counters *ctr, int grid,
