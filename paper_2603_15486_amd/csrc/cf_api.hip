@@ -207,15 +207,33 @@ constexpr uint64_t kPartBytes = 64 << 10;
 constexpr uint64_t kMinPartBytes = 1 << 10;
 constexpr uint32_t kWantParts = 256;
 constexpr uint32_t kOneLevelBins = 256;
-constexpr uint64_t kMinBulkKeys = 1 << 16;
 constexpr uint32_t kRestExtra = 64;  // blocks on the overflow list
 
 uint64_t slots_of(const cf_filter *f) { return f->p.num_buckets * f->p.slots_per_bucket; }
 
+// Whether a batch of n goes partitioned.  It then costs a fixed chain of
+// launches (40 us) and the table read and written twice, which must be less
+// than a CAS per key.  Measured, direct -> partitioned:
+//  - from empty, 2^19 keys 46-63 -> 41-47 us, 2^18 keys 39-45 -> 35-46: no
+//    gain below 2^19 keys;
+//  - an eighth of the slots at load 0 / 0.5 / 0.8, 32 MiB of 32-bit
+//    fingerprints (2^20 keys) 53 / 73 / 152 -> 56 / 71 / 127 us, 512 MiB of
+//    16-bit ones (2^25 keys) 1363 / 1367 / 1751 -> 611 / 759 / 1357;
+//  - a sixteenth on 512 MiB 687 / 694 / 958 -> 450 / 549 / 983, on 4 GiB
+//    (2^27 keys), where direct requests cost more, 6.8 / 6.9 / 9.9 -> 3.6 /
+//    4.4 / 8.2 ms; a thirty-second on 512 MiB 357 / 361 / 542 -> 374 / 457 /
+//    630.
 bool bulk_wanted(const cf_filter *f, uint64_t n) {
-    return f->may_partition && n >= kMinBulkKeys &&
-           std::min(n, cfk::kMaxBulkKeys) >= slots_of(f) / 8;
+    if (!f->may_partition || n < (1ull << 19)) return false;
+    const uint64_t share = n < (1ull << 20)                 ? 4
+                           : n < (1ull << 22)               ? 8
+                           : f->table_bytes < (2ull << 30) ? 12
+                                                            : 16;
+    return std::min(n, cfk::kMaxBulkKeys) >= slots_of(f) / share;
 }
+
+// No batch above this many keys goes direct if a larger one goes partitioned.
+uint64_t direct_most(const cf_filter *f) { return std::max(slots_of(f) / 8, uint64_t(1) << 20); }
 
 uint32_t bulk_cap(double mean) {
     return (uint32_t(mean + 8 * std::sqrt(mean) + 16) + 15u) & ~15u;
@@ -482,7 +500,7 @@ cf_status cf_reserve(cf_filter *f, uint64_t max_batch) {
     DeviceGuard g(f->device);
     // batches that go partitioned need no queue; those below the rule do
     if (bulk_wanted(f, max_batch) && bulk_reserve(f, max_batch, nullptr))
-        max_batch = std::min(max_batch, std::max(slots_of(f) / 8, kMinBulkKeys));
+        max_batch = std::min(max_batch, direct_most(f));
     return grow_queue(f, max_batch, nullptr);
 }
 

@@ -1,5 +1,5 @@
-"""The partitioned insert (batches of at least an eighth of the table's
-slots): one and two levels of grouping, a cut last part, bins that overflow,
+"""The partitioned insert (batches of 2^19 keys and more that are large
+against the table): one and two levels of grouping, a cut last part, bins that overflow,
 tables that are already partly full, and capture.  Whatever the path, every
 key is stored or logged: flags, counts, kick bound and the stored
 (bucket pair, fingerprint) content must be those of the inserted keys."""
@@ -47,11 +47,12 @@ def test_direct_insert_of_the_same_batch(cf, b, f, pl):
     r.close()
 
 
-# tables of one level of parts (the first two) and of two; the offset ones end
-# in a cut part, the 4-byte buckets of an odd count in one that is no multiple
-# of 16 bytes
+# tables of one level of parts (the first three) and of two; the offset ones
+# end in a cut part, the 4-byte buckets of an odd count in one that is no
+# multiple of 16 bytes
 @pytest.mark.parametrize("m,b,f,pl,hk", [
-    (4099, 16, 16, 1, 1), (1 << 15, 32, 32, 0, 0), ((1 << 22) + 4097, 4, 8, 1, 0),
+    ((1 << 17) + 3, 16, 16, 1, 1), (1 << 16, 32, 32, 0, 0), (1 << 18, 8, 8, 0, 0),
+    ((1 << 22) + 4097, 4, 8, 1, 0),
     (1 << 23, 4, 8, 0, 1), (3 * (1 << 18) + 7, 16, 16, 1, 0), (1 << 20, 8, 32, 0, 1),
     ((1 << 18) + 3, 32, 32, 1, 0), (1 << 21, 4, 16, 0, 0)])
 def test_partitioned_fill_on_a_half_full_table(cf, m, b, f, pl, hk):
@@ -59,7 +60,7 @@ def test_partitioned_fill_on_a_half_full_table(cf, m, b, f, pl, hk):
     g = cf.CuckooFilter(m, b, f, hash=hk, seed=5, placement=pl)
     lf = 0.85 if b == 4 else 0.92
     first, n = slots // 2 + 3, int(lf * slots) - slots // 2
-    assert n >= slots // 8 and n >= 1 << 14
+    assert n >= slots // 4 and n >= 1 << 19
     keys = K.keys(5, 0, first + n)
     g.insert(dev_u64(keys[:first]))
     ok, kicks = dev_zeros_u8(n), dev_zeros_u32(n)
@@ -81,11 +82,11 @@ def test_overflowing_bin(cf):
     nothing is lost."""
     m, b, f = 1 << 16, 16, 16
     r = OracleFilter(m, b, f, seed=6)
-    pool = K.keys(6, 0, 1 << 20)
+    pool = K.keys(6, 0, 3 << 20)
     i1 = np.asarray(r.derive_batch(pool)[1])
-    crowd = pool[i1 < 256][:3500]
-    keys = np.concatenate([crowd, K.keys(6, 1 << 30, 140_000)])
-    assert crowd.size == 3500
+    crowd = pool[i1 < 256][:9000]  # 2048 expected, and twice the part's slots
+    keys = np.concatenate([crowd, K.keys(6, 1 << 30, 1 << 19)])
+    assert crowd.size == 9000
     g = cf.CuckooFilter(m, b, f, seed=6)
     ok, kicks = dev_zeros_u8(keys.size), dev_zeros_u32(keys.size)
     g.insert(dev_u64(keys), ok, kicks)
@@ -100,9 +101,9 @@ def test_overflowing_bin(cf):
 def test_copies_of_few_keys_fail_and_are_logged(cf, b, f):
     """Copies beyond a pair's 2b slots cannot be stored: each is reported,
     counted and logged."""
-    m = (1 << 18) // b
+    m = (1 << 20) // b
     base = K.keys(7, 0, 64)
-    keys = np.concatenate([np.repeat(base, 4 * b), K.keys(7, 1000, 70_000)])
+    keys = np.concatenate([np.repeat(base, 4 * b), K.keys(7, 1000, 1 << 19)])
     g = cf.CuckooFilter(m, b, f, max_evict=8, seed=7)
     ok = dev_zeros_u8(keys.size)
     g.insert(dev_u64(keys), ok)
@@ -119,7 +120,7 @@ def test_copies_of_few_keys_fail_and_are_logged(cf, b, f):
 def test_captured_and_replayed(cf):
     """Reset and partitioned insert in one graph, replayed between eager
     work: each replay leaves the same content."""
-    m, b, f = 1 << 14, 8, 16
+    m, b, f = 1 << 17, 8, 16
     n = int(0.9 * m * b)
     g = cf.CuckooFilter(m, b, f, seed=8)
     keys = dev_u64(K.keys(8, 0, n))
