@@ -445,53 +445,27 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
     }
     __syncthreads();
     const uint32_t qn = ents ? uint32_t(ents) : s_qn < seg ? s_qn : uint32_t(seg);
-    // The searches: a wave steps its lanes' searches level by level, and lanes
-    // whose search ended take the next queued keys together once a quarter of
-    // the wave is free (taking a key is two dependent loads, which the others
-    // wait for).  Searches differ in length by an order of magnitude; run to
-    // the end by 64 lanes side by side, most lanes wait for the longest.
     Search<G> st;
     uint32_t idx = 0;
-    bool busy = false, more = qn != 0;
-    while (true) {
-        const uint64_t idle = __ballot(!busy);
-        if (more && __popcll(idle) >= kRefill) {
-            const int leader = __builtin_ctzll(idle);
-            uint32_t base = 0;
-            if (lane == leader) base = atomicAdd(&s_take, uint32_t(__popcll(idle)));
-            base = __shfl(base, leader, 64);
-            more = base + uint32_t(__popcll(idle)) < qn;
-            const uint32_t q = base + uint32_t(__popcll(idle & ((1ull << lane) - 1ull)));
-            if (!busy && q < qn) {
-                Derived d;
-                uint64_t draws;
-                if (ents) {
-                    const Ent e = unpack_ent<G::F>(rest.list.a[ent0 + q],
-                                                   G::F == 32 ? rest.list.b[ent0 + q] : 0u);
-                    idx = e.idx;
-                    d.i2 = (part << rest.shift) + e.bucket;
-                    d.t1 = d.t2 = e.tag;
-                    d.i1 = move_tag<G, HASH, POL>(d.i2, d.t1, pl);
-                    draws = (uint64_t(e.tag) << 32) ^ (uint64_t(d.i2) << 20) ^ idx;
-                } else {
-                    idx = myq[q];
-                    draws = keys[idx];
-                    d = derive<G, HASH, POL>(draws, pl);
-                }
-                search_start(st, d, draws ^ seed);
-                busy = true;
-            }
+    auto begin = [&](uint32_t q) {
+        Derived d;
+        uint64_t draws;
+        if (ents) {
+            const Ent e = unpack_ent<G::F>(rest.list.a[ent0 + q],
+                                           G::F == 32 ? rest.list.b[ent0 + q] : 0u);
+            idx = e.idx;
+            d.i2 = (part << rest.shift) + e.bucket;
+            d.t1 = d.t2 = e.tag;
+            d.i1 = move_tag<G, HASH, POL>(d.i2, d.t1, pl);
+            draws = (uint64_t(e.tag) << 32) ^ (uint64_t(d.i2) << 20) ^ idx;
+        } else {
+            idx = myq[q];
+            draws = keys[idx];
+            d = derive<G, HASH, POL>(draws, pl);
         }
-        if (__ballot(busy) == 0) break;  // nothing taken: the queue is empty
-        if (!busy) continue;
-        bool done = false, ended = st.n >= max_evict;
-        if (!ended) {
-            if constexpr (EVICT == 1) done = dfs_level<G, HASH, POL, true>(table, pl, st);
-            else done = bfs_level<G, HASH, POL, PW, true>(table, pl, st);
-            ended = done || st.n >= max_evict;
-        }
-        if (!ended) continue;
-        busy = false;
+        search_start(st, d, draws ^ seed);
+    };
+    auto end = [&](bool done) {
         placed += done;
         if (!done) {
             const unsigned long long slot = atomicAdd(&ctr->failures, 1ull);
@@ -502,6 +476,55 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
         }
         if (ok && !(left && done)) ok[idx] = uint8_t(done);
         if (kicks && !(left && st.kicks == 0)) kicks[idx] = st.kicks;
+    };
+    if constexpr (EVICT == 1) {
+        // Every step of the random walk is the same few accesses in every
+        // lane, so one lane takes one key after another (the scheme below
+        // measured 2-3% slower).
+        for (uint32_t q = threadIdx.x; q < qn; q += kBlock) {
+            begin(q);
+            end(evict_dfs<G, HASH, POL, false>(table, pl, st, max_evict));
+        }
+    } else {
+        // A wave steps its lanes' searches level by level, and lanes whose
+        // search ended take the next queued keys together once a quarter of
+        // the wave is free (taking a key is two dependent loads, which the
+        // others wait for).  Searches differ in length by an order of
+        // magnitude; run to the end by 64 lanes side by side, most lanes wait
+        // for the longest (64 MiB build at load 0.9: 2195 -> 1728 us).
+        // A wave takes at most its share of a short queue: lanes on different
+        // paths of a level run one path after another, so few lanes in each
+        // of four waves end sooner than many in one (2 MiB build: 144 -> 134
+        // us).
+        constexpr bool KEEP = G::B * G::F <= 256;  // larger buckets would cost waves in flight
+        constexpr uint32_t NW = kBlock / 64;
+        const uint32_t share = (qn + NW - 1) / NW;
+        bool busy = false, more = qn != 0;
+        while (true) {
+            const uint64_t idle = __ballot(!busy);
+            if (more && __popcll(idle) >= kRefill) {
+                const int leader = __builtin_ctzll(idle);
+                const uint32_t free = uint32_t(__popcll(idle));
+                const uint32_t take = free < share ? free : share;
+                uint32_t base = 0;
+                if (lane == leader) base = atomicAdd(&s_take, take);
+                base = __shfl(base, leader, 64);
+                more = base + take < qn;
+                const uint32_t k = uint32_t(__popcll(idle & ((1ull << lane) - 1ull)));
+                const uint32_t q = base + k;
+                if (!busy && k < take && q < qn) {
+                    begin(q);
+                    busy = true;
+                }
+            }
+            if (__ballot(busy) == 0) break;  // nothing taken: the queue is empty
+            if (!busy) continue;
+            bool done = false;
+            if (st.n < max_evict) done = bfs_level<G, HASH, POL, PW, KEEP>(table, pl, st);
+            if (!done && st.n < max_evict) continue;
+            busy = false;
+            end(done);
+        }
     }
     block_add(ctr, placed);
 }
