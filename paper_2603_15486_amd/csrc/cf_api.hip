@@ -351,7 +351,7 @@ cf_status bulk_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *o
         const cfk::Rest rest{list,    list_n, ovl, p.list_cap, p.parts, split, kRestExtra,
                              p.shift, uint32_t(p.cursors), cursors};
         f->L.ins(f->table, f->place, keys + lo, len, o, kk, f->ctr,
-                 reinterpret_cast<uint32_t *>(a.a), 0, log, f->p.max_evict, f->p.seed, rest,
+                 reinterpret_cast<uint32_t *>(a.a), 0, log, f->p.max_evict, f->p.seed, &rest,
                  cfl::grouped_probe(f->table_bytes, len), int(p.parts * split + kRestExtra), s);
         const cf_status st = check_launch("insert (partitioned)");
         if (st != CF_OK) {
@@ -521,7 +521,7 @@ cf_status cf_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *okv
         const uint64_t seg = ((len + per - 1) / per) * kBlock;
         f->L.ins(f->table, f->place, keys + off, len, okv ? okv + off : nullptr,
                  kicks ? kicks + off : nullptr, f->ctr, f->queue, seg, log, f->p.max_evict,
-                 f->p.seed, cfk::Rest{}, cfl::grouped_probe(f->table_bytes, len), grid, s);
+                 f->p.seed, nullptr, cfl::grouped_probe(f->table_bytes, len), grid, s);
         st = check_launch("insert");
         if (st != CF_OK) return st;
     }
@@ -553,7 +553,7 @@ cf_status cf_insert_noalloc(cf_filter *f, const uint64_t *keys, uint64_t n, uint
     const uint64_t seg = ((n + per - 1) / per) * kBlock;
     const cfk::LostLog log{f->lost_bucket, f->lost_tag, f->lost_cap};
     f->L.ins(f->table, f->place, keys, n, okv, kicks, f->ctr, q, seg, log, f->p.max_evict,
-             f->p.seed, cfk::Rest{}, cfl::grouped_probe(f->table_bytes, n), grid,
+             f->p.seed, nullptr, cfl::grouped_probe(f->table_bytes, n), grid,
              static_cast<hipStream_t>(stream));
     return check_launch("insert (fixed queue)");
 }

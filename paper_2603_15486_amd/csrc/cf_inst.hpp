@@ -48,15 +48,24 @@ struct InstI {
     using G = cfk::Geom<F, B>;
     static constexpr int PW = EVICT == 0 ? cfk::probe_width<G>() : 1;
     using W = typename G::W;
-    static void ins(void *t, const cfk::Place &pl, const uint64_t *k, uint64_t n, uint8_t *o,
+    template <class R>
+    static void run(void *t, const cfk::Place &pl, const uint64_t *k, uint64_t n, uint8_t *o,
                     uint32_t *kk, Counters *c, uint32_t *q, uint64_t seg, cfk::LostLog log,
-                    uint32_t me, uint64_t seed, const cfk::Rest &rest, bool grouped, int grid, hipStream_t s) {
+                    uint32_t me, uint64_t seed, const R &rest, bool grouped, int grid,
+                    hipStream_t s) {
         if (PW > 1 && grouped)
-            cfk::insert_kernel<G, HASH, EVICT, POL, PW><<<grid, kBlock, 0, s>>>(
+            cfk::insert_kernel<G, HASH, EVICT, POL, PW, R><<<grid, kBlock, 0, s>>>(
                 static_cast<W *>(t), pl, k, n, o, kk, c, q, seg, log, me, seed, rest);
         else
-            cfk::insert_kernel<G, HASH, EVICT, POL, 1><<<grid, kBlock, 0, s>>>(
+            cfk::insert_kernel<G, HASH, EVICT, POL, 1, R><<<grid, kBlock, 0, s>>>(
                 static_cast<W *>(t), pl, k, n, o, kk, c, q, seg, log, me, seed, rest);
+    }
+    static void ins(void *t, const cfk::Place &pl, const uint64_t *k, uint64_t n, uint8_t *o,
+                    uint32_t *kk, Counters *c, uint32_t *q, uint64_t seg, cfk::LostLog log,
+                    uint32_t me, uint64_t seed, const cfk::Rest *rest, bool grouped, int grid,
+                    hipStream_t s) {
+        if (rest) run(t, pl, k, n, o, kk, c, q, seg, log, me, seed, *rest, grouped, grid, s);
+        else run(t, pl, k, n, o, kk, c, q, seg, log, me, seed, cfk::NoRest{}, grouped, grid, s);
     }
 };
 

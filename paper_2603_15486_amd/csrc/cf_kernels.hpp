@@ -73,7 +73,8 @@ __device__ __forceinline__ Ent unpack_ent(uint64_t a, uint32_t b) {
                    uint32_t(a >> (F + kBulkIdxBits))};
 }
 
-// What a partitioned insert left over (see insert_kernel); list.a = NULL: none.
+// What a partitioned insert left over (see insert_kernel).
+struct NoRest {};
 struct Rest {
     Ents list;               // part p's entries at p * cap
     const uint32_t *list_n;  // how many; behind them the overflow list's length
@@ -369,7 +370,7 @@ __device__ __forceinline__ bool evict_dfs(typename G::W *table, const Place &pl,
 // wave64 lanes free of eviction-chain divergence, and blocks in different
 // passes overlap the read-heavy direct work with the atomic-heavy evictions.
 //
-// With rest.list set the launch takes what a partitioned insert left over
+// With R = Rest the launch takes what a partitioned insert left over
 // (cf_bulk.hpp) instead of keys [0, n): block b runs the searches of its share
 // of one part's list, entries in a full i2 whose i1 is full too, and the last
 // rest.extra blocks take shares of the overflow list from the start.  The
@@ -377,12 +378,13 @@ __device__ __forceinline__ bool evict_dfs(typename G::W *table, const Place &pl,
 // in memory, a request each).  The keys' flags and kick counts already hold
 // 1 and 0 then, so only what differs is written (single bytes at random
 // places cost a request each as well).
-template <class G, int HASH, int EVICT, int POL, int PW = 1>
+template <class G, int HASH, int EVICT, int POL, int PW, class R>
 __global__ __launch_bounds__(kBlock) void insert_kernel(
     typename G::W *__restrict__ table, Place pl, const uint64_t *__restrict__ keys,
     uint64_t n, uint8_t *__restrict__ ok, uint32_t *__restrict__ kicks, Counters *ctr,
     uint32_t *__restrict__ queue, uint64_t seg, LostLog log, uint32_t max_evict,
-    uint64_t seed, Rest rest) {
+    uint64_t seed, R rest) {
+    constexpr bool left = std::is_same<R, Rest>::value;
     __shared__ uint32_t s_qn, s_take;
     if (threadIdx.x == 0) s_qn = s_take = 0;
     __syncthreads();
@@ -390,11 +392,10 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
     unsigned long long placed = 0;
     uint64_t stride = uint64_t(gridDim.x) * kBlock;
     uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x;
-    const bool left = rest.list.a != nullptr;
     const uint32_t *ovl = nullptr;  // a share of the overflow list
     uint32_t part = 0;
     uint64_t ent0 = 0, ents = 0;    // a share of a part's list
-    if (left) {
+    if constexpr (left) {
         for (; i < rest.ncursors; i += stride) rest.cursors[i] = 0;
         const uint32_t lists = rest.parts * rest.split;
         const bool searches = blockIdx.x < lists;
@@ -418,7 +419,7 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
     }
     const int lane = threadIdx.x & 63;
     for (; i < n; i += stride) {
-        const uint64_t at = ovl ? ovl[i] : i;
+        const uint64_t at = left ? ovl[i] : i;
         const uint64_t key = __builtin_nontemporal_load(keys + at);
         const Derived d = derive<G, HASH, POL>(key, pl);
         Bucket<G> bk;
@@ -448,22 +449,23 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(
     Search<G> st;
     uint32_t idx = 0;
     auto begin = [&](uint32_t q) {
-        Derived d;
-        uint64_t draws;
-        if (ents) {
-            const Ent e = unpack_ent<G::F>(rest.list.a[ent0 + q],
-                                           G::F == 32 ? rest.list.b[ent0 + q] : 0u);
-            idx = e.idx;
-            d.i2 = (part << rest.shift) + e.bucket;
-            d.t1 = d.t2 = e.tag;
-            d.i1 = move_tag<G, HASH, POL>(d.i2, d.t1, pl);
-            draws = (uint64_t(e.tag) << 32) ^ (uint64_t(d.i2) << 20) ^ idx;
-        } else {
-            idx = myq[q];
-            draws = keys[idx];
-            d = derive<G, HASH, POL>(draws, pl);
+        if constexpr (left) {
+            if (ents) {
+                const Ent e = unpack_ent<G::F>(rest.list.a[ent0 + q],
+                                               G::F == 32 ? rest.list.b[ent0 + q] : 0u);
+                idx = e.idx;
+                Derived d;
+                d.i2 = (part << rest.shift) + e.bucket;
+                d.t1 = d.t2 = e.tag;
+                d.i1 = move_tag<G, HASH, POL>(d.i2, d.t1, pl);
+                search_start(st, d,
+                             (uint64_t(e.tag) << 32) ^ (uint64_t(d.i2) << 20) ^ idx ^ seed);
+                return;
+            }
         }
-        search_start(st, d, draws ^ seed);
+        idx = myq[q];
+        const uint64_t key = keys[idx];
+        search_start(st, derive<G, HASH, POL>(key, pl), key ^ seed);
     };
     auto end = [&](bool done) {
         placed += done;

@@ -21,7 +21,7 @@ struct Launchers {
                 uint8_t *okv, cfk::Counters *ctr, int grid, hipStream_t s);
     void (*ins)(void *table, const cfk::Place &pl, const uint64_t *keys, uint64_t n,
                 uint8_t *okv, uint32_t *kicks, cfk::Counters *ctr, uint32_t *queue, uint64_t seg,
-                cfk::LostLog log, uint32_t max_evict, uint64_t seed, const cfk::Rest &rest,
+                cfk::LostLog log, uint32_t max_evict, uint64_t seed, const cfk::Rest *rest,
                 bool grouped, int grid, hipStream_t s);
     // the partitioned insert (cf_bulk.hpp)
     void (*split)(const uint64_t *keys, uint32_t n, const cfk::Place &pl, uint32_t shift,

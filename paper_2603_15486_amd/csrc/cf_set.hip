@@ -689,7 +689,7 @@ cf_status cfs::apply_lane(cf_set *s, uint32_t lane, uint32_t fid, uint32_t op,
         const uint64_t seg = cfl::insert_segment(n, grid);
         const cfk::LostLog log{h.lost_bucket, h.lost_tag, h.lost_cap};
         L.ins(h.table, h.place, keys, n, results, nullptr, h.ctr, lane_of(s, lane).queue, seg,
-              log, h.max_evict, h.seed, cfk::Rest{},
+              log, h.max_evict, h.seed, nullptr,
               cfl::grouped_probe(tbytes(s->params[fid]), n), grid, st);
     }
     return check_launch("set apply");
