@@ -117,7 +117,9 @@ cf_status cf_create_in(const cf_params *params, void *d_table, uint64_t nbytes,
 cf_status cf_destroy(cf_filter *flt);
 
 /* Reserve internal scratch for batches of up to max_batch keys so that later
- * inserts of that size do not allocate.  Synchronous. */
+ * inserts of that size do not allocate: the eviction queue, and for a
+ * max_batch that would go partitioned (see cf_insert) its workspace of 20 to
+ * 40 bytes per key of min(max_batch, 2^27).  Synchronous. */
 cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
 
 /* Alg. 1 + Sec. 4.6.1: insert n keys.  d_ok (nullable): uint8[n], 1 if the
@@ -125,10 +127,20 @@ cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
  * displaced by that key's insertion.  The occupancy count grows by the
  * number of successes.  Keys may repeat (each copy is stored).  The first
  * call with a batch larger than any before it allocates scratch and
- * synchronises the stream (see cf_reserve).  On tables of at most 16 MiB the
- * breadth-first search loads a level's candidates' other buckets in groups
- * (as many as 128 bytes hold) instead of one by one; it picks the same
- * candidate either way. */
+ * synchronises the stream (see cf_reserve).  On tables of at most 16 MiB, and
+ * for batches of at most 2^19 keys, the breadth-first search loads a level's
+ * candidates' other buckets in groups (as many as 128 bytes hold) instead of
+ * one by one; it picks the same candidate either way.
+ * Batches of 2^19 keys and more that are large against the table (a quarter
+ * of its slots, from 2^20 keys an eighth, from 2^22 a twelfth or, on tables
+ * of 2 GiB, a sixteenth) go partitioned, in passes of up to 2^27 keys: keys
+ * are grouped by part of the table and placed part by part, all in their
+ * first bucket, then those left over in their second, then the eviction
+ * searches run, whose draws come from a key's index, bucket and fingerprint
+ * instead of the key.  The workspace stays with the filter until
+ * cf_destroy; where it cannot be allocated, and on a stream under capture
+ * that would need to, and under CF_GRID_PER_CU, the batch goes the direct
+ * way. */
 cf_status cf_insert(cf_filter *flt, const uint64_t *d_keys, uint64_t n,
                     uint8_t *d_ok, uint32_t *d_kicks, void *stream);
 

@@ -84,10 +84,10 @@ enum { CF_OP_QUERY = 0, CF_OP_DELETE = 1, CF_OP_INSERT = 2 };
  * unused).  Same results; needs the same as the persistent form (every
  * filter sharing f, hash and placement), else CF_EUNSUPPORTED.  0 = one
  * launch per (phase, class), except that batches (for a graph: max_batch) of
- * up to 2^15 operations, and of up to 2^18 or 2^20 on sets of few classes,
- * run one launch per phase and group of classes that share f, hash and
- * placement on the caller's stream, whatever `streams` says: such batches
- * last as long as issuing their launches does. */
+ * up to 2^15 operations, and of up to 2^18 or 2^20 on sets whose classes
+ * form few groups, run one launch per phase and group of classes that share
+ * hash and placement on the caller's stream, whatever `streams` says: such
+ * batches last as long as issuing their launches does. */
 typedef struct {
     uint32_t chunk;
     uint32_t streams;

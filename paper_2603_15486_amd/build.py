@@ -20,7 +20,7 @@ LIB = os.path.join(PKG, "libcf.so")
 SOURCES = ["cf_api.hip", "cf_inst_f8.hip", "cf_inst_f16.hip", "cf_inst_f32.hip",
            "cf_insi_f8.hip", "cf_insi_f16.hip", "cf_insi_f32.hip",
            "cf_set.hip", "cf_set_inst_f8.hip", "cf_set_inst_f16.hip", "cf_set_inst_f32.hip",
-           "cf_set_insi_f8.hip", "cf_set_insi_f16.hip", "cf_set_insi_f32.hip",
+           "cf_set_any.hip", "cf_set_insi_any.hip", "cf_set_insi_f8.hip", "cf_set_insi_f16.hip", "cf_set_insi_f32.hip",
            "cf_set_persist_insi_f8.hip", "cf_set_persist_insi_f16.hip",
            "cf_set_persist_insi_f32.hip",
            "cf_server.hip", "cf_tune.hip", "cf_keygen.hip"]

@@ -193,6 +193,9 @@ struct cf_set {
     // one launch per phase (cf_set_persist.hpp) and group of classes that
     // share f, hash and placement
     std::vector<cfs::PhaseGroup> groups;
+    // ... and share hash and placement only, for the smallest batches; empty
+    // where that makes no fewer groups
+    std::vector<cfs::PhaseGroup> wide;
     uint32_t fused = 0;
     std::vector<cfs::Scratch> lanes;  // scratch lanes 1.. (lane 0 is sc)
 };
@@ -281,17 +284,26 @@ uint32_t chunk_for(const cf_set *s, uint64_t n) {
     return c % 64 ? s->chunk : c;
 }
 
+// Batches up to this many operations run one launch per phase and (hash,
+// placement) on sets that mix fingerprint widths: fewer launches, with the
+// registers of the widest geometry.
+constexpr uint64_t kWideBatch = 1ull << 20;
+
+const std::vector<PhaseGroup> &groups_for(const cf_set *s, uint64_t n) {
+    return !s->wide.empty() && n <= kWideBatch ? s->wide : s->groups;
+}
+
 // Whether a batch of n runs one launch per phase and group of classes (the
 // phase form) although the shape asks for class kernels: up to 2^20
 // operations a batch of class kernels lasts as long as the host takes to
 // issue its launches and events, 15 us per class.  Measured (24 filters,
 // classes / groups, class kernels -> phases): 20 000 operations, 2/1 64 -> 18
-// us, 4/2 110 -> 32, 8/4 151 -> 59; 2^20 operations 84 -> 76, 118 -> 100,
-// 160 -> 145.  Beyond (2^22: 257 -> 287 us at 4/2) the groups' launches one
-// behind another leave more idle than streams do, and so do many groups
-// (12/12: 2^15 operations even, 200 000 182 -> 216 us).
+// us, 4/1 102 -> 19, 12/4 187 -> 64; 2^20 operations 2/1 84 -> 76, 4/1 123 ->
+// 78, 12/4 195 -> 169.  Beyond (2^22: 257 -> 287 us at 4/2) the groups' launches one
+// behind another leave more idle than streams do, and so do groups of one
+// class (4/4: 2^18 operations 107 -> 85, 2^20 117 -> 145).
 bool small_batch(const cf_set *s, uint64_t n) {
-    const uint64_t ncls = s->classes.size(), ng = s->groups.size();
+    const uint64_t ncls = s->classes.size(), ng = groups_for(s, n).size();
     return n <= (1ull << 15) ||
            (ng <= 6 && n <= (ncls >= 2 * ng ? 1ull << 20 : 1ull << 18));
 }
@@ -402,13 +414,14 @@ int verified_fit(cf_set *s, int k) {
 // the first sorts the batch as well.
 cf_status enqueue_phases(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st) {
     const Scratch &sc = s->sc;
+    const std::vector<PhaseGroup> &groups = groups_for(s, n);
     const uint32_t ncls = uint32_t(s->classes.size());
     const uint32_t chunk = chunk_for(s, n);
     const int grid = int((n + chunk - 1) / chunk);
     cf_status r = CF_OK;
-    for (const PhaseGroup &g : s->groups) {
+    for (const PhaseGroup &g : groups) {
         if (r != CF_OK) return r;
-        if (&g == &s->groups[0])  // it sorts the batch for the others too
+        if (&g == &groups[0])  // it sorts the batch for the others too
             g.launch.front(bt, s->d_filters, s->d_cls, g.classes, s->nfilters, ncls, chunk, sc,
                            grid, st);
         else
@@ -416,13 +429,13 @@ cf_status enqueue_phases(cf_set *s, const Batch &bt, uint64_t n, hipStream_t st)
                            grid * int(g.classes.n), st);
         r = check_launch("set query phase");
     }
-    for (const PhaseGroup &g : s->groups) {
+    for (const PhaseGroup &g : groups) {
         if (r != CF_OK) return r;
         g.launch.del(bt, s->d_filters, g.classes, s->nfilters, ncls, chunk, sc,
                      grid * int(g.classes.n), st);
         r = check_launch("set delete phase");
     }
-    for (const PhaseGroup &g : s->groups) {
+    for (const PhaseGroup &g : groups) {
         if (r != CF_OK) return r;
         g.launch.ins(bt, s->d_filters, g.classes, s->nfilters, ncls, chunk, sc, s->wave_bfs,
                      grid * int(g.classes.n), st);
@@ -784,8 +797,34 @@ cf_status cf_set_create(const cf_params *params, uint32_t nfilters, uint64_t max
         }
         cfs::ClassB &cb = s->groups[g].classes;
         cb.b[cb.n] = uint8_t(p.slots_per_bucket);
+        cb.f[cb.n] = uint8_t(p.fp_bits);
         cb.id[cb.n++] = uint8_t(c);
     }
+    std::vector<uint32_t> hp;  // a group's filter per (hash, placement)
+    for (uint32_t g = 0; g < first.size(); ++g) {
+        const cf_params &p = params[first[g]];
+        uint32_t w = 0;
+        while (w < hp.size() && (params[hp[w]].hash != p.hash ||
+                                 params[hp[w]].placement != p.placement))
+            ++w;
+        if (w == hp.size()) {
+            hp.push_back(first[g]);
+            s->wide.push_back({});
+            if (!cfs::pick_phase_any(p.hash, p.placement, s->wide[w].launch) ||
+                !cfs::pick_phase_insert_any(p.hash, p.placement, s->wide[w].launch)) {
+                delete s;
+                return fail(CF_EUNSUPPORTED, "no kernels for hash=%u", p.hash);
+            }
+        }
+        const cfs::ClassB &from = s->groups[g].classes;
+        cfs::ClassB &to = s->wide[w].classes;
+        for (uint32_t k = 0; k < from.n; ++k, ++to.n) {
+            to.b[to.n] = from.b[k];
+            to.f[to.n] = from.f[k];
+            to.id[to.n] = from.id[k];
+        }
+    }
+    if (s->wide.size() == s->groups.size()) s->wide.clear();
     for (uint32_t g = 0; g < first.size(); ++g) {
         const uint32_t f = params[first[g]].fp_bits, h = params[first[g]].hash,
                        pl = params[first[g]].placement;

@@ -65,10 +65,12 @@ struct PersistCtl {
     CtlStamps stamp;
 };
 
-// The classes a launch covers (all of one f, hash and placement): their
-// numbers in the set and bucket sizes b.
+// The classes a launch covers (all of one hash and placement, and of one f
+// unless the kernel is for any): their numbers in the set, bucket sizes b and
+// fingerprint widths f.
 struct ClassB {
     uint8_t b[kMaxClasses];
+    uint8_t f[kMaxClasses];
     uint8_t id[kMaxClasses];
     uint32_t n;
 };
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
             uint32_t b0, b1;
             bin_range(sc, nb, cid, c, b0, b1);
             if (b0 < b1)
-                with_b<F, BMAX>(cb.b[c], [&](auto g) {
+                with_b<F, BMAX>(cb.f[c], cb.b[c], [&](auto g) {
                     query_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, seg, cid * chunk}, filters, b0, b1);
                 });
         }
@@ -198,7 +200,7 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
             uint32_t b0, b1;
             bin_range(sc, nb, cid, ncls + c, b0, b1);
             if (b0 < b1)
-                with_b<F, BMAX>(cb.b[c], [&](auto g) {
+                with_b<F, BMAX>(cb.f[c], cb.b[c], [&](auto g) {
                     delete_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, seg, cid * chunk}, filters, b0, b1, tally);
                 });
         }
@@ -214,7 +216,7 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
             uint32_t b0, b1;
             bin_range(sc, nb, cid, 2 * ncls + c, b0, b1);
             if (b0 < b1)  // uniform across the block: insert_bin has block barriers
-                with_b<F, BMAX>(cb.b[c], [&](auto g) {
+                with_b<F, BMAX>(cb.f[c], cb.b[c], [&](auto g) {
                     insert_bin<decltype(g), HASH, POL, BT>(ChunkSrc{bt, sc.sorted + at, at}, filters,
                                                            b0, b1, sc.queue + at + b0, &s_qn,
                                                            tally, wave_bfs);
@@ -229,7 +231,8 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
 // launch: grid = chunks x classes, block k working on the bin of the launch's
 // class k mod cb.n in chunk k / cb.n, with that class's b chosen at run time
 // (with_b).  A set whose classes differ in f, hash or placement has one such
-// launch per phase and group of classes that agree.
+// launch per phase and group of classes that agree, or for small batches per
+// group that agrees in hash and placement (F = 0: f chosen per block too).
 // The queries of every class run side by side in one launch, then every
 // delete, then every insert, all on the caller's stream: no side streams,
 // and a captured batch is a straight chain of four kernels (partition and
@@ -259,6 +262,7 @@ __global__ __launch_bounds__(kFrontBlock) void phase_front_kernel(
     uint8_t *s_res = reinterpret_cast<uint8_t *>(s_ent + chunk);
     __shared__ uint32_t hist[kMaxBins + 1], base[kMaxBins + 2];
     __shared__ uint8_t s_b[kMaxClasses];  // b of the launch's classes, 0: not one of them
+    __shared__ uint8_t s_f[kMaxClasses];
     const uint64_t n = batch_n(bt);
     const uint64_t lo = uint64_t(blockIdx.x) * chunk;
     const uint32_t have = lo >= n ? 0u : n - lo < chunk ? uint32_t(n - lo) : chunk;
@@ -266,7 +270,10 @@ __global__ __launch_bounds__(kFrontBlock) void phase_front_kernel(
     for (uint32_t j = t; j <= nb; j += kFrontBlock) hist[j] = 0;
     if (t < kMaxClasses) s_b[t] = 0;
     __syncthreads();
-    if (t < cb.n) s_b[cb.id[t]] = cb.b[t];
+    if (t < cb.n) {
+        s_b[cb.id[t]] = cb.b[t];
+        s_f[cb.id[t]] = cb.f[t];
+    }
     uint64_t key[kFrontItems];
     uint32_t fid[kFrontItems], bin[kFrontItems], rank[kFrontItems];
 #pragma unroll
@@ -321,7 +328,7 @@ __global__ __launch_bounds__(kFrontBlock) void phase_front_kernel(
         while (p >= base[c + 1]) ++c;
         const uint32_t v = s_ent[p];
         bool hit = false;
-        with_b<F, BMAX>(s_b[c], [&](auto g) {
+        with_b<F, BMAX>(s_f[c], s_b[c], [&](auto g) {
             hit = query_one<decltype(g), HASH, POL>(filters[v / kMaxChunk], s_key[p]);
         });
         s_res[v & (kMaxChunk - 1)] = uint8_t(hit);
@@ -347,7 +354,7 @@ __global__ __launch_bounds__(kBlock) void phase_query_kernel(Batch bt,
     bin_range(sc, 3 * ncls, cid, cb.id[c], b0, b1);
     if (b0 >= b1) return;
     const uint32_t *seg = sc.sorted + cid * chunk;
-    with_b<F, BMAX>(cb.b[c], [&](auto g) {
+    with_b<F, BMAX>(cb.f[c], cb.b[c], [&](auto g) {
         query_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, seg, cid * chunk}, filters, b0, b1);
     });
 }
@@ -367,7 +374,7 @@ __global__ __launch_bounds__(kBlock) void phase_delete_kernel(Batch bt,
     Tally<kBlock> tally{lds, nfilters};
     tally.init();
     const uint32_t *seg = sc.sorted + cid * chunk;
-    with_b<F, BMAX>(cb.b[c], [&](auto g) {
+    with_b<F, BMAX>(cb.f[c], cb.b[c], [&](auto g) {
         delete_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, seg, cid * chunk}, filters, b0, b1, tally);
     });
     tally.flush(filters);
@@ -389,7 +396,7 @@ __global__ __launch_bounds__(kBlock) void phase_insert_kernel(Batch bt,
     Tally<kBlock> tally{lds, nfilters};
     tally.init();
     const uint64_t at = cid * chunk;
-    with_b<F, BMAX>(cb.b[c], [&](auto g) {
+    with_b<F, BMAX>(cb.f[c], cb.b[c], [&](auto g) {
         insert_bin<decltype(g), HASH, POL, kBlock>(ChunkSrc{bt, sc.sorted + at, at}, filters, b0, b1,
                                                    sc.queue + at + b0, &s_qn, tally, wave_bfs);
     });
@@ -460,13 +467,15 @@ bool pick_phase_fb(uint32_t hash, uint32_t placement, PhaseLaunch &L) {
         using I = decltype(inst);
         if constexpr (INSERT) {
             L.ins = &I::ins;
-            L.req_ins = &I::req_ins;
+            if constexpr (F != 0) L.req_ins = &I::req_ins;
         } else {
             L.front = &I::front;
             L.query = &I::query;
             L.del = &I::del;
-            L.req_query = &I::req_query;
-            L.req_del = &I::req_del;
+            if constexpr (F != 0) {
+                L.req_query = &I::req_query;
+                L.req_del = &I::req_del;
+            }
         }
     };
     if (hash == 0)
@@ -475,6 +484,11 @@ bool pick_phase_fb(uint32_t hash, uint32_t placement, PhaseLaunch &L) {
         placement ? fill(PhaseInst<F, 1, 1, BMAX>{}) : fill(PhaseInst<F, 1, 0, BMAX>{});
     return true;
 }
+
+// Launchers for classes of any f (no request kernels): query and delete in
+// cf_set_any.hip, insert in cf_set_insi_any.hip (built at -O1).
+bool pick_phase_any(uint32_t hash, uint32_t placement, PhaseLaunch &out);
+bool pick_phase_insert_any(uint32_t hash, uint32_t placement, PhaseLaunch &out);
 
 template <int F, bool INSERT>
 bool pick_phase_f(uint32_t hash, uint32_t placement, uint32_t bmax, PhaseLaunch &L) {

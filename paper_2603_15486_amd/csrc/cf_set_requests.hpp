@@ -39,21 +39,29 @@ struct ReqSpan {
     uint32_t e0[kMaxClasses], e1[kMaxClasses];
 };
 
-// Run fn(Geom<F, b>{}) for the bucket sizes the library compiles, up to
-// BMAX slots.  A kernel holds the code of every bucket size it may meet and
-// takes the registers of the largest: the 32-slot insert path alone limits
-// a kernel to 4 waves per SIMD, so sets whose buckets have at most 16 slots
-// get kernels without it (BMAX = 16).
+// Run fn(Geom<f, b>{}) for the bucket sizes the library compiles, up to
+// BMAX slots, and fingerprints of f = F bits, or of any width if F = 0.  A
+// kernel holds the code of every geometry it may meet and takes the registers
+// of the largest: the 32-slot insert path alone limits a kernel to 4 waves
+// per SIMD, so sets whose buckets have at most 16 slots get kernels without
+// it (BMAX = 16), and kernels for any width are for batches whose launches
+// cost more than their work.
 template <int F, int BMAX, class Fn>
-__device__ __forceinline__ void with_b(uint32_t b, Fn &&fn) {
-    switch (b) {
-        case 4: fn(cfk::Geom<F, 4>{}); break;
-        case 8: fn(cfk::Geom<F, 8>{}); break;
-        case 16: fn(cfk::Geom<F, 16>{}); break;
-        case 32:
-            if constexpr (BMAX >= 32) fn(cfk::Geom<F, 32>{});
-            break;
-        default: break;
+__device__ __forceinline__ void with_b(uint32_t f, uint32_t b, Fn &&fn) {
+    if constexpr (F == 0) {
+        if (f == 8) with_b<8, BMAX>(f, b, fn);
+        else if (f == 16) with_b<16, BMAX>(f, b, fn);
+        else if (f == 32) with_b<32, BMAX>(f, b, fn);
+    } else {
+        switch (b) {
+            case 4: fn(cfk::Geom<F, 4>{}); break;
+            case 8: fn(cfk::Geom<F, 8>{}); break;
+            case 16: fn(cfk::Geom<F, 16>{}); break;
+            case 32:
+                if constexpr (BMAX >= 32) fn(cfk::Geom<F, 32>{});
+                break;
+            default: break;
+        }
     }
 }
 
@@ -99,7 +107,7 @@ __global__ __launch_bounds__(kBlock) void req_query_kernel(ReqSpan sp,
                                                            const SetFilter *__restrict__ filters) {
     uint32_t c, p0, p1;
     const ReqSrc src = req_block(sp, tab, c, p0, p1);
-    with_b<F, BMAX>(sp.b[c], [&](auto g) {
+    with_b<F, BMAX>(F, sp.b[c], [&](auto g) {
         query_bin<decltype(g), HASH, POL, kBlock>(src, filters, p0, p1);
     });
 }
@@ -114,7 +122,7 @@ __global__ __launch_bounds__(kBlock) void req_delete_kernel(ReqSpan sp,
     const ReqSrc src = req_block(sp, tab, c, p0, p1);
     Tally<kBlock> tally{lds, nfilters};
     tally.init();
-    with_b<F, BMAX>(sp.b[c], [&](auto g) {
+    with_b<F, BMAX>(F, sp.b[c], [&](auto g) {
         delete_bin<decltype(g), HASH, POL, kBlock>(src, filters, p0, p1, tally);
     });
     tally.flush(filters);
@@ -133,7 +141,7 @@ __global__ __launch_bounds__(kBlock) void req_insert_kernel(ReqSpan sp,
     const ReqSrc src = req_block(sp, tab, c, p0, p1);
     Tally<kBlock> tally{lds, nfilters};
     tally.init();
-    with_b<F, BMAX>(sp.b[c], [&](auto g) {
+    with_b<F, BMAX>(F, sp.b[c], [&](auto g) {
         insert_bin<decltype(g), HASH, POL, kBlock>(src, filters, p0, p1, queue + p0, &s_qn, tally,
                                                    wave_bfs);
     });
