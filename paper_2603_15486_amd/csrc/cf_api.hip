@@ -207,7 +207,7 @@ constexpr uint64_t kPartBytes = 64 << 10;
 constexpr uint64_t kMinPartBytes = 1 << 10;
 constexpr uint32_t kWantParts = 256;
 constexpr uint32_t kOneLevelBins = 256;
-constexpr uint32_t kRestExtra = 64;  // blocks on the overflow list
+constexpr uint32_t kRestExtra = 512;  // blocks on the overflow list
 
 uint64_t slots_of(const cf_filter *f) { return f->p.num_buckets * f->p.slots_per_bucket; }
 
@@ -223,8 +223,10 @@ uint64_t slots_of(const cf_filter *f) { return f->p.num_buckets * f->p.slots_per
 //    (2^27 keys), where direct requests cost more, 6.8 / 6.9 / 9.9 -> 3.6 /
 //    4.4 / 8.2 ms; a thirty-second on 512 MiB 357 / 361 / 542 -> 374 / 457 /
 //    630.
+// A batch of more than twice the slots, most of which must fail, goes direct:
+// its failing searches need more blocks than a small table has parts.
 bool bulk_wanted(const cf_filter *f, uint64_t n) {
-    if (!f->may_partition || n < (1ull << 19)) return false;
+    if (!f->may_partition || n < (1ull << 19) || n / 2 > slots_of(f)) return false;
     const uint64_t share = n < (1ull << 20)                 ? 4
                            : n < (1ull << 22)               ? 8
                            : f->table_bytes < (2ull << 30) ? 12
@@ -232,7 +234,8 @@ bool bulk_wanted(const cf_filter *f, uint64_t n) {
     return std::min(n, cfk::kMaxBulkKeys) >= slots_of(f) / share;
 }
 
-// No batch above this many keys goes direct if a larger one goes partitioned.
+// Where a batch goes partitioned, smaller ones that go direct have at most
+// this many keys.
 uint64_t direct_most(const cf_filter *f) { return std::max(slots_of(f) / 8, uint64_t(1) << 20); }
 
 uint32_t bulk_cap(double mean) {

@@ -117,6 +117,27 @@ def test_copies_of_few_keys_fail_and_are_logged(cf, b, f):
     r.close()
 
 
+@pytest.mark.parametrize("m,b,f", [(64, 16, 16), (1 << 14, 16, 8)])
+def test_batch_that_cannot_fit(cf, m, b, f):
+    """Batches of 512 and of two times the slots: what does not fit is
+    reported, counted and logged (the log keeps its first entries)."""
+    n = 1 << 19
+    g = cf.CuckooFilter(m, b, f, max_evict=4, seed=13, lost_capacity=n)
+    keys = K.keys(13, 0, n)
+    ok = dev_zeros_u8(n)
+    g.insert(dev_u64(keys), ok)
+    fails = g.failures()
+    assert int(ok.sum()) == n - fails == g.count() <= m * b
+    r = OracleFilter(m, b, f, max_evict=4, seed=13)
+    r.load_words(host_u64(g.export_table()))
+    lost = g.lost(n)
+    assert len(lost[0]) == fails and r.count == g.count()
+    want = (r.digest_keys(keys) - r.digest_pairs(*lost)) % 2**64
+    assert r.digest_table() % 2**64 == want
+    g.close()
+    r.close()
+
+
 def test_captured_and_replayed(cf):
     """Reset and partitioned insert in one graph, replayed between eager
     work: each replay leaves the same content."""
