@@ -164,7 +164,8 @@ def _set_batch_spans(trace):
     import re
     short = {"partition_kernel": "partition", "persist_kernel": "persistent",
              "set_query_kernel": "query", "set_delete_kernel": "delete",
-             "set_insert_kernel": "insert", "phase_query_kernel": "query*",
+             "set_insert_kernel": "insert", "phase_front_kernel": "partition+query*",
+             "phase_query_kernel": "query*",
              "phase_delete_kernel": "delete*", "phase_insert_kernel": "insert*"}
     ev = []
     for r in trace:

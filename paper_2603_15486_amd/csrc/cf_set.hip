@@ -277,7 +277,8 @@ cf_status enqueue_persistent(cf_set *s, const Batch &bt, hipStream_t st) {
 
 // Operations per chunk for a batch of n: the shape's, or less for a batch
 // that would leave compute units without a block (a chunk is one block's
-// work in every launch; results do not depend on it).
+// work in every launch; results do not depend on it).  One class, 20 000
+// operations 32 -> 18 us, 2^18 41 -> 32.
 uint32_t chunk_for(const cf_set *s, uint64_t n) {
     uint32_t c = s->chunk;
     while (c > kSmallChunk && (n + c - 1) / c < uint64_t(s->cus)) c /= 2;

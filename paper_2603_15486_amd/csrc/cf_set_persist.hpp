@@ -247,6 +247,9 @@ __global__ __launch_bounds__(BT) void persist_kernel(Batch bt, const SetFilter *
 // starts) goes to the scratch as in partition_chunk.  Apart, the partition
 // read every kind and id twice and the queries then fetched entry, id and key
 // one behind another from scattered places before their first probe.
+// Per 2^22 operations over 256 filters: 19 + 130 us apart, 134 together, 26 of
+// them before the first probe (a batch of invalid operations).  512 threads:
+// with 256 and chunks of 1024 to 4096 the batch took 259-277 us for 257.
 // LDS per block: 13 bytes per operation of the chunk.
 constexpr int kFrontBlock = 512;
 constexpr int kFrontItems = int(kMaxChunk) / kFrontBlock;

@@ -26,7 +26,8 @@ struct ReqEntry {
     uint32_t fid;
 };
 
-// Positions per block.
+// Positions per block: a burst of 1024 requests of 1..2^20 keys took 4.49-4.56
+// ms with 512, 4.54 with 1024 and 4.93 with 2048 (7.96 laid out).
 constexpr uint32_t kReqOps = 1024;
 
 // One launch: its classes' bucket sizes, and per class the first block, the
