@@ -23,7 +23,7 @@
 //  insert_kernel        the searches of the entries left over (Rest)
 //
 // Measured, builds of 2 MiB (b = 4, f = 16), 64 MiB (b = 4, f = 8) and 512 MiB
-// (b = 16, f = 16) from one batch: 190, 3766 and 12476 us direct, 135, 1866
+// (b = 16, f = 16) from one batch: 190, 3766 and 12476 us direct, 135, 1731
 // and 5840 us this way.  The kernels are streams: of a pass of 2^27 keys on
 // 512 MiB the split takes 478 us (17 bytes a key: 4.5 TB/s), the resplit 548
 // (3.7 TB/s), the placement 487 on an empty table and 745 on a half-full one

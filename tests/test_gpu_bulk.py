@@ -47,20 +47,22 @@ def test_direct_insert_of_the_same_batch(cf, b, f, pl):
     r.close()
 
 
-# tables of one level of parts (the first three) and of two; the offset ones
-# end in a cut part, the 4-byte buckets of an odd count in one that is no
-# multiple of 16 bytes
-@pytest.mark.parametrize("m,b,f,pl,hk", [
-    ((1 << 17) + 3, 16, 16, 1, 1), (1 << 16, 32, 32, 0, 0), (1 << 18, 8, 8, 0, 0),
-    ((1 << 22) + 4097, 4, 8, 1, 0),
-    (1 << 23, 4, 8, 0, 1), (3 * (1 << 18) + 7, 16, 16, 1, 0), (1 << 20, 8, 32, 0, 1),
-    ((1 << 18) + 3, 32, 32, 1, 0), (1 << 21, 4, 16, 0, 0)])
-def test_partitioned_fill_on_a_half_full_table(cf, m, b, f, pl, hk):
+# tables of one level of parts (up to 1024) and, the last four, of two; the
+# offset ones end in a cut part, the 4-byte buckets of an odd count in one
+# that is no multiple of 16 bytes
+@pytest.mark.parametrize("m,b,f,pl,hk,before,after", [
+    ((1 << 17) + 3, 16, 16, 1, 1, 0.5, 0.92), (1 << 16, 32, 32, 0, 0, 0.5, 0.92),
+    (1 << 18, 8, 8, 0, 0, 0.5, 0.9), ((1 << 22) + 4097, 4, 8, 1, 0, 0.5, 0.85),
+    (3 * (1 << 18) + 7, 16, 16, 1, 0, 0.5, 0.92), (1 << 20, 8, 32, 0, 1, 0.5, 0.9),
+    (1 << 21, 4, 16, 0, 0, 0.5, 0.85), (1 << 19, 32, 32, 0, 0, 0.1, 0.36),
+    ((1 << 23) + 4097, 4, 16, 1, 0, 0.05, 0.31), ((1 << 21) + 5, 16, 16, 1, 1, 0.5, 0.9),
+    ((1 << 24) + 4097, 4, 8, 1, 0, 0.02, 0.15), ((1 << 19) + 3, 32, 32, 1, 1, 0.6, 0.92)])
+def test_partitioned_fill_on_a_part_full_table(cf, m, b, f, pl, hk, before, after):
     slots = m * b
     g = cf.CuckooFilter(m, b, f, hash=hk, seed=5, placement=pl)
-    lf = 0.85 if b == 4 else 0.92
-    first, n = slots // 2 + 3, int(lf * slots) - slots // 2
-    assert n >= slots // 4 and n >= 1 << 19
+    first = int(before * slots) + 3
+    n = int(after * slots) - first
+    assert n >= slots // (4 if n < 1 << 20 else 8 if n < 1 << 22 else 12) and n >= 1 << 19
     keys = K.keys(5, 0, first + n)
     g.insert(dev_u64(keys[:first]))
     ok, kicks = dev_zeros_u8(n), dev_zeros_u32(n)
