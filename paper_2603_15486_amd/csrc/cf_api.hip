@@ -7,7 +7,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -193,96 +192,24 @@ cf_status grow_queue(cf_filter *f, uint64_t n, hipStream_t s) {
 // ------------------------------------------------- partitioned insert
 // (cf_bulk.hpp)
 
-// Layout of one pass of `len` keys.
-struct BulkPlan {
-    uint32_t shift, parts;      // parts of 2^shift buckets
-    uint32_t bins, fine;        // bins of 2^fine parts; fine = 0: a bin is a part
-    uint32_t cap1, cap2;        // entries per run of a bin, per part (fine > 0)
-    uint32_t list_cap;
-    uint64_t cursors;           // cursors and overflow count; zero between passes
-    uint64_t o_cur, o_listn, o_a, o_a32, o_b, o_b32, o_list, o_list32, o_ovl, bytes;
-};
-
-constexpr uint64_t kPartBytes = 64 << 10;
-constexpr uint64_t kMinPartBytes = 1 << 10;
-constexpr uint32_t kWantParts = 256;
-// Up to this many parts one level of grouping, although a tile then leaves
-// runs of four entries: 32 MiB (b = 16, f = 16) 291 us with one level and 329
-// with two, 64 MiB 551 and 586 (b = 4, f = 8: 1731 and 1862), but 128 MiB 1274
-// and 1110.
-constexpr uint32_t kOneLevelBins = 1024;
 constexpr uint32_t kRestExtra = 512;  // blocks on the overflow list
 
-uint64_t slots_of(const cf_filter *f) { return f->p.num_buckets * f->p.slots_per_bucket; }
+using cfl::BulkPlan;
 
-// Whether a batch of n goes partitioned.  It then costs a fixed chain of
-// launches (40 us) and the table read and written twice, which must be less
-// than a CAS per key.  Measured, direct -> partitioned:
-//  - from empty, 2^19 keys 46-63 -> 41-47 us, 2^18 keys 39-45 -> 35-46: no
-//    gain below 2^19 keys;
-//  - an eighth of the slots at load 0 / 0.5 / 0.8, 32 MiB of 32-bit
-//    fingerprints (2^20 keys) 53 / 73 / 152 -> 56 / 71 / 127 us, 512 MiB of
-//    16-bit ones (2^25 keys) 1363 / 1367 / 1751 -> 611 / 759 / 1357;
-//  - a sixteenth on 512 MiB 687 / 694 / 958 -> 450 / 549 / 983, on 4 GiB
-//    (2^27 keys), where direct requests cost more, 6.8 / 6.9 / 9.9 -> 3.6 /
-//    4.4 / 8.2 ms; a thirty-second on 512 MiB 357 / 361 / 542 -> 374 / 457 /
-//    630.
-// A batch of more than twice the slots, most of which must fail, goes direct:
-// its failing searches need more blocks than a small table has parts.
+cfl::BulkTable table_of(const cf_filter *f) {
+    return {f->p.num_buckets, f->p.slots_per_bucket, f->p.fp_bits};
+}
+
+BulkPlan bulk_plan(const cf_filter *f, uint64_t len) { return cfl::bulk_plan(table_of(f), len); }
+
 bool bulk_wanted(const cf_filter *f, uint64_t n) {
-    if (!f->may_partition || n < (1ull << 19) || n / 2 > slots_of(f)) return false;
-    const uint64_t share = n < (1ull << 20)                 ? 4
-                           : n < (1ull << 22)               ? 8
-                           : f->table_bytes < (2ull << 30) ? 12
-                                                            : 16;
-    return std::min(n, cfk::kMaxBulkKeys) >= slots_of(f) / share;
+    return f->may_partition && cfl::bulk_wanted(table_of(f), n);
 }
 
 // Where a batch goes partitioned, smaller ones that go direct have at most
 // this many keys.
-uint64_t direct_most(const cf_filter *f) { return std::max(slots_of(f) / 8, uint64_t(1) << 20); }
-
-uint32_t bulk_cap(double mean) {
-    return (uint32_t(mean + 8 * std::sqrt(mean) + 16) + 15u) & ~15u;
-}
-
-BulkPlan bulk_plan(const cf_filter *f, uint64_t len) {
-    const uint64_t m = f->p.num_buckets, bucket = uint64_t(f->p.slots_per_bucket) * f->p.fp_bits / 8;
-    BulkPlan p{};
-    while ((bucket << (p.shift + 1)) <= kPartBytes) ++p.shift;
-    auto parts_at = [&](uint32_t s) { return (m + (1ull << s) - 1) >> s; };
-    while (parts_at(p.shift) < kWantParts && (bucket << p.shift) > kMinPartBytes) --p.shift;
-    p.parts = uint32_t(parts_at(p.shift));
-    while (p.parts > kOneLevelBins && (1u << (2 * p.fine)) < p.parts) ++p.fine;
-    p.bins = (p.parts + (1u << p.fine) - 1) >> p.fine;
-    const double share = double(1ull << (p.shift + p.fine)) / double(m);  // of a bin
-    const uint64_t tiles = (len + cfk::kSplitTile - 1) / cfk::kSplitTile;
-    const uint64_t per_run = (tiles + cfk::kBulkSegs - 1) / cfk::kBulkSegs * cfk::kSplitTile;
-    p.cap1 = bulk_cap(std::min(1.0, share) * double(std::min(per_run, len)));
-    p.cap2 = p.fine ? bulk_cap(double(len) * double(1ull << p.shift) / double(m)) : 0;
-    p.list_cap = p.fine ? p.cap2 : cfk::kBulkSegs * p.cap1;
-    const uint64_t wide = f->p.fp_bits == 32 ? 4 : 0;
-    const uint64_t n1 = uint64_t(p.bins) * cfk::kBulkSegs * p.cap1;
-    const uint64_t n2 = uint64_t(p.parts) * p.cap2;
-    const uint64_t lists = uint64_t(p.parts) * p.list_cap;
-    auto take = [&](uint64_t bytes) {
-        const uint64_t o = p.bytes;
-        p.bytes += (bytes + 255) & ~uint64_t(255);
-        return o;
-    };
-    p.cursors = 2 * (uint64_t(p.bins) * cfk::kBulkSegs + (p.fine ? p.parts : 0)) + 1;
-    p.o_cur = take(p.cursors * 4);
-    p.o_listn = take((uint64_t(p.parts) + 1) * 4);
-    // the first level's entries, and later (they are used up by then) the
-    // eviction queue of the overflow list
-    p.o_a = take(n1 * 8);  // n1 >= len
-    p.o_a32 = take(n1 * wide);
-    p.o_b = take(n2 * 8);
-    p.o_b32 = take(n2 * wide);
-    p.o_list = take(lists * 8);
-    p.o_list32 = take(lists * wide);
-    p.o_ovl = take(len * 4);
-    return p;
+uint64_t direct_most(const cf_filter *f) {
+    return std::max(table_of(f).slots() / 8, uint64_t(1) << 20);
 }
 
 // Room for passes of min(n, kMaxBulkKeys) keys; false if there is none to be

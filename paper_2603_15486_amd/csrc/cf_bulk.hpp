@@ -41,12 +41,6 @@
 
 namespace cfk {
 
-// 44 KiB of staging for 8-byte entries: three blocks on a compute unit.
-constexpr int kSplitBlock = 512;
-constexpr int kSplitItems = 8;                            // entries per thread and tile
-constexpr int kSplitTile = kSplitBlock * kSplitItems;
-constexpr uint32_t kMaxBulkBins = 1024;
-constexpr uint32_t kBulkSegs = 8;                         // one per XCD, see bulk_split_kernel
 // A part of 64 KiB leaves room for two blocks on a compute unit, one loading
 // or storing while the other places; parts of 32 KiB (with 512 or 1024
 // threads) built the 512 MiB table 8-13% slower.
@@ -149,11 +143,6 @@ __device__ __forceinline__ void split_tile(uint8_t *lds, uint32_t have, uint32_t
             append_wave(ovl, ovl_n, unpack_ent<F>(sa[p], F == 32 ? sb[p] : 0u).idx);
         }
     }
-}
-
-// Bytes of dynamic LDS of the two split kernels.
-inline size_t split_lds(int f, uint32_t nbins) {
-    return size_t(kSplitTile) * (8 + (f == 32 ? 4 : 0) + 2) + size_t(nbins) * 12;
 }
 
 // First level: keys [0, n) to bins of 2^shift buckets.  Each bin has

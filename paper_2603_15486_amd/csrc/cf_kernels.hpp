@@ -8,6 +8,7 @@
 // are full to a second pass of the same block (see insert_kernel).
 #pragma once
 
+#include "cf_bulk_plan.hpp"
 #include "cf_device.hpp"
 
 namespace cfk {
@@ -34,44 +35,11 @@ struct Counters {
 };
 
 // ------------------------------------------ entries of a partitioned insert
-// (cf_bulk.hpp)
-constexpr uint32_t kBulkIdxBits = 27;  // keys of one pass
-constexpr uint64_t kMaxBulkKeys = 1ull << kBulkIdxBits;
-
-// One entry: the tag as written in its bucket, the key's index in the pass, and
-// the low bits of the bucket (its place within the bin).  8 bytes for fingerprints of 8
-// and 16 bits (tag | index | bucket bits, so 64 - 27 - f of the latter), and
-// 12 bytes in two arrays for 32-bit ones.
-struct Ents {
-    uint64_t *a;
-    uint32_t *b;  // f = 32 only: the index
-};
-
-struct Ent {
-    uint32_t tag, idx, bucket;
-};
-
+// (cf_bulk.hpp; packed as cf_bulk_plan.hpp says)
 struct Raw {  // as loaded: a key, or an entry's words
     uint64_t a;
     uint32_t b;
 };
-
-template <int F>
-__device__ __forceinline__ uint64_t pack_ent(const Ent &e) {
-    if constexpr (F == 32) return uint64_t(e.tag) | (uint64_t(e.bucket) << 32);
-    else
-        return uint64_t(e.tag) | (uint64_t(e.idx) << F) |
-               (uint64_t(e.bucket) << (F + kBulkIdxBits));
-}
-
-template <int F>
-__device__ __forceinline__ Ent unpack_ent(uint64_t a, uint32_t b) {
-    if constexpr (F == 32) return Ent{uint32_t(a), b, uint32_t(a >> 32)};
-    else
-        return Ent{uint32_t(a) & ((1u << F) - 1u),
-                   uint32_t(a >> F) & ((1u << kBulkIdxBits) - 1u),
-                   uint32_t(a >> (F + kBulkIdxBits))};
-}
 
 // What a partitioned insert left over (see insert_kernel).
 struct NoRest {};

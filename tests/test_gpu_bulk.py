@@ -167,3 +167,19 @@ def test_captured_and_replayed(cf):
         assert bool(g.query(keys).all())
         assert _nonzero_slots(g.export_table(), f) == n
     g.close()
+
+
+@pytest.mark.parametrize("extra", [0, 1, 3])
+def test_most_bucket_bits_of_an_entry(cf, extra):
+    """2^29 buckets of 4 x 16 bits (4 GiB) take every bucket bit of an entry; with a
+    few buckets more there is none left for the topmost, and the batch goes
+    direct.  Either way every key is found where queries look."""
+    m, n = (1 << 29) + extra, 1 << 27
+    g = cf.CuckooFilter(m, 4, 16, seed=14, placement=oracle.PLACE_OFFSET)
+    keys = torch.empty(n, dtype=torch.int64, device="cuda")
+    cf.cf_keygen(keys, 14, 0)
+    ok = dev_zeros_u8(n)
+    g.insert(keys, ok)
+    assert g.failures() == 0 and bool(ok.all()) and g.count() == n
+    assert bool(g.query(keys).all())
+    g.close()
