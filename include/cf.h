@@ -117,9 +117,9 @@ cf_status cf_create_in(const cf_params *params, void *d_table, uint64_t nbytes,
 cf_status cf_destroy(cf_filter *flt);
 
 /* Reserve internal scratch for batches of up to max_batch keys so that later
- * inserts of that size do not allocate: the eviction queue, and for a
- * max_batch that would go partitioned (see cf_insert) its workspace of 20 to
- * 40 bytes per key of min(max_batch, 2^27).  Synchronous. */
+ * inserts of that size do not allocate: the eviction queue, and where such a
+ * batch would go partitioned (see cf_insert) the workspace of 20 to
+ * 40 bytes per key of the largest that would, or of 2^27.  Synchronous. */
 cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
 
 /* Alg. 1 + Sec. 4.6.1: insert n keys.  d_ok (nullable): uint8[n], 1 if the

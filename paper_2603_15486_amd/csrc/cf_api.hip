@@ -206,6 +206,10 @@ bool bulk_wanted(const cf_filter *f, uint64_t n) {
     return f->may_partition && cfl::bulk_wanted(table_of(f), n);
 }
 
+uint64_t bulk_most(const cf_filter *f, uint64_t n) {
+    return f->may_partition ? cfl::bulk_most(table_of(f), n) : 0;
+}
+
 // Where a batch goes partitioned, smaller ones that go direct have at most
 // this many keys.
 uint64_t direct_most(const cf_filter *f) {
@@ -432,8 +436,10 @@ cf_status cf_destroy(cf_filter *f) {
 cf_status cf_reserve(cf_filter *f, uint64_t max_batch) {
     if (!f) return fail(CF_EINVAL, "filter is NULL");
     DeviceGuard g(f->device);
-    // batches that go partitioned need no queue; those below the rule do
-    if (bulk_wanted(f, max_batch) && bulk_reserve(f, max_batch, nullptr))
+    // the workspace for the largest batch that goes partitioned, the queue
+    // for the largest that goes direct
+    const uint64_t most = bulk_most(f, max_batch);
+    if (most && bulk_reserve(f, most, nullptr) && most == max_batch)
         max_batch = std::min(max_batch, direct_most(f));
     return grow_queue(f, max_batch, nullptr);
 }

@@ -170,4 +170,11 @@ inline bool bulk_wanted(const BulkTable &t, uint64_t n) {
     return len * share >= t.slots() && bulk_fits(t, bulk_plan(t, len));
 }
 
+// The largest batch of at most n keys that goes partitioned, 0 if none does:
+// up to twice the slots the rule only gets easier with more keys.
+inline uint64_t bulk_most(const BulkTable &t, uint64_t n) {
+    const uint64_t most = std::min(n, 2 * t.slots() + 1);
+    return bulk_wanted(t, most) ? most : 0;
+}
+
 }  // namespace cfl

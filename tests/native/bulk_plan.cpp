@@ -22,6 +22,10 @@ int fits(uint64_t m, uint32_t b, uint32_t f, uint64_t n) {
     return cfl::bulk_fits(t, cfl::bulk_plan(t, n));
 }
 
+uint64_t most(uint64_t m, uint32_t b, uint32_t f, uint64_t n) {
+    return cfl::bulk_most(cfl::BulkTable{m, b, f}, n);
+}
+
 void plan(uint64_t m, uint32_t b, uint32_t f, uint64_t len, uint64_t *out) {
     const cfl::BulkPlan p = cfl::bulk_plan(cfl::BulkTable{m, b, f}, len);
     const uint64_t v[] = {p.shift, p.parts, p.bins,  p.fine,  p.cap1, p.cap2, p.list_cap, p.cursors,

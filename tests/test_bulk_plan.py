@@ -37,6 +37,8 @@ def lib(tmp_path_factory):
     u32, u64 = ctypes.c_uint32, ctypes.c_uint64
     so.wanted.argtypes = [u64, u32, u32, u64]
     so.fits.argtypes = [u64, u32, u32, u64]
+    so.most.argtypes = [u64, u32, u32, u64]
+    so.most.restype = u64
     so.plan.argtypes = [u64, u32, u32, u64, ctypes.POINTER(u64)]
     so.plan.restype = None
     so.entry_survives.argtypes = [u32, u32, u32, u32]
@@ -144,3 +146,18 @@ def test_a_workspace_serves_every_smaller_batch(lib, b, f):
             p = Plan(lib, m, b, f, min(n, PASS))
             assert p.bytes >= held and cursors in (None, p.cursors), (m, b, f, n)
             held, cursors = p.bytes, p.cursors
+
+
+@pytest.mark.parametrize("f", [8, 16, 32])
+@pytest.mark.parametrize("b", [4, 8, 16, 32])
+def test_the_largest_partitioned_batch_below_any_other(lib, b, f):
+    """What is reserved for batches of up to n keys serves all of them, also
+    where n itself is too large for the table to go partitioned."""
+    for m in bucket_counts():
+        held = 0
+        for n in batch_sizes(m * b) + [8 * m * b]:
+            if lib.wanted(m, b, f, n):
+                held = max(held, n)
+            most = lib.most(m, b, f, n)
+            assert held <= most <= n and (most == 0) == (held == 0), (m, b, f, n)
+            assert most == 0 or lib.wanted(m, b, f, most), (m, b, f, n)

@@ -1,0 +1,48 @@
+"""What a filter's inserts allocate and keep: cf_reserve and a larger batch
+before cover every smaller one, whichever way the batches go."""
+import pytest
+
+from gpu_util import dev_u64, dev_zeros_u8
+from workloads import keys as K
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def cf():
+    import paper_2603_15486_amd as mod
+    return mod
+
+
+def _free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def _inserts_allocate_nothing(cf, g, keys, sizes):
+    """Inserts of these sizes into an emptied filter leave free memory alone."""
+    warm = cf.CuckooFilter(g.num_buckets, g.slots_per_bucket, g.params.fp_bits)
+    for n in sizes:  # what the runtime itself takes for these launches
+        warm.reset()
+        warm.insert(keys[:n])
+        warm.query(keys[:n])
+    for n in sizes:
+        ok = dev_zeros_u8(n)
+        g.reset()
+        g.query(keys[:n])
+        free = _free()
+        g.insert(keys[:n], ok)
+        assert _free() == free, n
+        assert bool(ok.all()) and g.count() == n and bool(g.query(keys[:n]).all())
+
+
+def test_reserve_beyond_twice_the_slots(cf):
+    """A reserve for batches that go direct covers the smaller ones that go
+    partitioned."""
+    m, b, f = 1 << 16, 16, 16
+    g = cf.CuckooFilter(m, b, f, seed=21)
+    keys = dev_u64(K.keys(21, 0, int(0.95 * m * b)))
+    g.reserve(1 << 24)
+    _inserts_allocate_nothing(cf, g, keys, (keys.numel(), 1 << 19, 5000))
+    g.close()
