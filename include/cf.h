@@ -139,8 +139,8 @@ cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
  * searches run, whose draws come from a key's index, bucket and fingerprint
  * instead of the key.  The workspace stays with the filter until
  * cf_destroy; where it cannot be allocated, and on a stream under capture
- * that would need to, and under CF_GRID_PER_CU, the batch goes the direct
- * way. */
+ * that would need to, and in a batch smaller than one before that left none,
+ * and under CF_GRID_PER_CU, the batch goes the direct way. */
 cf_status cf_insert(cf_filter *flt, const uint64_t *d_keys, uint64_t n,
                     uint8_t *d_ok, uint32_t *d_kicks, void *stream);
 

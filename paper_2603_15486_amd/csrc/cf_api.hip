@@ -140,6 +140,7 @@ struct cf_filter {
     bool may_partition;   // false: the caller fixed the launch shape
     char *bulk;           // workspace of the partitioned insert
     uint64_t bulk_bytes;
+    uint64_t scratch_keys;  // batches of up to this many keys allocate nothing
     bool owns_table;     // false for a table in caller memory (cf_create_in)
 };
 
@@ -216,19 +217,31 @@ uint64_t direct_most(const cf_filter *f) {
     return std::max(table_of(f).slots() / 8, uint64_t(1) << 20);
 }
 
-// Room for passes of min(n, kMaxBulkKeys) keys; false if there is none to be
-// had (the caller then inserts directly), which includes a stream under
-// capture.
-bool bulk_reserve(cf_filter *f, uint64_t n, hipStream_t s) {
-    const uint64_t want = bulk_plan(f, std::min(n, cfk::kMaxBulkKeys)).bytes;
-    if (want <= f->bulk_bytes) return true;
+bool capturing(hipStream_t s) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (s && hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-    if (cap != hipStreamCaptureStatusNone) return false;
-    (void)hipDeviceSynchronize();
+    return cap != hipStreamCaptureStatusNone;
+}
+
+// Whether the workspace has room for passes of min(n, kMaxBulkKeys) keys.
+bool bulk_held(const cf_filter *f, uint64_t n) {
+    return bulk_plan(f, std::min(n, cfk::kMaxBulkKeys)).bytes <= f->bulk_bytes;
+}
+
+void bulk_drop(cf_filter *f) {
     if (f->bulk) (void)hipFree(f->bulk);
     f->bulk = nullptr;
     f->bulk_bytes = 0;
+}
+
+// Makes that room; false if there is none to be had (the caller then inserts
+// directly), which includes a stream under capture.
+bool bulk_reserve(cf_filter *f, uint64_t n, hipStream_t s) {
+    const uint64_t want = bulk_plan(f, std::min(n, cfk::kMaxBulkKeys)).bytes;
+    if (want <= f->bulk_bytes) return true;
+    if (capturing(s)) return false;
+    (void)hipDeviceSynchronize();
+    bulk_drop(f);
     if (hipMalloc(&f->bulk, want) != hipSuccess) {
         (void)hipGetLastError();
         f->bulk = nullptr;
@@ -239,12 +252,25 @@ bool bulk_reserve(cf_filter *f, uint64_t n, hipStream_t s) {
     if (hipMemset(f->bulk, 0, bulk_plan(f, 1).cursors * 4) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess) {
         (void)hipGetLastError();
-        (void)hipFree(f->bulk);
-        f->bulk = nullptr;
+        bulk_drop(f);
         return false;
     }
     f->bulk_bytes = want;
     return true;
+}
+
+// Scratch for every batch of up to n keys: the workspace for `bulk` of them
+// (0: none) and the eviction queue for those that go direct.  Where both
+// cannot be had, the queue for all of them alone.
+cf_status reserve_scratch(cf_filter *f, uint64_t n, uint64_t bulk, hipStream_t s) {
+    if (bulk && !bulk_reserve(f, bulk, s)) bulk = 0;
+    cf_status st = grow_queue(f, bulk && bulk == n ? std::min(n, direct_most(f)) : n, s);
+    if (st == CF_ENOMEM && f->bulk && !capturing(s)) {
+        bulk_drop(f);
+        st = grow_queue(f, n, s);
+    }
+    if (st == CF_OK && !capturing(s)) f->scratch_keys = std::max(f->scratch_keys, n);
+    return st;
 }
 
 // Insert n keys in passes of equal size; the workspace is reserved.
@@ -293,7 +319,8 @@ cf_status bulk_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *o
                  cfl::grouped_probe(f->table_bytes, len), int(p.parts * split + kRestExtra), s);
         const cf_status st = check_launch("insert (partitioned)");
         if (st != CF_OK) {
-            f->bulk_bytes = 0;  // the cursors may be left dirty: a new workspace next time
+            // the cursors may be left dirty: a new workspace next time
+            f->bulk_bytes = f->scratch_keys = 0;
             return st;
         }
         lo += len;
@@ -428,7 +455,7 @@ cf_status cf_destroy(cf_filter *f) {
     if (f->lost_bucket) (void)hipFree(f->lost_bucket);
     if (f->lost_tag) (void)hipFree(f->lost_tag);
     if (f->queue) (void)hipFree(f->queue);
-    if (f->bulk) (void)hipFree(f->bulk);
+    bulk_drop(f);
     delete f;
     return CF_OK;
 }
@@ -436,12 +463,7 @@ cf_status cf_destroy(cf_filter *f) {
 cf_status cf_reserve(cf_filter *f, uint64_t max_batch) {
     if (!f) return fail(CF_EINVAL, "filter is NULL");
     DeviceGuard g(f->device);
-    // the workspace for the largest batch that goes partitioned, the queue
-    // for the largest that goes direct
-    const uint64_t most = bulk_most(f, max_batch);
-    if (most && bulk_reserve(f, most, nullptr) && most == max_batch)
-        max_batch = std::min(max_batch, direct_most(f));
-    return grow_queue(f, max_batch, nullptr);
+    return reserve_scratch(f, max_batch, bulk_most(f, max_batch), nullptr);
 }
 
 cf_status cf_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *okv,
@@ -450,7 +472,12 @@ cf_status cf_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *okv
     if (st != CF_OK || n == 0) return st;
     DeviceGuard g(f->device);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (bulk_wanted(f, n) && bulk_reserve(f, n, s)) return bulk_insert(f, keys, n, okv, kicks, s);
+    const bool bulk = bulk_wanted(f, n);
+    if (n > f->scratch_keys) {  // larger than any before
+        st = reserve_scratch(f, n, bulk ? n : 0, s);
+        if (st != CF_OK) return st;
+    }
+    if (bulk && bulk_held(f, n)) return bulk_insert(f, keys, n, okv, kicks, s);
     st = grow_queue(f, n, s);
     if (st != CF_OK) return st;
     const cfk::LostLog log{f->lost_bucket, f->lost_tag, f->lost_cap};

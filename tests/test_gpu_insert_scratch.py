@@ -46,3 +46,40 @@ def test_reserve_beyond_twice_the_slots(cf):
     g.reserve(1 << 24)
     _inserts_allocate_nothing(cf, g, keys, (keys.numel(), 1 << 19, 5000))
     g.close()
+
+
+def test_smaller_batches_after_a_partitioned_one(cf):
+    """A batch that goes partitioned leaves scratch for the smaller ones that
+    go direct, eager or captured."""
+    m, b, f = 1 << 18, 16, 16
+    g = cf.CuckooFilter(m, b, f, seed=22)
+    keys = dev_u64(K.keys(22, 0, int(0.95 * m * b)))
+    n = (1 << 20) - 1  # one key short of the rule's line
+    g.insert(keys)
+    _inserts_allocate_nothing(cf, g, keys, (n, 1 << 19, 5000))
+    ok = dev_zeros_u8(n)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        g.reset()
+        g.insert(keys[:n], ok)
+    for _ in range(3):
+        g.reset()
+        g.insert(keys[n:2 * n])
+        ok.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert bool(ok.all()) and g.count() == n and bool(g.query(keys[:n]).all())
+    g.close()
+
+
+def test_smaller_batches_after_one_that_cannot_fit(cf):
+    """A batch of more than twice the slots goes direct; the smaller ones that
+    would go partitioned have no workspace then, and allocate none."""
+    m, b, f = 1 << 16, 16, 16
+    g = cf.CuckooFilter(m, b, f, max_evict=32, seed=23)
+    keys = dev_u64(K.keys(23, 0, 3 * m * b))
+    g.insert(keys)
+    _inserts_allocate_nothing(cf, g, keys, (int(0.9 * m * b), 1 << 19, 1 << 17))
+    g.close()
