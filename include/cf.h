@@ -140,7 +140,11 @@ cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
  * instead of the key.  The workspace stays with the filter until
  * cf_destroy; where it cannot be allocated, and on a stream under capture
  * that would need to, and in a batch smaller than one before that left none,
- * and under CF_GRID_PER_CU, the batch goes the direct way. */
+ * and under CF_GRID_PER_CU, the batch goes the direct way.
+ * Capture.  A graph that holds a partitioned insert stays valid when a larger
+ * batch outgrows the workspace (the old one is kept until cf_destroy).  One
+ * that holds a direct insert uses the eviction queue, which a batch larger
+ * than any before replaces: reserve for the largest before capturing. */
 cf_status cf_insert(cf_filter *flt, const uint64_t *d_keys, uint64_t n,
                     uint8_t *d_ok, uint32_t *d_kicks, void *stream);
 

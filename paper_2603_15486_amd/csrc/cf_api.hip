@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 
 #include "cf.h"
@@ -140,6 +141,11 @@ struct cf_filter {
     bool may_partition;   // false: the caller fixed the launch shape
     char *bulk;           // workspace of the partitioned insert
     uint64_t bulk_bytes;
+    bool bulk_captured;   // a graph may hold pointers into it
+    struct Kept {
+        char *p;
+        Kept *next;
+    } *kept;              // outgrown ones that a graph may still use
     uint64_t scratch_keys;  // batches of up to this many keys allocate nothing
     bool owns_table;     // false for a table in caller memory (cf_create_in)
 };
@@ -228,10 +234,18 @@ bool bulk_held(const cf_filter *f, uint64_t n) {
     return bulk_plan(f, std::min(n, cfk::kMaxBulkKeys)).bytes <= f->bulk_bytes;
 }
 
+// Gives the workspace back, or keeps it until cf_destroy for the graphs that
+// were captured with it (their replays leave its cursors at zero, as every
+// pass does).  Without memory for the note it is never freed.
 void bulk_drop(cf_filter *f) {
-    if (f->bulk) (void)hipFree(f->bulk);
+    if (f->bulk && f->bulk_captured) {
+        if (auto *k = new (std::nothrow) cf_filter::Kept{f->bulk, f->kept}) f->kept = k;
+    } else if (f->bulk) {
+        (void)hipFree(f->bulk);
+    }
     f->bulk = nullptr;
     f->bulk_bytes = 0;
+    f->bulk_captured = false;
 }
 
 // Makes that room; false if there is none to be had (the caller then inserts
@@ -278,6 +292,7 @@ cf_status bulk_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *o
                       uint32_t *kicks, hipStream_t s) {
     const uint64_t passes = (n + cfk::kMaxBulkKeys - 1) / cfk::kMaxBulkKeys;
     const cfk::LostLog log{f->lost_bucket, f->lost_tag, f->lost_cap};
+    if (!f->bulk_captured) f->bulk_captured = capturing(s);
     for (uint64_t k = 0, lo = 0; k < passes; ++k) {
         const uint64_t len = n * (k + 1) / passes - lo;
         const BulkPlan p = bulk_plan(f, len);
@@ -455,7 +470,12 @@ cf_status cf_destroy(cf_filter *f) {
     if (f->lost_bucket) (void)hipFree(f->lost_bucket);
     if (f->lost_tag) (void)hipFree(f->lost_tag);
     if (f->queue) (void)hipFree(f->queue);
-    bulk_drop(f);
+    if (f->bulk) (void)hipFree(f->bulk);
+    while (cf_filter::Kept *k = f->kept) {
+        (void)hipFree(k->p);
+        f->kept = k->next;
+        delete k;
+    }
     delete f;
     return CF_OK;
 }

@@ -83,3 +83,35 @@ def test_smaller_batches_after_one_that_cannot_fit(cf):
     g.insert(keys)
     _inserts_allocate_nothing(cf, g, keys, (int(0.9 * m * b), 1 << 19, 1 << 17))
     g.close()
+
+
+def test_captured_insert_outlives_its_workspace(cf):
+    """A larger batch replaces the workspace; graphs captured before keep
+    theirs and leave the new one alone."""
+    m, b, f = 1 << 17, 16, 16
+    sizes = [int(share * m * b) for share in (0.3, 0.5, 0.9)]
+    g = cf.CuckooFilter(m, b, f, seed=24)
+    keys = dev_u64(K.keys(24, 0, sizes[-1]))
+    ok = dev_zeros_u8(sizes[-1])
+    graphs = []
+    for n in sizes:
+        g.reset()
+        g.insert(keys[:n])  # outgrows the one before
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            g.reset()
+            g.insert(keys[:n], ok[:n])
+        graphs.append(graph)
+    for k in (0, 1, 2, 0, 2, 1, 1, 0):
+        n = sizes[k]
+        ok.zero_()
+        torch.cuda.synchronize()
+        graphs[k].replay()
+        torch.cuda.synchronize()
+        assert int(ok.sum()) == n == g.count() and bool(g.query(keys[:n]).all())
+        g.reset()
+        g.insert(keys, ok)
+        assert bool(ok.all()) and g.count() == sizes[-1]
+    del graphs
+    g.close()
