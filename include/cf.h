@@ -131,9 +131,11 @@ cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
  * for batches of at most 2^19 keys, the breadth-first search loads a level's
  * candidates' other buckets in groups (as many as 128 bytes hold) instead of
  * one by one; it picks the same candidate either way.
- * Batches of 2^19 keys and more that are large against the table (a quarter
- * of its slots, from 2^20 keys an eighth, from 2^22 a twelfth or, on tables
- * of 2 GiB, a sixteenth) go partitioned, in passes of up to 2^27 keys: keys
+ * Batches that are large against the table go partitioned: of at most 4 bytes
+ * of table per key from 2^19 keys, 8 from 2^20, 16 from 2^21 and 24 from 2^22
+ * (32 on tables of 2 GiB) for 16-bit fingerprints and the breadth-first
+ * search; less for other widths and the random walk, and from 2^20 keys for
+ * 32-bit fingerprints (2^21 with b = 32).  They run in passes of up to 2^27 keys: keys
  * are grouped by part of the table and placed part by part, all in their
  * first bucket, then those left over in their second, then the eviction
  * searches run, whose draws come from a key's index, bucket and fingerprint

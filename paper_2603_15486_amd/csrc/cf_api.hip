@@ -204,7 +204,7 @@ constexpr uint32_t kRestExtra = 512;  // blocks on the overflow list
 using cfl::BulkPlan;
 
 cfl::BulkTable table_of(const cf_filter *f) {
-    return {f->p.num_buckets, f->p.slots_per_bucket, f->p.fp_bits};
+    return {f->p.num_buckets, f->p.slots_per_bucket, f->p.fp_bits, f->p.evict == CF_EVICT_DFS};
 }
 
 BulkPlan bulk_plan(const cf_filter *f, uint64_t len) { return cfl::bulk_plan(table_of(f), len); }
@@ -215,12 +215,6 @@ bool bulk_wanted(const cf_filter *f, uint64_t n) {
 
 uint64_t bulk_most(const cf_filter *f, uint64_t n) {
     return f->may_partition ? cfl::bulk_most(table_of(f), n) : 0;
-}
-
-// Where a batch goes partitioned, smaller ones that go direct have at most
-// this many keys.
-uint64_t direct_most(const cf_filter *f) {
-    return std::max(table_of(f).slots() / 8, uint64_t(1) << 20);
 }
 
 bool capturing(hipStream_t s) {
@@ -278,7 +272,7 @@ bool bulk_reserve(cf_filter *f, uint64_t n, hipStream_t s) {
 // cannot be had, the queue for all of them alone.
 cf_status reserve_scratch(cf_filter *f, uint64_t n, uint64_t bulk, hipStream_t s) {
     if (bulk && !bulk_reserve(f, bulk, s)) bulk = 0;
-    cf_status st = grow_queue(f, bulk && bulk == n ? std::min(n, direct_most(f)) : n, s);
+    cf_status st = grow_queue(f, bulk && bulk == n ? cfl::bulk_least(table_of(f), n) : n, s);
     if (st == CF_ENOMEM && f->bulk && !capturing(s)) {
         bulk_drop(f);
         st = grow_queue(f, n, s);

@@ -65,10 +65,12 @@ inline uint64_t split_lds(int f, uint32_t nbins) {
 
 namespace cfl {
 
-// The table a batch goes into: m buckets of b slots of f bits.
+// The table a batch goes into: m buckets of b slots of f bits, filled by the
+// breadth-first search or (walk) the random walk.
 struct BulkTable {
     uint64_t m;
     uint32_t b, f;
+    bool walk;
     uint64_t slots() const { return m * b; }
     uint64_t bucket_bytes() const { return uint64_t(b) * f / 8; }
     uint64_t bytes() const { return m * bucket_bytes(); }
@@ -148,33 +150,62 @@ inline bool bulk_fits(const BulkTable &t, const BulkPlan &p) {
 
 // Whether a batch of n goes partitioned.  It then costs a fixed chain of
 // launches (40 us) and the table read and written twice, which must be less
-// than a CAS per key.  Measured, direct -> partitioned:
-//  - from empty, 2^19 keys 46-63 -> 41-47 us, 2^18 keys 39-45 -> 35-46: no
-//    gain below 2^19 keys;
-//  - an eighth of the slots at load 0 / 0.5 / 0.8, 32 MiB of 32-bit
-//    fingerprints (2^20 keys) 53 / 73 / 152 -> 56 / 71 / 127 us, 512 MiB of
-//    16-bit ones (2^25 keys) 1363 / 1367 / 1751 -> 611 / 759 / 1357;
-//  - a sixteenth on 512 MiB 687 / 694 / 958 -> 450 / 549 / 983, on 4 GiB
-//    (2^27 keys), where direct requests cost more, 6.8 / 6.9 / 9.9 -> 3.6 /
-//    4.4 / 8.2 ms; a thirty-second on 512 MiB 357 / 361 / 542 -> 374 / 457 /
-//    630.
+// than a CAS per key, so the rule is a line of table bytes per key.  The host
+// does not know how full the table is, and the gain is least where it is
+// fullest (the searches cost the same either way, and those of a partitioned
+// batch have fewer blocks to overlap with), so each line lies where a batch
+// still gains that ends at load 0.86 / 0.91 / 0.945 / 0.955 (b = 4 / 8 / 16 /
+// 32).  Measured, direct time over partitioned time at the lines, the least
+// over b and loads 0, 0.5 and the highest (and the mean):
+//   keys, fingerprints      breadth-first              random walk
+//   2^19, 8 / 16 bits    4 B 0.99 (1.07), 4 B 1.04    4 B 0.92 (1.07), 4 B 0.98
+//   2^20, 8 / 16 bits    8 B 1.13 (1.49), 8 B 1.02    8 B 1.02 (1.29), 8 B 1.00
+//   2^20, 32 bits, b < 32   6 B 1.05 (1.10)            6 B 1.00 (1.10)
+//   2^21, 8 / 16 / 32    8 B 1.22, 16 B 1.13, 16 B 1.00    8 B 1.01, 12 B 1.01, 8 B 1.10
+//   2^22, 8 / 16 / 32    12 B 1.30, 24 B 1.17, 16 B 1.01   12 B 1.07, 12 B 1.09, 8 B 1.13
+//   2^24, 8 / 16 / 32    12 B 1.15, 24 B 1.06, 16 B 1.11   12 B 1.03, 12 B 1.10, 8 B 1.18
+//   2^26, 2 GiB, 16 bits    32 B 1.07 (1.41)           32 B 1.05 (1.41)
+//   2^27, 2 GiB, 32 bits    16 B 1.25 (1.56)           16 B 1.22 (1.57)
+// and one step beyond: 16 bits 2^19 8 B 0.87 and 0.93, 2^20 16 B 0.96 and
+// 0.96; random walk 2^22 16 B 0.97, 24 B on 512 MiB 0.95; 32 bits (entries
+// of 12 bytes) 2^20 b = 32 6 B 0.94 and 0.90, 2^22 24 B 0.97, random walk 16 B
+// 0.90, 2^25 keys on 2 GiB 64 B 0.72 and 0.71.  Below 2^19 keys nothing is
+// gained (2^18 from empty 39-45 -> 35-46 us).
 // A batch of more than twice the slots, most of which must fail, goes direct:
 // its failing searches need more blocks than a small table has parts.
-inline bool bulk_wanted(const BulkTable &t, uint64_t n) {
-    if (n < (1ull << 19) || n / 2 > t.slots()) return false;
-    const uint64_t share = n < (1ull << 20)            ? 4
-                           : n < (1ull << 22)          ? 8
-                           : t.bytes() < (2ull << 30) ? 12
-                                                       : 16;
-    const uint64_t len = std::min(n, cfk::kMaxBulkKeys);
-    return len * share >= t.slots() && bulk_fits(t, bulk_plan(t, len));
+inline uint32_t bulk_bytes_per_key(const BulkTable &t, uint64_t n) {
+    const int band = n < (1ull << 20)            ? 0
+                     : n < (1ull << 21)          ? 1
+                     : n < (1ull << 22)          ? 2
+                     : t.bytes() < (2ull << 30) ? 3
+                                                 : 4;
+    constexpr uint8_t most[2][3][5] = {{{4, 8, 8, 12, 16}, {4, 8, 16, 24, 32}, {0, 6, 16, 16, 16}},
+                                       {{4, 8, 8, 12, 16}, {4, 8, 12, 12, 32}, {0, 6, 8, 8, 16}}};
+    if (t.f == 32 && t.b == 32 && band == 1) return 0;
+    return most[t.walk][t.f == 8 ? 0 : t.f == 16 ? 1 : 2][band];
 }
 
-// The largest batch of at most n keys that goes partitioned, 0 if none does:
-// up to twice the slots the rule only gets easier with more keys.
+inline bool bulk_wanted(const BulkTable &t, uint64_t n) {
+    if (n < (1ull << 19) || n / 2 > t.slots()) return false;
+    const uint64_t len = std::min(n, cfk::kMaxBulkKeys);
+    return len * bulk_bytes_per_key(t, n) >= t.bytes() && bulk_fits(t, bulk_plan(t, len));
+}
+
+// The largest batch of at most n keys that goes partitioned, 0 if none does,
+// and the smallest that does if `most` does: up to twice the slots the rule
+// only gets easier with more keys.
 inline uint64_t bulk_most(const BulkTable &t, uint64_t n) {
     const uint64_t most = std::min(n, 2 * t.slots() + 1);
     return bulk_wanted(t, most) ? most : 0;
+}
+
+inline uint64_t bulk_least(const BulkTable &t, uint64_t most) {
+    uint64_t no = 0;
+    while (most - no > 1) {
+        const uint64_t mid = no + (most - no) / 2;
+        (bulk_wanted(t, mid) ? most : no) = mid;
+    }
+    return most;
 }
 
 }  // namespace cfl

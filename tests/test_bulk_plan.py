@@ -35,10 +35,9 @@ def lib(tmp_path_factory):
                            os.path.join(HERE, "native", "bulk_plan.cpp"), "-o", out])
     so = ctypes.CDLL(out)
     u32, u64 = ctypes.c_uint32, ctypes.c_uint64
-    so.wanted.argtypes = [u64, u32, u32, u64]
-    so.fits.argtypes = [u64, u32, u32, u64]
-    so.most.argtypes = [u64, u32, u32, u64]
-    so.most.restype = u64
+    so.wanted.argtypes = so.most.argtypes = so.least.argtypes = so.fits.argtypes = \
+        [u64, u32, u32, ctypes.c_int, u64]
+    so.most.restype = so.least.restype = u64
     so.plan.argtypes = [u64, u32, u32, u64, ctypes.POINTER(u64)]
     so.plan.restype = None
     so.entry_survives.argtypes = [u32, u32, u32, u32]
@@ -55,10 +54,25 @@ def bucket_counts():
     return sorted(m for m in out if 1 <= m <= 1 << 32)
 
 
-def batch_sizes(slots):
-    out = set()
-    for base in (1 << 19, 1 << 20, 1 << 22, PASS, 2 * PASS, slots // 4, slots // 8, slots // 12,
-                 slots // 16, slots, 2 * slots):
+def line(b, f, walk, n, table):
+    """Bytes of table per key up to which a batch of n keys goes partitioned."""
+    if f == 32:
+        if n < 1 << (21 if b == 32 else 20):
+            return 0
+        return 6 if n < 1 << 21 else 8 if walk and (n < 1 << 22 or table < 2 << 30) else 16
+    if n < 1 << 21:
+        return 4 if n < 1 << 20 else 8
+    if f == 8:
+        return 8 if n < 1 << 22 else 12 if table < 2 << 30 else 16
+    if n >= 1 << 22 and table >= 2 << 30:
+        return 32
+    return 12 if walk else 16 if n < 1 << 22 else 24
+
+
+def batch_sizes(m, b, f):
+    out, slots, table = set(), m * b, m * b * f // 8
+    for base in (1 << 19, 1 << 20, 1 << 21, 1 << 22, PASS, 2 * PASS, slots, 2 * slots,
+                 *(table // k for k in (4, 6, 8, 12, 16, 24, 32))):
         out.update(base + d for d in (-1, 0, 1, 2))
     return sorted(n for n in out if n >= 1)
 
@@ -68,15 +82,16 @@ def passes(n):
     return sorted({n * (i + 1) // k - n * i // k for i in range(k)})
 
 
+@pytest.mark.parametrize("walk", [0, 1])
 @pytest.mark.parametrize("f", [8, 16, 32])
 @pytest.mark.parametrize("b", [4, 8, 16, 32])
-def test_every_plan_that_is_run_addresses_what_is_there(lib, b, f):
+def test_every_plan_that_is_run_addresses_what_is_there(lib, b, f, walk):
     bucket = b * f // 8
     seen = 0
     for m in bucket_counts():
         slots = m * b
-        for n in batch_sizes(slots):
-            if not lib.wanted(m, b, f, n):
+        for n in batch_sizes(m, b, f):
+            if not lib.wanted(m, b, f, walk, n):
                 continue
             share = 4 if n < 1 << 20 else 8 if n < 1 << 22 else 12 if m * bucket < 2 << 30 else 16
             assert n >= 1 << 19 and n <= 2 * slots + 1 and min(n, PASS) * share >= slots
@@ -122,42 +137,51 @@ def test_every_plan_that_is_run_addresses_what_is_there(lib, b, f):
 def test_a_bucket_too_many_for_an_entry(lib):
     """2^29 buckets of 4 x 16 bits need all of an entry's 21 bucket bits; a
     few buckets more need 22, and the batch goes direct."""
-    assert lib.fits(1 << 29, 4, 16, PASS)
+    assert lib.fits(1 << 29, 4, 16, 0, PASS)
     assert Plan(lib, 1 << 29, 4, 16, PASS).shift + Plan(lib, 1 << 29, 4, 16, PASS).fine == 21
-    assert lib.wanted(1 << 29, 4, 16, PASS)
+    assert lib.wanted(1 << 29, 4, 16, 0, PASS)
     for m in ((1 << 29) + 1, (1 << 29) + 2, (1 << 29) + 3):
         p = Plan(lib, m, 4, 16, PASS)
         assert p.shift + p.fine == 22
         assert not lib.entry_survives(16, 1, 0, 1 << 21)
-        assert not lib.fits(m, 4, 16, PASS)
-        assert not lib.wanted(m, 4, 16, PASS) and not lib.wanted(m, 4, 16, 2 * PASS)
+        assert not lib.fits(m, 4, 16, 0, PASS)
+        assert not lib.wanted(m, 4, 16, 0, PASS) and not lib.wanted(m, 4, 16, 0, 2 * PASS)
 
 
+@pytest.mark.parametrize("walk", [0, 1])
 @pytest.mark.parametrize("f", [8, 16, 32])
 @pytest.mark.parametrize("b", [4, 8, 16, 32])
-def test_a_workspace_serves_every_smaller_batch(lib, b, f):
+def test_a_workspace_serves_every_smaller_batch(lib, b, f, walk):
     """The size grows with the batch, and the cursors, which a new workspace
     has cleared once, are as many for every batch."""
     for m in bucket_counts():
         held, cursors = 0, None
-        for n in batch_sizes(m * b):
-            if not lib.wanted(m, b, f, n):
+        for n in batch_sizes(m, b, f):
+            if not lib.wanted(m, b, f, walk, n):
                 continue
             p = Plan(lib, m, b, f, min(n, PASS))
             assert p.bytes >= held and cursors in (None, p.cursors), (m, b, f, n)
             held, cursors = p.bytes, p.cursors
 
 
+@pytest.mark.parametrize("walk", [0, 1])
 @pytest.mark.parametrize("f", [8, 16, 32])
 @pytest.mark.parametrize("b", [4, 8, 16, 32])
-def test_the_largest_partitioned_batch_below_any_other(lib, b, f):
+def test_the_largest_partitioned_batch_below_any_other(lib, b, f, walk):
     """What is reserved for batches of up to n keys serves all of them, also
     where n itself is too large for the table to go partitioned."""
     for m in bucket_counts():
         held = 0
-        for n in batch_sizes(m * b) + [8 * m * b]:
-            if lib.wanted(m, b, f, n):
+        for n in batch_sizes(m, b, f) + [8 * m * b]:
+            if lib.wanted(m, b, f, walk, n):
                 held = max(held, n)
-            most = lib.most(m, b, f, n)
+            most = lib.most(m, b, f, walk, n)
             assert held <= most <= n and (most == 0) == (held == 0), (m, b, f, n)
-            assert most == 0 or lib.wanted(m, b, f, most), (m, b, f, n)
+            if most:
+                assert lib.wanted(m, b, f, walk, most), (m, b, f, n)
+                # smaller batches than the least that does go direct, all of them
+                least = lib.least(m, b, f, walk, most)
+                assert lib.wanted(m, b, f, walk, least), (m, b, f, n)
+                assert not lib.wanted(m, b, f, walk, least - 1), (m, b, f, n)
+                assert all(lib.wanted(m, b, f, walk, k) == (k >= least)
+                           for k in batch_sizes(m, b, f) if k <= most), (m, b, f, n)
