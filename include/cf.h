@@ -99,7 +99,9 @@ uint64_t cf_table_bytes(const cf_params *params);
  * queries, deletes and whole-table kernels (one key per thread up to that,
  * then grid-stride) and 128 per compute unit for inserts.  The environment
  * variable CF_GRID_PER_CU (1..1024), read here, sets both caps to that many
- * blocks per compute unit for this filter; results do not depend on it. */
+ * blocks per compute unit for this filter; results do not depend on it.
+ * CF_INSERT_PASS_KEYS (2^16..2^27), read here, bounds the passes of
+ * partitioned inserts (see cf_insert) and with them their workspace. */
 cf_status cf_create(const cf_params *params, cf_filter **out);
 
 /* As cf_create, with the table in caller-owned device memory: d_table
@@ -135,7 +137,8 @@ cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
  * of table per key from 2^19 keys, 8 from 2^20, 16 from 2^21 and 24 from 2^22
  * (32 on tables of 2 GiB) for 16-bit fingerprints and the breadth-first
  * search; less for other widths and the random walk, and from 2^20 keys for
- * 32-bit fingerprints (2^21 with b = 32).  They run in passes of up to 2^27 keys: keys
+ * 32-bit fingerprints (2^21 with b = 32).  They run in passes of up to 2^27 keys
+ * (CF_INSERT_PASS_KEYS): keys
  * are grouped by part of the table and placed part by part, all in their
  * first bucket, then those left over in their second, then the eviction
  * searches run, whose draws come from a key's index, bucket and fingerprint

@@ -139,6 +139,7 @@ struct cf_filter {
     int grid_cap;         // blocks of the query, delete and whole-table launches
     int insert_grid_cap;  // blocks of an insert launch
     bool may_partition;   // false: the caller fixed the launch shape
+    uint64_t pass_keys;   // most keys of a partitioned pass
     char *bulk;           // workspace of the partitioned insert
     uint64_t bulk_bytes;
     bool bulk_captured;   // a graph may hold pointers into it
@@ -223,9 +224,9 @@ bool capturing(hipStream_t s) {
     return cap != hipStreamCaptureStatusNone;
 }
 
-// Whether the workspace has room for passes of min(n, kMaxBulkKeys) keys.
+// Whether the workspace has room for a batch's passes.
 bool bulk_held(const cf_filter *f, uint64_t n) {
-    return bulk_plan(f, std::min(n, cfk::kMaxBulkKeys)).bytes <= f->bulk_bytes;
+    return bulk_plan(f, std::min(n, f->pass_keys)).bytes <= f->bulk_bytes;
 }
 
 // Gives the workspace back, or keeps it until cf_destroy for the graphs that
@@ -245,7 +246,7 @@ void bulk_drop(cf_filter *f) {
 // Makes that room; false if there is none to be had (the caller then inserts
 // directly), which includes a stream under capture.
 bool bulk_reserve(cf_filter *f, uint64_t n, hipStream_t s) {
-    const uint64_t want = bulk_plan(f, std::min(n, cfk::kMaxBulkKeys)).bytes;
+    const uint64_t want = bulk_plan(f, std::min(n, f->pass_keys)).bytes;
     if (want <= f->bulk_bytes) return true;
     if (capturing(s)) return false;
     (void)hipDeviceSynchronize();
@@ -284,7 +285,7 @@ cf_status reserve_scratch(cf_filter *f, uint64_t n, uint64_t bulk, hipStream_t s
 // Insert n keys in passes of equal size; the workspace is reserved.
 cf_status bulk_insert(cf_filter *f, const uint64_t *keys, uint64_t n, uint8_t *okv,
                       uint32_t *kicks, hipStream_t s) {
-    const uint64_t passes = (n + cfk::kMaxBulkKeys - 1) / cfk::kMaxBulkKeys;
+    const uint64_t passes = (n + f->pass_keys - 1) / f->pass_keys;
     const cfk::LostLog log{f->lost_bucket, f->lost_tag, f->lost_cap};
     if (!f->bulk_captured) f->bulk_captured = capturing(s);
     for (uint64_t k = 0, lo = 0; k < passes; ++k) {
@@ -410,6 +411,11 @@ static cf_status create_impl(const cf_params *params, void *table, cf_filter **o
             f->grid_cap = f->insert_grid_cap = cus * v;
             f->may_partition = false;
         }
+    }
+    f->pass_keys = cfk::kMaxBulkKeys;
+    if (const char *env = getenv("CF_INSERT_PASS_KEYS")) {
+        const long long v = atoll(env);
+        if (v >= (1 << 16) && uint64_t(v) < f->pass_keys) f->pass_keys = uint64_t(v);
     }
     f->owns_table = table == nullptr;
     f->table = table;
