@@ -119,9 +119,12 @@ cf_status cf_create_in(const cf_params *params, void *d_table, uint64_t nbytes,
 cf_status cf_destroy(cf_filter *flt);
 
 /* Reserve internal scratch for batches of up to max_batch keys so that later
- * inserts of that size do not allocate: the eviction queue, and where such a
- * batch would go partitioned (see cf_insert) the workspace of 20 to
- * 40 bytes per key of the largest that would, or of 2^27.  Synchronous. */
+ * inserts of that size do not allocate: the eviction queue (4 bytes per key of
+ * the largest that goes direct, up to 8 beyond 2^23) and, where a smaller batch
+ * would go partitioned (see cf_insert), the workspace of the largest that
+ * would: 21 to 35 bytes per key of a pass, 31 to 46 for 32-bit fingerprints
+ * (more if CF_INSERT_PASS_KEYS makes passes shorter).  Where both cannot be
+ * had, the queue alone.  Synchronous. */
 cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
 
 /* Alg. 1 + Sec. 4.6.1: insert n keys.  d_ok (nullable): uint8[n], 1 if the

@@ -121,6 +121,8 @@ def test_every_plan_that_is_run_addresses_what_is_there(lib, b, f, walk):
                         (p.o_list, 8 * lists), (p.o_list32, wide * lists), (p.o_ovl, 4 * size)]
                 for (o, s), (nxt, _) in zip(need, need[1:] + [(p.bytes, 0)]):
                     assert o % 256 == 0 and o + s <= nxt, at
+                # the bytes per key that cf.h states
+                assert (31 if f == 32 else 21) * size <= p.bytes <= (46 if f == 32 else 35) * size, at
                 # the overflow list's eviction queue lies over the first level's
                 # entries, and a part's list holds every entry the part can get
                 assert 8 * n1 >= 4 * size, at
