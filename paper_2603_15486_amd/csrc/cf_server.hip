@@ -305,9 +305,16 @@ cf_status launch(cf_server *s, int slot_idx, std::vector<Req *> &take) {
     } else {
         std::vector<cfs::Request> &rq = s->batch;
         rq.clear();
-        for (const Req *r : take) rq.push_back({r->fid, r->op, r->keys, r->results, r->n});
-        st = cfs::requests_lane(s->set, lane_of(slot_idx), rq.data(), uint32_t(rq.size()),
-                                sl.h_tab, sl.d_tab, sl.stream);
+        for (const Req *r : take) {
+            int attached = 0;
+            (void)cf_set_attached(s->set, r->fid, &attached);
+            if (attached) rq.push_back({r->fid, r->op, r->keys, r->results, r->n});
+            else  // detached through the server's set: invalid operations, as in a mixed batch
+                fill_kernel<<<grid_for(r->n), kBlock, 0, sl.stream>>>(r->results, r->n, 0xFF);
+        }
+        if (!rq.empty())
+            st = cfs::requests_lane(s->set, lane_of(slot_idx), rq.data(), uint32_t(rq.size()),
+                                    sl.h_tab, sl.d_tab, sl.stream);
     }
     if (st == CF_OK && hipGetLastError() != hipSuccess) st = fail(CF_EDEVICE, "batch launch failed");
     // Every path records the slot's event and hands the requests to the slot,
