@@ -160,7 +160,8 @@ def kernel_summary(args):
 def _set_batch_spans(trace):
     """Filter-set batches in a kernel trace: every run of set kernels from one
     partition (or persistent) launch to the next, grouped by its launch
-    sequence (kernel per launch, and how many hardware queues the batch used),
+    sequence (kernel per launch, how many hardware queues the batch used, and
+    the blocks of its first launch: batches of other sizes and chunks apart),
     with the median span from the first start to the last end, the median gap
     to the batch before, and each launch's median duration."""
     import re
@@ -175,7 +176,8 @@ def _set_batch_spans(trace):
         if not m or m.group(1) not in short:
             continue
         name = short[m.group(1)] + (f" b{m.group(4)}" if m.group(4) else "")
-        ev.append((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), name, r["Queue_Id"]))
+        blocks = int(r.get("Grid_Size_X") or 0) // int(r.get("Workgroup_Size_X") or 1)
+        ev.append((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), name, r["Queue_Id"], blocks))
     ev.sort()
     batches, cur = [], None
     for e in ev:
@@ -193,17 +195,19 @@ def _set_batch_spans(trace):
         t0, t1 = b[0][0], max(x[1] for x in b)
         gap = (t0 - prev_end) / 1e3 if prev_end is not None else None
         prev_end = t1
-        sig = (tuple(x[2] for x in b), len({x[3] for x in b}))
+        sig = (tuple(x[2] for x in b), len({x[3] for x in b}), b[0][4])
         groups.setdefault(sig, []).append(((t1 - t0) / 1e3, gap, [(x[1] - x[0]) / 1e3 for x in b]))
     med = lambda v: sorted(v)[len(v) // 2]
     out = ["", "filter-set batches (from the kernel trace): launch sequence, hardware queues used, "
                "batches seen, median span and gap before, median duration per launch (us)"]
-    for (names, nq), rows in sorted(groups.items(), key=lambda kv: -len(kv[1])):
+    for (names, nq, blocks), rows in sorted(groups.items(), key=lambda kv: -len(kv[1]))[:24]:
         if len(rows) < 3:
             continue
         gaps = [g for _, g, _ in rows if g is not None]
         per = [med([d[k] for _, _, d in rows]) for k in range(len(names))]
-        out.append(f"  {len(rows):>5} batches, {nq} queue(s): span {med([r[0] for r in rows]):.1f}, "
+        out.append(f"  {len(rows):>5} batches, {nq} queue(s)" +
+                   (f", {blocks} blocks" if blocks else "") +
+                   f": span {med([r[0] for r in rows]):.1f}, "
                    f"gap {med(gaps) if gaps else 0:.1f}")
         out.append("        " + ", ".join(f"{n} {d:.1f}" for n, d in zip(names, per)))
     return out if len(out) > 2 else []  # no filter-set batches in this trace
