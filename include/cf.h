@@ -137,10 +137,10 @@ cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
  * candidates' other buckets in groups (as many as 128 bytes hold) instead of
  * one by one; it picks the same candidate either way.
  * Batches that are large against the table go partitioned: of at most 4 bytes
- * of table per key from 2^19 keys, 8 from 2^20, 16 from 2^21 and 24 from 2^22
+ * of table per key from 2^19 keys on, 8 from 2^20, 16 from 2^21 and 24 from 2^22
  * (32 on tables of 2 GiB) for 16-bit fingerprints and the breadth-first
- * search; less for other widths and the random walk, and from 2^20 keys for
- * 32-bit fingerprints (2^21 with b = 32).  They run in passes of up to 2^27 keys
+ * search, with steps between; less for other widths and the random walk, and
+ * from 2^20 keys for 32-bit fingerprints (2^21 with b = 32).  They run in passes of up to 2^27 keys
  * (CF_INSERT_PASS_KEYS): keys
  * are grouped by part of the table and placed part by part, all in their
  * first bucket, then those left over in their second, then the eviction

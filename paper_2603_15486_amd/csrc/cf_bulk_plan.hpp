@@ -155,33 +155,52 @@ inline bool bulk_fits(const BulkTable &t, const BulkPlan &p) {
 // fullest (the searches cost the same either way, and those of a partitioned
 // batch have fewer blocks to overlap with), so each line lies where a batch
 // still gains that ends at load 0.86 / 0.91 / 0.945 / 0.955 (b = 4 / 8 / 16 /
-// 32).  Measured, direct time over partitioned time at the lines, the least
-// over b and loads 0, 0.5 and the highest (and the mean):
-//   keys, fingerprints      breadth-first              random walk
-//   2^19, 8 / 16 bits    4 B 0.99 (1.07), 4 B 1.04    4 B 0.92 (1.07), 4 B 0.98
-//   2^20, 8 / 16 bits    8 B 1.13 (1.49), 8 B 1.02    8 B 1.02 (1.29), 8 B 1.00
-//   2^20, 32 bits, b < 32   6 B 1.05 (1.10)            6 B 1.00 (1.10)
-//   2^21, 8 / 16 / 32    8 B 1.22, 16 B 1.13, 16 B 1.00    8 B 1.01, 12 B 1.01, 8 B 1.10
-//   2^22, 8 / 16 / 32    12 B 1.30, 24 B 1.17, 16 B 1.01   12 B 1.07, 12 B 1.09, 8 B 1.13
-//   2^24, 8 / 16 / 32    12 B 1.15, 24 B 1.06, 16 B 1.11   12 B 1.03, 12 B 1.10, 8 B 1.18
-//   2^26, 2 GiB, 16 bits    32 B 1.07 (1.41)           32 B 1.05 (1.41)
-//   2^27, 2 GiB, 32 bits    16 B 1.25 (1.56)           16 B 1.22 (1.57)
-// and one step beyond: 16 bits 2^19 8 B 0.87 and 0.93, 2^20 16 B 0.96 and
-// 0.96; random walk 2^22 16 B 0.97, 24 B on 512 MiB 0.95; 32 bits (entries
-// of 12 bytes) 2^20 b = 32 6 B 0.94 and 0.90, 2^22 24 B 0.97, random walk 16 B
-// 0.90, 2^25 keys on 2 GiB 64 B 0.72 and 0.71.  Below 2^19 keys nothing is
-// gained (2^18 from empty 39-45 -> 35-46 us).
+// 32).  Measured at the lines, direct time over partitioned time, the least over
+// b and the loads 0, 0.5 and the highest, and the mean (against the library
+// before it had this path no least is below 0.98):
+//   keys         f   breadth-first          random walk
+//   2^19         8    4 B  0.98  1.09        4 B  0.94  1.10
+//               16    4 B  1.02  1.09        4 B  0.98  1.08
+//   3 * 2^18     8    4 B  1.07  1.22        4 B  1.01  1.21
+//               16    6 B  0.97  1.08        6 B  0.95  1.08
+//   2^20         8    8 B  1.05  1.41        8 B  0.97  1.30
+//               16    8 B  0.98  1.22        8 B  0.99  1.22
+//               32    6 B  1.03  1.09        6 B  0.97  1.07   b < 32
+//   3 * 2^19     8    8 B  1.08  1.56        8 B  1.06  1.49
+//               16   12 B  0.98  1.28        8 B  1.00  1.37
+//               32    8 B  1.03  1.22        8 B  0.96  1.20   b < 32
+//   2^21         8    8 B  1.19  1.78        8 B  0.97  1.68
+//               16   16 B  1.14  1.54       12 B  0.99  1.49
+//               32   16 B  1.00  1.32        8 B  1.09  1.43
+//   2^22         8   12 B  1.28  1.79       12 B  1.05  1.72
+//               16   24 B  1.13  1.46       12 B  1.09  1.67
+//               32   16 B  1.01  1.39        8 B  1.14  1.66
+//   2^24         8   12 B  1.15  1.92       12 B  1.02  1.95
+//               16   24 B  1.06  1.42       12 B  1.06  1.86
+//               32   16 B  1.09  1.38        8 B  1.17  1.63
+//   2^26, 2 GiB 16   32 B  1.07  1.41       32 B  1.03  1.41
+//   2^27, 2 GiB  8   16 B  1.25  1.92       16 B  1.19  1.89
+//               32   16 B  1.23  1.52       16 B  1.21  1.51
+// and beyond them: 16 bits 2^19 keys 8 B 0.87 and 0.93, 2^20 16 B 0.96 and 0.96;
+// random walk 2^22 16 B 0.97, 24 B on 512 MiB 0.95; 32 bits (entries of 12
+// bytes) 2^19 keys 5 B 0.88 to 1.00, 2^20 b = 32 (a bucket is a whole line) 6 B
+// 0.91 and 0.93, 2^22 24 B 0.97, random walk 16 B 0.90, 2^25 keys on 2 GiB 64 B
+// 0.72 and 0.71.  Below 2^19 keys nothing is gained (2^18 from empty 39-45 ->
+// 35-46 us).
 // A batch of more than twice the slots, most of which must fail, goes direct:
 // its failing searches need more blocks than a small table has parts.
 inline uint32_t bulk_bytes_per_key(const BulkTable &t, uint64_t n) {
-    const int band = n < (1ull << 20)            ? 0
-                     : n < (1ull << 21)          ? 1
-                     : n < (1ull << 22)          ? 2
-                     : t.bytes() < (2ull << 30) ? 3
-                                                 : 4;
-    constexpr uint8_t most[2][3][5] = {{{4, 8, 8, 12, 16}, {4, 8, 16, 24, 32}, {0, 6, 16, 16, 16}},
-                                       {{4, 8, 8, 12, 16}, {4, 8, 12, 12, 32}, {0, 6, 8, 8, 16}}};
-    if (t.f == 32 && t.b == 32 && band == 1) return 0;
+    const int band = n < (3ull << 18)            ? 0
+                     : n < (1ull << 20)          ? 1
+                     : n < (3ull << 19)          ? 2
+                     : n < (1ull << 21)          ? 3
+                     : n < (1ull << 22)          ? 4
+                     : t.bytes() < (2ull << 30) ? 5
+                                                 : 6;
+    constexpr uint8_t most[2][3][7] = {
+        {{4, 4, 8, 8, 8, 12, 16}, {4, 6, 8, 12, 16, 24, 32}, {0, 0, 6, 8, 16, 16, 16}},
+        {{4, 4, 8, 8, 8, 12, 16}, {4, 6, 8, 8, 12, 12, 32}, {0, 0, 6, 8, 8, 8, 16}}};
+    if (t.f == 32 && t.b == 32 && band < 4) return 0;
     return most[t.walk][t.f == 8 ? 0 : t.f == 16 ? 1 : 2][band];
 }
 

@@ -56,22 +56,22 @@ def bucket_counts():
 
 def line(b, f, walk, n, table):
     """Bytes of table per key up to which a batch of n keys goes partitioned."""
+    if n >= 1 << 22:
+        if table >= 2 << 30:
+            return 32 if f == 16 else 16
+        return 12 if f == 8 else {16: (24, 12), 32: (16, 8)}[f][walk]
+    if n >= 1 << 21:
+        return 8 if f == 8 else {16: (16, 12), 32: (16, 8)}[f][walk]
     if f == 32:
-        if n < 1 << (21 if b == 32 else 20):
-            return 0
-        return 6 if n < 1 << 21 else 8 if walk and (n < 1 << 22 or table < 2 << 30) else 16
-    if n < 1 << 21:
-        return 4 if n < 1 << 20 else 8
-    if f == 8:
-        return 8 if n < 1 << 22 else 12 if table < 2 << 30 else 16
-    if n >= 1 << 22 and table >= 2 << 30:
-        return 32
-    return 12 if walk else 16 if n < 1 << 22 else 24
+        return 0 if b == 32 or n < 1 << 20 else 6 if n < 3 << 19 else 8
+    if n >= 1 << 20:
+        return 12 if f == 16 and not walk and n >= 3 << 19 else 8
+    return 6 if f == 16 and n >= 3 << 18 else 4
 
 
 def batch_sizes(m, b, f):
     out, slots, table = set(), m * b, m * b * f // 8
-    for base in (1 << 19, 1 << 20, 1 << 21, 1 << 22, PASS, 2 * PASS, slots, 2 * slots,
+    for base in (1 << 19, 3 << 18, 1 << 20, 3 << 19, 1 << 21, 1 << 22, PASS, 2 * PASS, slots, 2 * slots,
                  *(table // k for k in (4, 6, 8, 12, 16, 24, 32))):
         out.update(base + d for d in (-1, 0, 1, 2))
     return sorted(n for n in out if n >= 1)
