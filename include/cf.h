@@ -140,9 +140,9 @@ cf_status cf_reserve(cf_filter *flt, uint64_t max_batch);
  * of table per key from 2^19 keys on, 8 from 2^20, 16 from 2^21 and 24 from 2^22
  * (32 on tables of 2 GiB) for 16-bit fingerprints and the breadth-first
  * search, with steps between; less for other widths and the random walk, and
- * from 2^20 keys for 32-bit fingerprints (2^21 with b = 32).  They run in passes of up to 2^27 keys
- * (CF_INSERT_PASS_KEYS): keys
- * are grouped by part of the table and placed part by part, all in their
+ * from 2^20 keys for 32-bit fingerprints (2^21 with b = 32).  They run in
+ * passes of up to 2^27 keys (CF_INSERT_PASS_KEYS): keys are grouped by part
+ * of the table and placed part by part, all in their
  * first bucket, then those left over in their second, then the eviction
  * searches run, whose draws come from a key's index, bucket and fingerprint
  * instead of the key.  The workspace stays with the filter until
